@@ -30,8 +30,9 @@ def _hipcc():
 
 
 def generate():
-    subprocess.run([sys.executable, os.path.join(CSRC, "gen_expansions.py"),
-                    os.path.join(CSRC, "generated", "expansions.h")], check=True)
+    for name in ("expansions", "harmonics"):
+        subprocess.run([sys.executable, os.path.join(CSRC, f"gen_{name}.py"),
+                        os.path.join(CSRC, "generated", f"{name}.h")], check=True)
 
 
 def build(jobs: int = 8, verbose: bool = False) -> str:

@@ -1747,6 +1747,7 @@ void adjoint_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
     momsub = t->momsub.as<T>();
   }
   if constexpr (sizeof(T) == 4) {
+    weighted_fp32(ctx, t);
     momw = t->mom32.as<T>();
   } else {
     weighted_fp64(ctx, t);

@@ -17,6 +17,17 @@ constexpr int kMaxLevel = 21;      // deepest cell level
 constexpr int kMaxP = 8;           // highest expansion order
 constexpr int kWave = 64;
 
+// Newtonian multipoles under Plummer softening: a cell's expansion with its
+// degrees l >= 2 taken as those of the unsoftened kernel (harmonic, no trace
+// parts; the radial powers keep the softened distance) differs from the full
+// one by at most kNewtonC eps^2 b^2 / (d - b)^4 of the monopole's field for a
+// mass at distance b from the centre and a sink at distance d, and a cell is a
+// positive sum of those. The expansion kernels take them where that is below
+// one FP32 (FP64) epsilon; kNewtonCH is the same constant for the field's
+// derivatives (against the monopole's).
+constexpr double kNewtonC = 2.6;
+constexpr double kNewtonCH = 9.0;
+
 __host__ __device__ constexpr int nm(int p) { return (p + 1) * (p + 2) * (p + 3) / 6; }
 // moment slot of (a, b, c): by order, then a descending, then b descending
 __host__ __device__ constexpr int mslot(int a, int b, int c) {
@@ -25,6 +36,16 @@ __host__ __device__ constexpr int mslot(int a, int b, int c) {
 }
 // padded stride (floats) of one cell's FP32 expansion coefficients
 __host__ __device__ constexpr int nm_pad(int p) { return (nm(p) + 3) & ~3; }
+
+// padded rows of one cell's solid-harmonic coefficients (gradient form): the
+// harmonic part and the trace part
+__host__ __device__ constexpr int harm_stride(int p) { return (1 + 3 * p * p + 3) & ~3; }
+__host__ __device__ constexpr int trace_stride(int p) {
+  int n = 0;
+  for (int o = 2; o <= p; ++o)
+    for (int k = 1; 2 * k <= o; ++k) n += o == 2 * k ? 1 : 3 * (2 * (o - 2 * k) - 1);
+  return (n + 3) & ~3;
+}
 
 // ---------------------------------------------------------------------------
 // Errors
@@ -199,7 +220,12 @@ struct hot_tree {
   // moments
   int p = -1;
   hot::DBuf mom64, mom32, momw64;
-  bool momw64_valid = false;
+  bool mom32_valid = false, momw64_valid = false;
+  // solid-harmonic coefficients of the expansion (harmonic and trace parts,
+  // gen_harmonics.py), FP32 built with the moments, FP64 on first use; c_reach:
+  // (kNewtonC trace / mass)^(1/4) per cell, for the Newtonian-multipole rule
+  hot::DBuf hc32, tc32, hc64, tc64, c_reach;
+  bool harm64_valid = false;
   // P2P / M2P pair counts of the current lists (host copies)
   int64_t p2p_pairs = 0, m2p_pairs = 0;
   // lists
@@ -225,7 +251,7 @@ struct hot_tree {
   bool bg = false;
   int bg_width = 3;  // side of N(g) in group sides
   int64_t n_boxes = 0;
-  hot::DBuf m2p_sub, box_off, boxes, box_sign, momsub;
+  hot::DBuf m2p_sub, box_off, boxes, box_sign, momsub, hsub, tsub;
   // pair segments of the P2P lists (CSR per group, built with the lists):
   // consecutive entries with contiguous particle ranges (and one image) form
   // a run, cut at source-group boundaries into segments
@@ -288,7 +314,15 @@ void split_items(hot_ctx* ctx, hot_tree* t);
 void gather_sorted(hot_ctx* ctx, const hot_tree* t, const double* pos, const double* mass,
                    double* spos, double* smass, int check_mass);
 void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, int p);
+// weighted scaled Cartesian moments (the adjoint's expansion kernels), on first use
+void weighted_fp32(hot_ctx* ctx, hot_tree* t);
 void weighted_fp64(hot_ctx* ctx, hot_tree* t);
+// solid-harmonic coefficients: of the matter in FP64 (hc64, tc64); of the
+// matter minus each cell's uniform cube of the mean density (hsub, tsub); of
+// the negated cubes per unit density (the caller's arrays)
+void harmonics_fp64(hot_ctx* ctx, hot_tree* t);
+void harmonics_sub(hot_ctx* ctx, hot_tree* t, bool fp64);
+void harmonics_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* h, void* tr);
 void build_lists(hot_ctx* ctx, hot_tree* t, double theta, int direct_max);
 void build_lists_err(hot_ctx* ctx, hot_tree* t, const double* mass, double tol, int p_max,
                      int direct_max);
@@ -304,9 +338,6 @@ void background_boxes(hot_ctx* ctx, hot_tree* t, const double* pos, double* acc)
 // their adjoint and that of the mean density (through every mass)
 void background_adjoint(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
                         double eps, int precision, const double* abar, double* xbar, double* mbar);
-// weighted scaled moments of every cell's uniform cube per unit density, negated
-// (C x nm_pad(p), FP32 or FP64)
-void weighted_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* out);
 // field (caller order, N x 3) of the flagged M2P entries' uniform cubes per
 // unit mean density, with the sign they enter the forces with
 void cube_field(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, double eps,

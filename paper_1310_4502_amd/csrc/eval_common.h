@@ -64,6 +64,15 @@ __device__ __forceinline__ T k1_hess(T v) {
   return hot_fma(v, hot_fma(v, T(72.1875), T(7.5)), T(3));
 }
 
+// compensated s += x * sc for sc an exact power of two (the product is exact)
+template <typename T>
+__device__ __forceinline__ void kahan_scaled(T& s, T& c, T x, T sc) {
+  const T y = hot_fma(x, sc, -c);
+  const T t = s + y;
+  c = (t - s) - y;
+  s = t;
+}
+
 template <typename T>
 __device__ __forceinline__ void kahan_add(T& s, T& c, T x) {
   const T y = x - c;
@@ -95,6 +104,110 @@ __global__ void k_offsets(const double* __restrict__ pos, const double* __restri
   o.z = (T)(z - c_centre[3 * gc + 2]);
   o.w = (T)m;
   off[i] = o;
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_max(T v) {
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) {
+    const T o = __shfl_xor(v, m);
+    v = o > v ? o : v;
+  }
+  return v;
+}
+
+// Bits of a value as 32-bit words, for the cross-lane builtins.
+template <typename T>
+struct Words {
+  static constexpr int n = sizeof(T) / 4;
+  unsigned w[n];
+};
+template <typename T>
+__device__ __forceinline__ T read_lane(T v, int lane) {
+  Words<T> a = __builtin_bit_cast(Words<T>, v);
+#pragma unroll
+  for (int i = 0; i < a.n; ++i) a.w[i] = __builtin_amdgcn_readlane(a.w[i], lane);
+  return __builtin_bit_cast(T, a);
+}
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp(T v) {
+  Words<T> a = __builtin_bit_cast(Words<T>, v);
+#pragma unroll
+  for (int i = 0; i < a.n; ++i) a.w[i] = __builtin_amdgcn_update_dpp(0, a.w[i], CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(T, a);
+}
+// sum of a over its lanes' partner half in the lower 32 lanes, of b in the upper
+template <typename T>
+__device__ __forceinline__ T fold32(T a, T b) {
+  Words<T> x = __builtin_bit_cast(Words<T>, a), y = __builtin_bit_cast(Words<T>, b);
+#pragma unroll
+  for (int i = 0; i < x.n; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x.w[i], y.w[i], false, false);
+    x.w[i] = r[0];
+    y.w[i] = r[1];
+  }
+  return __builtin_bit_cast(T, x) + __builtin_bit_cast(T, y);
+}
+// the same for neighbouring rows of 16 lanes: a in the even rows, b in the odd
+template <typename T>
+__device__ __forceinline__ T fold16(T a, T b) {
+  Words<T> x = __builtin_bit_cast(Words<T>, a), y = __builtin_bit_cast(Words<T>, b);
+#pragma unroll
+  for (int i = 0; i < x.n; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x.w[i], y.w[i], false, false);
+    x.w[i] = r[0];
+    y.w[i] = r[1];
+  }
+  return __builtin_bit_cast(T, x) + __builtin_bit_cast(T, y);
+}
+// Wavefront sums of four values at once, in 10 instructions instead of 24:
+// row r of 16 lanes ends with the sum of v[kFoldRow[r]], on all its lanes.
+template <typename T>
+__device__ __forceinline__ T fold4(const T* v) {
+  T t = fold16(fold32(v[0], v[1]), fold32(v[2], v[3]));
+  t += dpp<0xB1>(t);   // quad_perm(1,0,3,2)
+  t += dpp<0x4E>(t);   // quad_perm(2,3,0,1)
+  t += dpp<0x141>(t);  // row_half_mirror
+  t += dpp<0x140>(t);  // row_mirror
+  return t;
+}
+__device__ __forceinline__ int fold_row(int row) { return (row & 1) * 2 + (row >> 1); }  // 0 2 1 3
+
+// What the expansion kernels need to choose between a cell's Newtonian
+// multipoles and its full softened expansion (kNewtonC): the softening and
+// nq = (eps^2 / tolerance)^(1/4), tolerance one epsilon of the arithmetic.
+// c_reach carries kNewtonC; the derivative kernels fold (kNewtonCH /
+// kNewtonC)^(1/4) into nq.
+struct NewtonRule {
+  double eps, nq;
+  const double* bmax;   // per cell
+  const float* reach;   // per cell
+};
+template <typename T>
+inline NewtonRule newton_rule(const hot_tree* t, double eps, bool derivative) {
+  const double tol = sizeof(T) == 4 ? 0x1p-21 : 0x1p-50;
+  NewtonRule r;
+  r.eps = eps;
+  r.nq = sqrt(eps) * pow((derivative ? kNewtonCH / kNewtonC : 1.0) / tol, 0.25);
+  r.bmax = t->c_bmax.as<double>();
+  r.reach = t->c_reach.as<float>();
+  return r;
+}
+// d: distance of the nearest sink from the cell's centre. K1 is Newtonian
+// beyond its radius. sub: cube-subtracted moments, whose error is held to a
+// 256th of the tolerance against a full cell's mass (the subtracted moments
+// of a near-uniform cell are that much smaller than its mass); b and the
+// trace are then bounded by the cell's cube.
+template <int P, bool K1>
+__device__ __forceinline__ bool newton_ok(const NewtonRule& r, double d, int c, bool sub,
+                                          double side_c) {
+  if constexpr (K1) return d >= r.eps;
+  if (P < 2 || r.eps == 0.0) return true;
+  if (sub) {
+    // (kNewtonC * 1.5 * 256)^(1/4) s^(1/2), half diagonal 0.8661 s
+    return d >= 0.8661 * side_c + 5.623 * sqrt(side_c) * r.nq;
+  }
+  return d >= r.bmax[c] + (double)r.reach[c] * r.nq;
 }
 
 // Expansion coefficients of one cell, for a wavefront. Up to ~400 bytes they

@@ -10,6 +10,7 @@
 #include "common.h"
 #include "eval_common.h"
 #include "generated/expansions.h"
+#include "generated/harmonics.h"
 
 namespace hot {
 
@@ -254,41 +255,86 @@ __global__ void k_weighted_sub(const double* __restrict__ mom, int64_t C,
   out[c * stride + s] = (T)(kAlpha.w[s] * v);
 }
 
-// Weighted scaled moments of each cell's uniform cube per unit density, with
-// the minus sign they are subtracted with: -w_alpha L^3 2^(-3 level - |alpha|)
-// prod_d 1 / (alpha_d + 1) for all alpha_d even, else 0.
-template <typename T>
-__global__ void k_weighted_cube(int64_t C, const int8_t* __restrict__ c_level, double vol, int p,
-                                T* __restrict__ out) {
-  const int nmv = nm(p), stride = nm_pad(p);
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t c;
-  int s;
-  row_col(t, stride, c, s);
-  if (c >= C) return;
-  double v = 0.0;
-  if (s < nmv) {
-    const int a = kAlpha.a[s], b = kAlpha.b[s], cc = kAlpha.c[s];
-    if (!((a | b | cc) & 1))
-      v = -kAlpha.w[s] * ldexp(vol, -3 * (int)c_level[c] - (a + b + cc)) /
-          ((double)(a + 1) * (double)(b + 1) * (double)(cc + 1));
+// Solid-harmonic coefficients of every cell (gen_harmonics.py), one thread per
+// cell and order, the orders of a run of cells on one XCD so that its L2 holds
+// their moments. SRC 0: the matter's moments; 1: minus the cell's uniform cube
+// of the mean density; 2: the negated cube per unit density (vol = L^3).
+// reach (SRC 0, nullable): (kNewtonC trace / mass)^(1/4), trace the sum of
+// m |x - c|^2.
+template <typename T, int SRC, int N>
+__device__ __forceinline__ void harm_order(const double* __restrict__ mom, int64_t c, int lev,
+                                           double inv_side, double vol, int p,
+                                           T* __restrict__ h, T* __restrict__ t,
+                                           float* __restrict__ reach) {
+  constexpr int K = (N + 1) * (N + 2) / 2, OFF = N * (N + 1) * (N + 2) / 6;
+  const double sc = pow2_pow(ldexp(inv_side, lev), N);
+  double M[K];
+  const double* row = mom + c * nm(p) + OFF;
+#pragma unroll
+  for (int k = 0; k < K; ++k) M[k] = SRC == 2 ? 0.0 : row[k] * sc;
+  if constexpr (SRC != 0 && N % 2 == 0) {
+    const double cm = SRC == 1 ? ldexp(mom[0], -3 * lev - N) : ldexp(vol, -3 * lev - N);
+    int k = 0;
+#pragma unroll
+    for (int a = N; a >= 0; --a)
+#pragma unroll
+      for (int b = N - a; b >= 0; --b, ++k) {
+        const int cc = N - a - b;
+        if (!((a | b | cc) & 1)) M[k] -= cm / ((double)(a + 1) * (double)(b + 1) * (double)(cc + 1));
+      }
   }
-  out[c * stride + s] = (T)v;
+  if constexpr (N == 0) harm_grad_coef0<T>(M, 1.0, h, t);
+  if constexpr (N == 1) harm_grad_coef1<T>(M, 1.0, h, t);
+  if constexpr (N == 2) harm_grad_coef2<T>(M, 1.0, h, t);
+  if constexpr (N == 3) harm_grad_coef3<T>(M, 1.0, h, t);
+  if constexpr (N == 4) harm_grad_coef4<T>(M, 1.0, h, t);
+  if constexpr (N == 5) harm_grad_coef5<T>(M, 1.0, h, t);
+  if constexpr (N == 6) harm_grad_coef6<T>(M, 1.0, h, t);
+  if constexpr (N == 7) harm_grad_coef7<T>(M, 1.0, h, t);
+  if constexpr (N == 8) harm_grad_coef8<T>(M, 1.0, h, t);
+  if constexpr (SRC == 0 && N == 2) {
+    if (reach) {
+      const double m0 = mom[c * nm(p)];
+      const double tr = row[0] + row[3] + row[5];
+      // rounded up
+      reach[c] = m0 > 0.0 && tr > 0.0 ? (float)sqrt(sqrt(kNewtonC * tr / m0)) * 1.000001f : 0.0f;
+    }
+  }
+}
+
+template <typename T, int SRC>
+__global__ __launch_bounds__(kB) void k_harmonics(const double* __restrict__ mom, int64_t C,
+                                                  const int8_t* __restrict__ c_level,
+                                                  double inv_side, double vol, int p,
+                                                  T* __restrict__ h, T* __restrict__ t,
+                                                  float* __restrict__ reach) {
+  int64_t run;
+  int ord;
+  order_block(p, run, ord);
+  const int64_t c = run * kB + threadIdx.x;
+  if (c >= C) return;
+  const int lev = (int)c_level[c];
+  T* hr = h + c * harm_stride(p);
+  T* tr = t + c * trace_stride(p);
+#define HOT_HARM(N) \
+  case N: harm_order<T, SRC, N>(mom, c, lev, inv_side, vol, p, hr, tr, reach); break;
+  switch (ord) {
+    HOT_HARM(0) HOT_HARM(1) HOT_HARM(2) HOT_HARM(3) HOT_HARM(4)
+    HOT_HARM(5) HOT_HARM(6) HOT_HARM(7) HOT_HARM(8)
+  }
+#undef HOT_HARM
+}
+
+template <typename T, int SRC>
+void launch_harmonics(hot_ctx* ctx, hot_tree* t, T* h, T* tr, float* reach) {
+  const int64_t C = t->n_cells;
+  const double vol = (t->side * t->side) * t->side;
+  k_harmonics<T, SRC><<<order_grid(grid_for(C, kB), t->p), kB, 0, ctx->stream>>>(
+      t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, vol, t->p, h, tr, reach);
+  HOT_CHECK_LAUNCH();
 }
 
 }  // namespace
-
-void weighted_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* out) {
-  const int64_t tot = t->n_cells * nm_pad(t->p);
-  const double vol = (t->side * t->side) * t->side;
-  if (fp64)
-    k_weighted_cube<double><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-        t->n_cells, t->c_level.as<int8_t>(), vol, t->p, static_cast<double*>(out));
-  else
-    k_weighted_cube<float><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-        t->n_cells, t->c_level.as<int8_t>(), vol, t->p, static_cast<float*>(out));
-  HOT_CHECK_LAUNCH();
-}
 
 void weighted_sub(hot_ctx* ctx, hot_tree* t, bool fp64) {
   const int64_t C = t->n_cells;
@@ -304,6 +350,11 @@ void weighted_sub(hot_ctx* ctx, hot_tree* t, bool fp64) {
         t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p,
         t->momsub.as<float>());
   HOT_CHECK_LAUNCH();
+}
+
+static void alloc_harmonics(hot_ctx* ctx, hot_tree* t, DBuf& h, DBuf& tr, size_t elem) {
+  h.alloc(ctx, (size_t)t->n_cells * harm_stride(t->p) * elem);
+  tr.alloc(ctx, std::max<size_t>(16, (size_t)t->n_cells * trace_stride(t->p) * elem));
 }
 
 void gather_sorted(hot_ctx* ctx, const hot_tree* t, const double* pos, const double* mass,
@@ -339,15 +390,49 @@ void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* m
                                t->mom64.as<double>());
     HOT_CHECK_LAUNCH();
   }
-  // scaled, weighted FP32 copy for the mixed-precision expansion kernels
-  t->mom32.alloc(ctx, (size_t)C * nm_pad(p) * sizeof(float));
-  const int64_t tot = C * nm_pad(p);
-  k_weighted<float><<<grid_for(tot, kB), kB, 0, st>>>(t->mom64.as<double>(), C,
-                                                      t->c_level.as<int8_t>(), 1.0 / t->side, p,
-                                                      t->mom32.as<float>());
-  HOT_CHECK_LAUNCH();
+  t->mom32_valid = false;
   t->momw64_valid = false;
   t->p = p;
+  // the expansion kernels' coefficients
+  alloc_harmonics(ctx, t, t->hc32, t->tc32, sizeof(float));
+  t->c_reach.alloc(ctx, C * sizeof(float));
+  launch_harmonics<float, 0>(ctx, t, t->hc32.as<float>(), t->tc32.as<float>(),
+                             t->c_reach.as<float>());
+  t->harm64_valid = false;
+}
+
+void harmonics_fp64(hot_ctx* ctx, hot_tree* t) {
+  if (t->harm64_valid) return;
+  alloc_harmonics(ctx, t, t->hc64, t->tc64, sizeof(double));
+  launch_harmonics<double, 0>(ctx, t, t->hc64.as<double>(), t->tc64.as<double>(), nullptr);
+  t->harm64_valid = true;
+}
+
+void harmonics_sub(hot_ctx* ctx, hot_tree* t, bool fp64) {
+  alloc_harmonics(ctx, t, t->hsub, t->tsub, fp64 ? sizeof(double) : sizeof(float));
+  if (fp64)
+    launch_harmonics<double, 1>(ctx, t, t->hsub.as<double>(), t->tsub.as<double>(), nullptr);
+  else
+    launch_harmonics<float, 1>(ctx, t, t->hsub.as<float>(), t->tsub.as<float>(), nullptr);
+}
+
+void harmonics_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* h, void* tr) {
+  if (fp64)
+    launch_harmonics<double, 2>(ctx, t, static_cast<double*>(h), static_cast<double*>(tr), nullptr);
+  else
+    launch_harmonics<float, 2>(ctx, t, static_cast<float*>(h), static_cast<float*>(tr), nullptr);
+}
+
+void weighted_fp32(hot_ctx* ctx, hot_tree* t) {
+  if (t->mom32_valid) return;
+  const int64_t C = t->n_cells;
+  const int p = t->p;
+  t->mom32.alloc(ctx, (size_t)C * nm_pad(p) * sizeof(float));
+  const int64_t tot = C * nm_pad(p);
+  k_weighted<float><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
+      t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p, t->mom32.as<float>());
+  HOT_CHECK_LAUNCH();
+  t->mom32_valid = true;
 }
 
 void weighted_fp64(hot_ctx* ctx, hot_tree* t) {
