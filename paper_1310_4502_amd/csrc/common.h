@@ -46,6 +46,19 @@ __host__ __device__ constexpr int trace_stride(int p) {
     for (int k = 1; 2 * k <= o; ++k) n += o == 2 * k ? 1 : 3 * (2 * (o - 2 * k) - 1);
   return (n + 3) & ~3;
 }
+// the same for the second-derivative form
+__host__ __device__ constexpr int hess_stride(int p) {
+  return p == 0 ? 4 : p == 1 ? 4 : (4 + 5 * (p - 1) * (p - 1) + 3) & ~3;
+}
+__host__ __device__ constexpr int hess_trace_stride(int p) {
+  int n = 0;
+  for (int o = 2; o <= p; ++o)
+    for (int k = 1; 2 * k <= o; ++k) {
+      const int l = o - 2 * k;
+      n += l == 0 ? 1 : l == 1 ? 3 : 5 * (2 * l - 3);
+    }
+  return (n + 3) & ~3;
+}
 
 // ---------------------------------------------------------------------------
 // Errors
@@ -219,8 +232,7 @@ struct hot_tree {
   hot::DBuf g_cell, g_first, g_count;
   // moments
   int p = -1;
-  hot::DBuf mom64, mom32, momw64;
-  bool mom32_valid = false, momw64_valid = false;
+  hot::DBuf mom64;
   // solid-harmonic coefficients of the expansion (harmonic and trace parts,
   // gen_harmonics.py), FP32 built with the moments, FP64 on first use; c_reach:
   // (kNewtonC trace / mass)^(1/4) per cell, for the Newtonian-multipole rule
@@ -247,11 +259,11 @@ struct hot_tree {
   // background subtraction (periodic lists only): per M2P entry 1 if its
   // cell's uniform cube is subtracted; per group (CSR) the boxes whose exact
   // uniform field enters with sign +1 / -1 (lo[3], hi[3] each); the
-  // subtracted weighted moments built at evaluation
+  // subtracted coefficients built at evaluation
   bool bg = false;
   int bg_width = 3;  // side of N(g) in group sides
   int64_t n_boxes = 0;
-  hot::DBuf m2p_sub, box_off, boxes, box_sign, momsub, hsub, tsub;
+  hot::DBuf m2p_sub, box_off, boxes, box_sign, hsub, tsub;
   // pair segments of the P2P lists (CSR per group, built with the lists):
   // consecutive entries with contiguous particle ranges (and one image) form
   // a run, cut at source-group boundaries into segments
@@ -314,15 +326,15 @@ void split_items(hot_ctx* ctx, hot_tree* t);
 void gather_sorted(hot_ctx* ctx, const hot_tree* t, const double* pos, const double* mass,
                    double* spos, double* smass, int check_mass);
 void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, int p);
-// weighted scaled Cartesian moments (the adjoint's expansion kernels), on first use
-void weighted_fp32(hot_ctx* ctx, hot_tree* t);
-void weighted_fp64(hot_ctx* ctx, hot_tree* t);
 // solid-harmonic coefficients: of the matter in FP64 (hc64, tc64); of the
 // matter minus each cell's uniform cube of the mean density (hsub, tsub); of
 // the negated cubes per unit density (the caller's arrays)
 void harmonics_fp64(hot_ctx* ctx, hot_tree* t);
 void harmonics_sub(hot_ctx* ctx, hot_tree* t, bool fp64);
 void harmonics_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* h, void* tr);
+// second-derivative form (sink-side adjoint) into the caller's buffers: of the
+// matter, or (sub) of the matter minus each cell's cube
+void harmonics_hess(hot_ctx* ctx, hot_tree* t, bool fp64, bool sub, DBuf& h, DBuf& tr);
 void build_lists(hot_ctx* ctx, hot_tree* t, double theta, int direct_max);
 void build_lists_err(hot_ctx* ctx, hot_tree* t, const double* mass, double tol, int p_max,
                      int direct_max);
@@ -330,9 +342,6 @@ void build_lists_periodic(hot_ctx* ctx, hot_tree* t, double theta, int direct_ma
 void build_lists_periodic_bs(hot_ctx* ctx, hot_tree* t, double theta, int direct_max, int width);
 void build_lists_periodic_err(hot_ctx* ctx, hot_tree* t, const double* mass, double tol,
                               int p_max, int direct_max);
-// weighted scaled moments minus those of each cell's uniform cube of the mean
-// density (into t->momsub, FP32 or FP64 as asked)
-void weighted_sub(hot_ctx* ctx, hot_tree* t, bool fp64);
 // exact background fields of the listed boxes, minus N(g), plus the near zone
 void background_boxes(hot_ctx* ctx, hot_tree* t, const double* pos, double* acc);
 // their adjoint and that of the mean density (through every mass)

@@ -19,12 +19,9 @@
 // (group, entry) and rounded to FP32. Expansions run on coordinates scaled by
 // the source cell side s (a power of two): R/s, eps/s and the weighted moments
 // M_alpha / s^|alpha| are all O(1), and the result is rescaled by s^-2.
-#include <type_traits>
-
 #include "common.h"
 #include "eval_common.h"
-#include "expansion_q.h"
-#include "generated/expansions.h"
+#include "expand.h"
 
 namespace hot {
 namespace {
@@ -215,391 +212,6 @@ void k_p2p(
   }
 }
 
-// Expansion terms of one work item, one sink per lane.
-//
-// Per 64 list entries, one entry per lane prepares what the wavefront shares
-// (the scaled centre difference from FP64 centres, the softening, whether the
-// Newtonian multipoles serve every sink of the item) and leaves it in LDS; the
-// entries are then evaluated one after another, the cell's coefficients read at
-// wavefront-uniform addresses (scalar loads, operands of the multiply-adds).
-//
-// MIXQ: every entry carries its own order q <= P (m2p_q), error-bound lists.
-// PER: every entry carries the image of its cell (periodic lists).
-// BG: background subtraction; an entry flagged in m2p_sub takes its cell's
-// coefficients minus those of its uniform cube (hsub, tsub).
-template <int P, typename T, bool POT, bool MIXQ, bool PER, bool BG, bool K1>
-__global__ __launch_bounds__(kB) void k_m2p(
-    const int2* __restrict__ items, int64_t n_items, const int64_t* __restrict__ m2p_off,
-    const int32_t* __restrict__ m2p, const int8_t* __restrict__ m2p_q,
-    const int8_t* __restrict__ m2p_img, double side, const int8_t* __restrict__ m2p_sub,
-    const T* __restrict__ hsub, const T* __restrict__ tsub, const int8_t* __restrict__ c_level,
-    const int32_t* __restrict__ g_first, const int32_t* __restrict__ g_count,
-    const int32_t* __restrict__ g_cell, const double* __restrict__ c_centre,
-    const V4<T>* __restrict__ off, const T* __restrict__ hc, const T* __restrict__ tc,
-    double inv_side, NewtonRule rule, T* __restrict__ state) {
-  __shared__ V4<T> s_rec[kWavesPerBlock][64];
-  __shared__ T s_e2[kWavesPerBlock][64];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t it = (int64_t)blockIdx.x * kWavesPerBlock + w;
-  if (it >= n_items) return;
-  const int2 item = items[it];
-  const int g = uniform_i32(item.x);
-  const int gend = g_first[g] + g_count[g];
-  const int i = item.y + lane;
-  const bool active = i < gend;
-  const int gc = g_cell[g];
-  const double cgx = c_centre[3 * gc], cgy = c_centre[3 * gc + 1], cgz = c_centre[3 * gc + 2];
-  V4<T> me;
-  me.x = me.y = me.z = me.w = T(0);
-  T sx = 0, sy = 0, sz = 0, sp = 0, cx = 0, cy = 0, cz = 0, cp = 0;
-  if (active) {
-    me = off[i];
-    const T* st = state + (int64_t)i * 8;
-    sx = st[0];
-    sy = st[1];
-    sz = st[2];
-    sp = st[3];
-    cx = st[4];
-    cy = st[5];
-    cz = st[6];
-    cp = st[7];
-  }
-  // the item's sinks lie within bs of the group's centre (idle lanes at it)
-  const double bs = sqrt((double)wave_max(hot_fma(me.x, me.x, hot_fma(me.y, me.y, me.z * me.z)))) *
-                    1.000001;
-  const int64_t e0 = m2p_off[g], e1 = m2p_off[g + 1];
-  for (int64_t eb = e0; eb < e1; eb += 64) {
-    const int nb = e1 - eb < 64 ? (int)(e1 - eb) : 64;
-    int cl = 0, fl = 0;  // cell; bit 0 Newtonian, bit 1 subtracted, order above
-    V4<T> rec;
-    rec.x = rec.y = rec.z = rec.w = T(0);
-    T e2 = T(0);
-    if (lane < nb) {
-      cl = m2p[eb + lane];
-      double nx = c_centre[3 * cl], ny = c_centre[3 * cl + 1], nz = c_centre[3 * cl + 2];
-      if (PER) {
-        double tx, ty, tz;
-        image_shift((int)m2p_img[eb + lane], side, tx, ty, tz);
-        nx += tx;
-        ny += ty;
-        nz += tz;
-      }
-      const bool sub = BG && m2p_sub[eb + lane];
-      const int lev = (int)c_level[cl];
-      const double inv_s = ldexp(inv_side, lev);
-      const double dx = cgx - nx, dy = cgy - ny, dz = cgz - nz;
-      rec.x = (T)(dx * inv_s);
-      rec.y = (T)(dy * inv_s);
-      rec.z = (T)(dz * inv_s);
-      rec.w = (T)inv_s;
-      const double es = rule.eps * inv_s;
-      const bool newton = newton_ok<P, K1>(rule, sqrt(dx * dx + dy * dy + dz * dz) - bs, cl, sub,
-                                           1.0 / inv_s);
-      e2 = K1 && newton ? T(0) : (T)(es * es);
-      fl = (newton ? 1 : 0) | (sub ? 2 : 0);
-      if (MIXQ) fl |= (int)m2p_q[eb + lane] << 2;
-    }
-    __builtin_amdgcn_wave_barrier();
-    s_rec[w][lane] = rec;
-    s_e2[w][lane] = e2;
-    __builtin_amdgcn_wave_barrier();
-    V4<T> nr = s_rec[w][0];
-    T ne2 = s_e2[w][0];
-    for (int k = 0; k < nb; ++k) {
-      const V4<T> r = nr;
-      const T ke2 = ne2;
-      nr = s_rec[w][(k + 1) & 63];
-      ne2 = s_e2[w][(k + 1) & 63];
-      const int c = __builtin_amdgcn_readlane(cl, k);
-      const int f = __builtin_amdgcn_readlane(fl, k);
-      const bool sub = BG && (f & 2);
-      const T* C = (sub ? hsub : hc) + (int64_t)c * harm_stride(P);
-      const T* D = (sub ? tsub : tc) + (int64_t)c * trace_stride(P);
-      const T X = hot_fma(me.x, r.w, r.x);
-      const T Y = hot_fma(me.y, r.w, r.y);
-      const T Z = hot_fma(me.z, r.w, r.z);
-      T ax = 0, ay = 0, az = 0, ph = 0;
-      if (MIXQ)
-        harm_fwd_q<P, T, POT, K1>(f >> 2, f & 1, X, Y, Z, ke2, C, D, ax, ay, az, ph);
-      else
-        harm_fwd<P, T, POT, K1>(f & 1, X, Y, Z, ke2, C, D, ax, ay, az, ph);
-      const T sa = -(r.w * r.w);
-      kahan_scaled(sx, cx, ax, sa);
-      kahan_scaled(sy, cy, ay, sa);
-      kahan_scaled(sz, cz, az, sa);
-      if (POT) kahan_scaled(sp, cp, ph, r.w);
-    }
-  }
-  if (active) {
-    T* st = state + (int64_t)i * 8;
-    st[0] = sx;
-    st[1] = sy;
-    st[2] = sz;
-    st[3] = sp;
-    st[4] = cx;
-    st[5] = cy;
-    st[6] = cz;
-    st[7] = cp;
-  }
-}
-
-// Expansion terms of an item of few sinks, one cell per lane: 64 list entries
-// are taken at a time, each lane keeps its cell's coefficients in registers, and
-// the item's sinks are swept uniformly, four at a time, so that every lane works
-// whatever the number of sinks (one sink per lane leaves most of a wavefront
-// idle there). A sink's 64 terms are summed across the lanes in a fixed tree
-// and enter its compensated sums with one add per batch.
-//
-// The entries are queued by class, so that batches are full: those served by
-// their Newtonian multipoles, and those that need the full softened expansion
-// (its harmonic and trace parts in two sweeps where the registers do not hold
-// the coefficients of both).
-template <int P, typename T>
-struct CellLane {
-  static constexpr int kWords = sizeof(T) / 4;
-  static constexpr int kHarm = harm_stride(P), kTrace = trace_stride(P);
-  // registers for coefficients: FP32 to order 8, FP64, whose temporaries take
-  // twice the room, to order 4 (at order 5 the spills cost more than the lanes
-  // gain: 2.2 against 1.2 ms)
-  static constexpr int kRoom = sizeof(T) == 4 ? 200 : 140;
-  static constexpr bool fits = kHarm * kWords <= kRoom;
-  static constexpr bool one_sweep = (kHarm + kTrace) * kWords <= (sizeof(T) == 4 ? 80 : 140);
-  static constexpr int waves = sizeof(T) == 8 ? (P <= 1 ? 4 : 2) : P <= 4 ? 4 : P <= 6 ? 3 : 2;
-};
-
-template <typename T, int N>
-__device__ __forceinline__ void load_row(const T* __restrict__ src, T* dst) {
-  // rows are padded to 16-byte multiples
-  constexpr int V = 16 / sizeof(T);
-#pragma unroll
-  for (int k = 0; k < N / V; ++k) {
-    const uint4 v = reinterpret_cast<const uint4*>(src)[k];
-    struct Quad {
-      T t[V];
-    };
-    const Quad q = __builtin_bit_cast(Quad, v);
-#pragma unroll
-    for (int j = 0; j < V; ++j) dst[k * V + j] = q.t[j];
-  }
-}
-
-template <int P, typename T, bool POT, bool PER, bool K1>
-__global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(CellLane<P, T>::waves))) void k_m2p_cl(
-    const int2* __restrict__ items, int64_t n_items, const int64_t* __restrict__ m2p_off,
-    const int32_t* __restrict__ m2p, const int8_t* __restrict__ m2p_img, double side,
-    const int8_t* __restrict__ c_level, const int32_t* __restrict__ g_first,
-    const int32_t* __restrict__ g_count, const int32_t* __restrict__ g_cell,
-    const double* __restrict__ c_centre, const V4<T>* __restrict__ off,
-    const T* __restrict__ hc, const T* __restrict__ tc, double inv_side, NewtonRule rule,
-    T* __restrict__ state) {
-  using CL = CellLane<P, T>;
-  constexpr int HS = harm_stride(P), TS = trace_stride(P);
-  constexpr int NC = POT ? 4 : 3;  // components
-  constexpr int Q = 128;           // queue room: fewer than 64 left over + 64 new
-  __shared__ V4<T> q_rec[2][Q];    // scaled centre difference, 1 / side
-  __shared__ T q_e2[2][Q];
-  __shared__ int q_cell[2][Q];
-  const int lane = threadIdx.x;
-  const int64_t it = blockIdx.x;
-  if (it >= n_items) return;
-  const int2 item = items[it];
-  const int g = uniform_i32(item.x);
-  const int ns = uniform_i32(min(64, g_first[g] + g_count[g] - item.y));
-  const int gc = g_cell[g];
-  const double cgx = c_centre[3 * gc], cgy = c_centre[3 * gc + 1], cgz = c_centre[3 * gc + 2];
-  // lane l holds sink l (lanes past the last one repeat the first)
-  const V4<T> me = off[item.y + (lane < ns ? lane : 0)];
-  const double bs = sqrt((double)wave_max(hot_fma(me.x, me.x, hot_fma(me.y, me.y, me.z * me.z)))) *
-                    1.000001;
-  // the compensated sums of sink 4 j + fold_row(row) on lane j of that row
-  const int si = 4 * (lane & 15) + fold_row(lane >> 4);
-  T sum[NC], com[NC];
-#pragma unroll
-  for (int d = 0; d < NC; ++d) sum[d] = com[d] = T(0);
-  if (si < ns) {
-    const T* st = state + (int64_t)(item.y + si) * 8;
-#pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      sum[d] = st[d];
-      com[d] = st[4 + d];
-    }
-  }
-  // One sweep over the item's sinks: F(X, Y, Z, a) adds a sink's terms of this
-  // lane's cell. got: each sink's sums on its lane.
-  auto sweep = [&](const V4<T>& r, T sa, T sp, T* got, auto F) {
-#pragma unroll
-    for (int d = 0; d < NC; ++d) got[d] = T(0);
-    for (int j = 0; 4 * j < ns; ++j) {
-      T v[NC][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = 4 * j + u;
-        T a[4] = {T(0), T(0), T(0), T(0)};
-        F(hot_fma(read_lane(me.x, k), r.w, r.x), hot_fma(read_lane(me.y, k), r.w, r.y),
-          hot_fma(read_lane(me.z, k), r.w, r.z), a);
-        v[0][u] = a[0] * sa;
-        v[1][u] = a[1] * sa;
-        v[2][u] = a[2] * sa;
-        if constexpr (POT) v[3][u] = a[3] * sp;
-        __builtin_amdgcn_sched_barrier(0);  // one sink's temporaries at a time
-      }
-#pragma unroll
-      for (int d = 0; d < NC; ++d) {
-        const T t = fold4(v[d]);
-        got[d] = (lane & 15) == j ? t : got[d];
-      }
-    }
-  };
-  // a batch of n <= 64 entries of one class from the head of its queue
-  auto batch = [&](auto full_c, int n) {
-    constexpr bool FULL = decltype(full_c)::value;
-    const int slot = lane < n ? lane : 0;
-    const V4<T> r = q_rec[FULL][slot];
-    const T e2 = q_e2[FULL][slot];
-    const int64_t c = q_cell[FULL][slot];
-    const T sa = lane < n ? -(r.w * r.w) : T(0), sp = lane < n ? r.w : T(0);
-    T got[NC];
-    if constexpr (!FULL || CL::one_sweep) {
-      T C[HS], D[FULL && TS > 0 ? TS : 4];
-      load_row<T, HS>(hc + c * HS, C);
-      if constexpr (FULL) load_row<T, TS>(tc + c * TS, D);
-      sweep(r, sa, sp, got, [&](T X, T Y, T Z, T* a) {
-        if constexpr (FULL)
-          harm_fwd_full<P, T, POT, K1>(X, Y, Z, e2, C, D, a[0], a[1], a[2], a[3]);
-        else
-          harm_fwd_newton<P, T, POT>(X, Y, Z, e2, C, a[0], a[1], a[2], a[3]);
-      });
-    } else {
-      T more[NC];
-      {
-        T C[HS];
-        load_row<T, HS>(hc + c * HS, C);
-        sweep(r, sa, sp, got, [&](T X, T Y, T Z, T* a) {
-          harm_fwd_full_h<P, T, POT, K1>(X, Y, Z, e2, C, a[0], a[1], a[2], a[3]);
-        });
-      }
-      {
-        T D[TS > 0 ? TS : 4];
-        load_row<T, TS>(tc + c * TS, D);
-        sweep(r, sa, sp, more, [&](T X, T Y, T Z, T* a) {
-          harm_fwd_full_t<P, T, POT, K1>(X, Y, Z, e2, D, a[0], a[1], a[2], a[3]);
-        });
-      }
-#pragma unroll
-      for (int d = 0; d < NC; ++d) got[d] += more[d];
-    }
-#pragma unroll
-    for (int d = 0; d < NC; ++d) kahan_add(sum[d], com[d], got[d]);
-  };
-  // n entries one after another, a sink per lane as in k_m2p: cheaper than a
-  // batch when there are fewer entries than sinks
-  auto single = [&](auto full_c, int n) {
-    constexpr bool FULL = decltype(full_c)::value;
-    T fs[NC], fc[NC];
-#pragma unroll
-    for (int d = 0; d < NC; ++d) fs[d] = fc[d] = T(0);
-    for (int k = 0; k < n; ++k) {
-      const V4<T> r = q_rec[FULL][k];
-      const T e2 = q_e2[FULL][k];
-      const int64_t c = uniform_i32(q_cell[FULL][k]);
-      T a[4] = {T(0), T(0), T(0), T(0)};
-      const T X = hot_fma(me.x, r.w, r.x), Y = hot_fma(me.y, r.w, r.y), Z = hot_fma(me.z, r.w, r.z);
-      if constexpr (FULL)
-        harm_fwd_full<P, T, POT, K1>(X, Y, Z, e2, hc + c * HS, tc + c * TS, a[0], a[1], a[2], a[3]);
-      else
-        harm_fwd_newton<P, T, POT>(X, Y, Z, e2, hc + c * HS, a[0], a[1], a[2], a[3]);
-      const T sa = -(r.w * r.w);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) kahan_scaled(fs[d], fc[d], a[d], sa);
-      if constexpr (POT) kahan_scaled(fs[3], fc[3], a[3], r.w);
-    }
-    // to the lanes that keep the sinks' sums (every lane takes part)
-#pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      const T o = __shfl(fs[d], si), oc = __shfl(fc[d], si);
-      kahan_add(sum[d], com[d], o);
-      com[d] += oc;
-    }
-  };
-  auto flush = [&](int which, int n) {
-    const bool few = n < ns;
-    if (which == 0)
-      few ? single(std::false_type{}, n) : batch(std::false_type{}, n);
-    else
-      few ? single(std::true_type{}, n) : batch(std::true_type{}, n);
-  };
-  int have[2] = {0, 0};
-  const int64_t e0 = m2p_off[g], e1 = m2p_off[g + 1];
-  for (int64_t eb = e0; eb < e1; eb += 64) {
-    const bool in = eb + lane < e1;
-    bool newton = false;
-    int cl = 0;
-    V4<T> rec;
-    rec.x = rec.y = rec.z = rec.w = T(0);
-    T e2 = T(0);
-    if (in) {
-      cl = m2p[eb + lane];
-      double nx = c_centre[3 * cl], ny = c_centre[3 * cl + 1], nz = c_centre[3 * cl + 2];
-      if (PER) {
-        double tx, ty, tz;
-        image_shift((int)m2p_img[eb + lane], side, tx, ty, tz);
-        nx += tx;
-        ny += ty;
-        nz += tz;
-      }
-      const double inv_s = ldexp(inv_side, (int)c_level[cl]);
-      const double dx = cgx - nx, dy = cgy - ny, dz = cgz - nz;
-      rec.x = (T)(dx * inv_s);
-      rec.y = (T)(dy * inv_s);
-      rec.z = (T)(dz * inv_s);
-      rec.w = (T)inv_s;
-      const double es = rule.eps * inv_s;
-      newton = newton_ok<P, K1>(rule, sqrt(dx * dx + dy * dy + dz * dz) - bs, cl, false, 0.0);
-      e2 = K1 && newton ? T(0) : (T)(es * es);
-    }
-    const uint64_t mn = __ballot(in && newton), mf = __ballot(in && !newton);
-    if (in) {
-      const int q = newton ? 0 : 1;
-      const int at = have[q] + __popcll((newton ? mn : mf) & lanemask_lt());
-      q_rec[q][at] = rec;
-      q_e2[q][at] = e2;
-      q_cell[q][at] = cl;
-    }
-    have[0] += __popcll(mn);
-    have[1] += __popcll(mf);
-    __syncthreads();
-    const bool last = eb + 64 >= e1;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      // a full batch, and at the end what is left
-      while (have[q] >= 64 || (last && have[q] > 0)) {
-        const int n = have[q] < 64 ? have[q] : 64;
-        flush(q, n);
-        have[q] -= n;
-        __syncthreads();
-        if (lane < have[q]) {  // fewer than 64 remain: move them to the head
-          const V4<T> r = q_rec[q][64 + lane];
-          const T f = q_e2[q][64 + lane];
-          const int c = q_cell[q][64 + lane];
-          q_rec[q][lane] = r;
-          q_e2[q][lane] = f;
-          q_cell[q][lane] = c;
-        }
-        __syncthreads();
-      }
-    }
-  }
-  if (si < ns) {
-    T* st = state + (int64_t)(item.y + si) * 8;
-#pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      st[d] = sum[d];
-      st[4 + d] = com[d];
-    }
-  }
-}
-
 // split of the work items by sink count (at most 32, or more)
 __global__ void k_item_flags(const int2* __restrict__ items, int64_t n_items,
                              const int32_t* __restrict__ g_first,
@@ -655,70 +267,6 @@ void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1
     go(k_p2p<T, POT, true, false>);
 }
 
-// The cells' coefficients an evaluation reads.
-template <typename T>
-struct Coef {
-  const T *h, *t, *hsub, *tsub;  // harmonic and trace parts; cube-subtracted ones
-};
-
-template <int P, typename T, bool POT, bool K1>
-void launch_m2p_p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, const Coef<T>& cf, double eps,
-                  T* state) {
-  const unsigned grid = grid_for(t->n_items, kWavesPerBlock);
-  const NewtonRule rule = newton_rule<T>(t, eps, false);
-  auto go = [&](auto kern) {
-    kern<<<grid, kB, 0, ctx->stream>>>(
-        t->items.as<int2>(), t->n_items, t->m2p_off.as<int64_t>(), t->m2p.as<int32_t>(),
-        t->m2p_q.as<int8_t>(), t->m2p_img.as<int8_t>(), t->side, t->m2p_sub.as<int8_t>(), cf.hsub,
-        cf.tsub, t->c_level.as<int8_t>(), t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
-        t->g_cell.as<int32_t>(), t->c_centre.as<double>(), off, cf.h, cf.t, 1.0 / t->side, rule,
-        state);
-    HOT_CHECK_LAUNCH();
-  };
-  if (t->list_p >= 0) {
-    if (t->periodic)
-      go(k_m2p<P, T, POT, true, true, false, K1>);
-    else
-      go(k_m2p<P, T, POT, true, false, false, K1>);
-  } else if (CellLane<P, T>::fits && !t->bg && t->n_items_small * 10 >= t->n_items) {
-    // theta lists with many part-empty items: those of at most 32 sinks with a
-    // cell per lane, the others as usual
-    if (t->n_items_big > 0) {
-      auto kb = t->periodic ? k_m2p<P, T, POT, false, true, false, K1>
-                            : k_m2p<P, T, POT, false, false, false, K1>;
-      kb<<<grid_for(t->n_items_big, kWavesPerBlock), kB, 0, ctx->stream>>>(
-          t->items_big.as<int2>(), t->n_items_big, t->m2p_off.as<int64_t>(), t->m2p.as<int32_t>(),
-          t->m2p_q.as<int8_t>(), t->m2p_img.as<int8_t>(), t->side, t->m2p_sub.as<int8_t>(),
-          cf.hsub, cf.tsub, t->c_level.as<int8_t>(), t->g_first.as<int32_t>(),
-          t->g_count.as<int32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(), off, cf.h,
-          cf.t, 1.0 / t->side, rule, state);
-      HOT_CHECK_LAUNCH();
-    }
-    if (t->n_items_small > 0) {
-      if constexpr (CellLane<P, T>::fits) {
-        auto ks = t->periodic ? k_m2p_cl<P, T, POT, true, K1> : k_m2p_cl<P, T, POT, false, K1>;
-        ks<<<(unsigned)t->n_items_small, 64, 0, ctx->stream>>>(
-            t->items_small.as<int2>(), t->n_items_small, t->m2p_off.as<int64_t>(),
-            t->m2p.as<int32_t>(), t->m2p_img.as<int8_t>(), t->side, t->c_level.as<int8_t>(),
-            t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), t->g_cell.as<int32_t>(),
-            t->c_centre.as<double>(), off, cf.h, cf.t, 1.0 / t->side, rule, state);
-        HOT_CHECK_LAUNCH();
-      }
-    }
-  } else if (t->periodic) {
-    // potentials are refused with background subtraction: no variant for them
-    if constexpr (!POT) {
-      if (t->bg) {
-        go(k_m2p<P, T, POT, false, true, true, K1>);
-        return;
-      }
-    }
-    go(k_m2p<P, T, POT, false, true, false, K1>);
-  } else {
-    go(k_m2p<P, T, POT, false, false, false, K1>);
-  }
-}
-
 }  // namespace
 
 // Items of at most 32 sinks and the others, listed apart (built with the tree)
@@ -748,30 +296,13 @@ void split_items(hot_ctx* ctx, hot_tree* t) {
 
 namespace {
 
-template <typename T, bool POT, bool K1>
-void launch_m2p_k(hot_ctx* ctx, hot_tree* t, const V4<T>* off, const Coef<T>& cf, double eps,
-                  T* state) {
-  switch (t->p) {
-    case 0: launch_m2p_p<0, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 1: launch_m2p_p<1, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 2: launch_m2p_p<2, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 3: launch_m2p_p<3, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 4: launch_m2p_p<4, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 5: launch_m2p_p<5, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 6: launch_m2p_p<6, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 7: launch_m2p_p<7, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    case 8: launch_m2p_p<8, T, POT, K1>(ctx, t, off, cf, eps, state); break;
-    default: invalid("p out of range");
-  }
-}
-
 template <typename T, bool POT>
 void launch_m2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, const Coef<T>& cf, double eps,
                 bool k1, T* state) {
   if (k1)
-    launch_m2p_k<T, POT, true>(ctx, t, off, cf, eps, state);
+    launch_expand_p<T, FieldOp<T, POT, true>>(ctx, t, off, nullptr, cf, eps, state);
   else
-    launch_m2p_k<T, POT, false>(ctx, t, off, cf, eps, state);
+    launch_expand_p<T, FieldOp<T, POT, false>>(ctx, t, off, nullptr, cf, eps, state);
 }
 
 template <typename T>

@@ -579,13 +579,18 @@ def gen_sink_newton(P):
     return L
 
 
-def gen_sink_full(P):
+def gen_sink_full(P, ks=None):
     """The same for any softening, every (l, k) block with its own radial
     functions g, g' = -(2l+1) g_{l+1,k}, g'' = (2l+1)(2l+3) g_{l+2,k}:
-      g = g A b + g' (R (b.grad H) + (b.R) grad H + b H) + g'' R (b.R) H."""
+      g = g A b + g' (R (b.grad H) + (b.R) grad H + b H) + g'' R (b.R) H.
+    ks as in gen_fwd_full."""
+    def want(k):
+        return ks is None or (k > 0) == (ks > 0)
+
     L = ["  const T x = X, y = Y, z = Z;"]
     emit_radial(L, P + 2)
-    emit_g(L, lambda k: P - 2 * k + 2, P)
+    if ks != 0:
+        emit_g(L, lambda k: P - 2 * k + 2, P)
 
     def g(l, k):
         return f"f{l}" if k == 0 else f"gh{l}_{k}"
@@ -593,12 +598,16 @@ def gen_sink_full(P):
     L += ["  const T xb = hot_fma(x, bx, hot_fma(y, by, z * bz));",
           "  T al = T(0), be = T(0);"]
     for k in range(P // 2 + 1):
+        if not want(k):
+            continue
         c = f"C[0]" if k == 0 else f"D[{off_th(0, k)}]"
         L.append(f"  al = hot_fma({c}, -{g(1, k)}, al); "
                  f"be = hot_fma({c} * xb, T(3.0) * {g(2, k)}, be);")
     L.append("  T Ux = T(0), Uy = T(0), Uz = T(0);")
     if P >= 1:
         for k in range((P - 1) // 2 + 1):
+            if not want(k):
+                continue
             arr, off = ("C", off_hh(1)) if k == 0 else ("D", off_th(1, k))
             c = [f"{arr}[{off + i}]" for i in range(3)]
             L += ["  {",
@@ -613,9 +622,12 @@ def gen_sink_full(P):
         L.append("  T " + ", ".join(f"A{a}{h} = T(0)" for a in "0123" for h in HN) + ";")
     for l in range(2, P + 1):
         deg = l - 2
+        kl = [k for k in range((P - l) // 2 + 1) if want(k)]
+        if not kl:
+            continue
         if deg >= 1:
             emit_basis(L, deg, "rho")
-        for k in range((P - l) // 2 + 1):
+        for k in kl:
             arr, off = ("C", off_hh(l)) if k == 0 else ("D", off_th(l, k))
             t = f"{l}_{k}"
             emit_row(L, [f"h{h}" for h in HN], arr, off, deg, 5, t)
@@ -715,6 +727,11 @@ def main(path):
                      "__device__ __forceinline__ void harm_sink_full(T X, T Y, T Z, T e2, "
                      "const T* __restrict__ C, const T* __restrict__ D, T bx, T by, T bz, T& gx, "
                      "T& gy, T& gz) {"], gen_sink_full)
+    for part, arr in enumerate("CD"):
+        dispatch(parts, ["template <int P, typename T, bool K1>",
+                         f"__device__ __forceinline__ void harm_sink_full_{'ht'[part]}(T X, T Y, "
+                         f"T Z, T e2, const T* __restrict__ {arr}, T bx, T by, T bz, T& gx, T& gy, "
+                         "T& gz) {"], lambda P, part=part: gen_sink_full(P, part))
     dispatch(parts, ["template <int P, typename T>",
                      "__device__ __forceinline__ void harm_cell_newton(T X, T Y, T Z, T e2, T bx, "
                      "T by, T bz, T* row) {"], gen_cell_newton)

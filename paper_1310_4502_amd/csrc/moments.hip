@@ -204,64 +204,13 @@ __global__ __launch_bounds__(kB) void k_m2m(int64_t c0, int64_t c1, const int32_
   }
 }
 
-template <typename T>
-__global__ void k_weighted(const double* __restrict__ mom, int64_t C,
-                           const int8_t* __restrict__ c_level, double inv_side, int p,
-                           T* __restrict__ out) {
-  const int nmv = nm(p), stride = nm_pad(p);
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t c;
-  int s;
-  row_col(t, stride, c, s);
-  if (c >= C) return;
-  if (s >= nmv) {
-    out[c * stride + s] = T(0);
-    return;
-  }
-  const int order = kAlpha.a[s] + kAlpha.b[s] + kAlpha.c[s];
-  const double sc = pow2_pow(ldexp(inv_side, (int)c_level[c]), order);
-  out[c * stride + s] = (T)(kAlpha.w[s] * (mom[c * nmv + s] * sc));
-}
-
-// The same weighted scaled moments with each cell's uniform cube of the mean
-// density taken off (background subtraction). Scaled by the cell side s, the
-// raw moments of a cube of mass m_c are m_c prod_d 2^(-alpha_d) / (alpha_d + 1)
-// for all alpha_d even (zero otherwise), and m_c = M_total 2^(-3 level): the
-// mean density M_total / L^3 (M_total the root's monopole) times s^3.
-template <typename T>
-__global__ void k_weighted_sub(const double* __restrict__ mom, int64_t C,
-                               const int8_t* __restrict__ c_level, double inv_side, int p,
-                               T* __restrict__ out) {
-  const int nmv = nm(p), stride = nm_pad(p);
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t c;
-  int s;
-  row_col(t, stride, c, s);
-  if (c >= C) return;
-  if (s >= nmv) {
-    out[c * stride + s] = T(0);
-    return;
-  }
-  const int a = kAlpha.a[s], b = kAlpha.b[s], cc = kAlpha.c[s];
-  const int order = a + b + cc;
-  const int lev = (int)c_level[c];
-  const double sc = pow2_pow(ldexp(inv_side, lev), order);
-  double v = mom[c * nmv + s] * sc;
-  if (!((a | b | cc) & 1)) {
-    const double cube = ldexp(mom[0], -3 * lev - order) /
-                        ((double)(a + 1) * (double)(b + 1) * (double)(cc + 1));
-    v -= cube;
-  }
-  out[c * stride + s] = (T)(kAlpha.w[s] * v);
-}
-
 // Solid-harmonic coefficients of every cell (gen_harmonics.py), one thread per
 // cell and order, the orders of a run of cells on one XCD so that its L2 holds
 // their moments. SRC 0: the matter's moments; 1: minus the cell's uniform cube
 // of the mean density; 2: the negated cube per unit density (vol = L^3).
-// reach (SRC 0, nullable): (kNewtonC trace / mass)^(1/4), trace the sum of
+// HESS: the second-derivative form. reach (SRC 0, nullable): (kNewtonC trace / mass)^(1/4), trace the sum of
 // m |x - c|^2.
-template <typename T, int SRC, int N>
+template <typename T, int SRC, bool HESS, int N>
 __device__ __forceinline__ void harm_order(const double* __restrict__ mom, int64_t c, int lev,
                                            double inv_side, double vol, int p,
                                            T* __restrict__ h, T* __restrict__ t,
@@ -283,15 +232,23 @@ __device__ __forceinline__ void harm_order(const double* __restrict__ mom, int64
         if (!((a | b | cc) & 1)) M[k] -= cm / ((double)(a + 1) * (double)(b + 1) * (double)(cc + 1));
       }
   }
-  if constexpr (N == 0) harm_grad_coef0<T>(M, 1.0, h, t);
-  if constexpr (N == 1) harm_grad_coef1<T>(M, 1.0, h, t);
-  if constexpr (N == 2) harm_grad_coef2<T>(M, 1.0, h, t);
-  if constexpr (N == 3) harm_grad_coef3<T>(M, 1.0, h, t);
-  if constexpr (N == 4) harm_grad_coef4<T>(M, 1.0, h, t);
-  if constexpr (N == 5) harm_grad_coef5<T>(M, 1.0, h, t);
-  if constexpr (N == 6) harm_grad_coef6<T>(M, 1.0, h, t);
-  if constexpr (N == 7) harm_grad_coef7<T>(M, 1.0, h, t);
-  if constexpr (N == 8) harm_grad_coef8<T>(M, 1.0, h, t);
+#define HOT_COEF(Q)                         \
+  if constexpr (N == Q) {                   \
+    if constexpr (HESS)                     \
+      harm_hess_coef##Q<T>(M, 1.0, h, t);   \
+    else                                    \
+      harm_grad_coef##Q<T>(M, 1.0, h, t);   \
+  }
+  HOT_COEF(0)
+  HOT_COEF(1)
+  HOT_COEF(2)
+  HOT_COEF(3)
+  HOT_COEF(4)
+  HOT_COEF(5)
+  HOT_COEF(6)
+  HOT_COEF(7)
+  HOT_COEF(8)
+#undef HOT_COEF
   if constexpr (SRC == 0 && N == 2) {
     if (reach) {
       const double m0 = mom[c * nm(p)];
@@ -302,7 +259,7 @@ __device__ __forceinline__ void harm_order(const double* __restrict__ mom, int64
   }
 }
 
-template <typename T, int SRC>
+template <typename T, int SRC, bool HESS>
 __global__ __launch_bounds__(kB) void k_harmonics(const double* __restrict__ mom, int64_t C,
                                                   const int8_t* __restrict__ c_level,
                                                   double inv_side, double vol, int p,
@@ -314,10 +271,10 @@ __global__ __launch_bounds__(kB) void k_harmonics(const double* __restrict__ mom
   const int64_t c = run * kB + threadIdx.x;
   if (c >= C) return;
   const int lev = (int)c_level[c];
-  T* hr = h + c * harm_stride(p);
-  T* tr = t + c * trace_stride(p);
+  T* hr = h + c * (HESS ? hess_stride(p) : harm_stride(p));
+  T* tr = t + c * (HESS ? hess_trace_stride(p) : trace_stride(p));
 #define HOT_HARM(N) \
-  case N: harm_order<T, SRC, N>(mom, c, lev, inv_side, vol, p, hr, tr, reach); break;
+  case N: harm_order<T, SRC, HESS, N>(mom, c, lev, inv_side, vol, p, hr, tr, reach); break;
   switch (ord) {
     HOT_HARM(0) HOT_HARM(1) HOT_HARM(2) HOT_HARM(3) HOT_HARM(4)
     HOT_HARM(5) HOT_HARM(6) HOT_HARM(7) HOT_HARM(8)
@@ -325,32 +282,16 @@ __global__ __launch_bounds__(kB) void k_harmonics(const double* __restrict__ mom
 #undef HOT_HARM
 }
 
-template <typename T, int SRC>
+template <typename T, int SRC, bool HESS = false>
 void launch_harmonics(hot_ctx* ctx, hot_tree* t, T* h, T* tr, float* reach) {
   const int64_t C = t->n_cells;
   const double vol = (t->side * t->side) * t->side;
-  k_harmonics<T, SRC><<<order_grid(grid_for(C, kB), t->p), kB, 0, ctx->stream>>>(
+  k_harmonics<T, SRC, HESS><<<order_grid(grid_for(C, kB), t->p), kB, 0, ctx->stream>>>(
       t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, vol, t->p, h, tr, reach);
   HOT_CHECK_LAUNCH();
 }
 
 }  // namespace
-
-void weighted_sub(hot_ctx* ctx, hot_tree* t, bool fp64) {
-  const int64_t C = t->n_cells;
-  const int p = t->p;
-  const int64_t tot = C * nm_pad(p);
-  t->momsub.alloc(ctx, (size_t)tot * (fp64 ? sizeof(double) : sizeof(float)));
-  if (fp64)
-    k_weighted_sub<double><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-        t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p,
-        t->momsub.as<double>());
-  else
-    k_weighted_sub<float><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-        t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p,
-        t->momsub.as<float>());
-  HOT_CHECK_LAUNCH();
-}
 
 static void alloc_harmonics(hot_ctx* ctx, hot_tree* t, DBuf& h, DBuf& tr, size_t elem) {
   h.alloc(ctx, (size_t)t->n_cells * harm_stride(t->p) * elem);
@@ -390,8 +331,6 @@ void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* m
                                t->mom64.as<double>());
     HOT_CHECK_LAUNCH();
   }
-  t->mom32_valid = false;
-  t->momw64_valid = false;
   t->p = p;
   // the expansion kernels' coefficients
   alloc_harmonics(ctx, t, t->hc32, t->tc32, sizeof(float));
@@ -423,29 +362,18 @@ void harmonics_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* h, void* tr) {
     launch_harmonics<float, 2>(ctx, t, static_cast<float*>(h), static_cast<float*>(tr), nullptr);
 }
 
-void weighted_fp32(hot_ctx* ctx, hot_tree* t) {
-  if (t->mom32_valid) return;
-  const int64_t C = t->n_cells;
-  const int p = t->p;
-  t->mom32.alloc(ctx, (size_t)C * nm_pad(p) * sizeof(float));
-  const int64_t tot = C * nm_pad(p);
-  k_weighted<float><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-      t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p, t->mom32.as<float>());
-  HOT_CHECK_LAUNCH();
-  t->mom32_valid = true;
-}
-
-void weighted_fp64(hot_ctx* ctx, hot_tree* t) {
-  if (t->momw64_valid) return;
-  const int64_t C = t->n_cells;
-  const int p = t->p;
-  t->momw64.alloc(ctx, (size_t)C * nm_pad(p) * sizeof(double));
-  const int64_t tot = C * nm_pad(p);
-  k_weighted<double><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
-      t->mom64.as<double>(), C, t->c_level.as<int8_t>(), 1.0 / t->side, p,
-      t->momw64.as<double>());
-  HOT_CHECK_LAUNCH();
-  t->momw64_valid = true;
+void harmonics_hess(hot_ctx* ctx, hot_tree* t, bool fp64, bool sub, DBuf& h, DBuf& tr) {
+  const size_t elem = fp64 ? sizeof(double) : sizeof(float);
+  h.alloc(ctx, (size_t)t->n_cells * hess_stride(t->p) * elem);
+  tr.alloc(ctx, std::max<size_t>(16, (size_t)t->n_cells * hess_trace_stride(t->p) * elem));
+  if (fp64 && sub)
+    launch_harmonics<double, 1, true>(ctx, t, h.as<double>(), tr.as<double>(), nullptr);
+  else if (fp64)
+    launch_harmonics<double, 0, true>(ctx, t, h.as<double>(), tr.as<double>(), nullptr);
+  else if (sub)
+    launch_harmonics<float, 1, true>(ctx, t, h.as<float>(), tr.as<float>(), nullptr);
+  else
+    launch_harmonics<float, 0, true>(ctx, t, h.as<float>(), tr.as<float>(), nullptr);
 }
 
 }  // namespace hot
