@@ -32,6 +32,7 @@ namespace hot {
 namespace {
 
 static __constant__ AlphaTable kAlpha = make_alpha_table();
+static __constant__ HarmRows kRows = kHarmRows;
 
 constexpr int kB = 256;
 constexpr int kWPB = kB / 64;
@@ -810,24 +811,36 @@ __global__ void k_src_unit_sum(const int2* __restrict__ items, int64_t n_items,
 // concatenated, 64 at a time. Each
 // lane accumulates sum_k abar_k d^(alpha+e_k) G for all alpha in registers; the
 // item's partial sums are reduced across lanes with a fixed butterfly.
-// P: the expansion order of the item's records. MIXQ (lists with per-entry
-// orders): the block's item is qitems[qbase + block], its records end at
-// citem_end, and the row is written with stride out_stride, zero-filled from
-// nm(P) up to out_nm (the cell's full moment count).
-template <int P, typename T, bool MIXQ, bool PER, bool K1>
-__global__ __launch_bounds__(64) void k_m2p_cell_adj(
-    int64_t n_citems, const uint32_t* __restrict__ citem_rec, const int32_t* __restrict__ citem_cell,
-    const uint32_t* __restrict__ crec_off, const uint32_t* __restrict__ qitems, int64_t qbase,
-    const uint32_t* __restrict__ citem_end, int out_stride, int out_nm,
+// P: the expansion order of the item's records. The block's item is
+// list[*first + block], below *last; its records end at citem_end (MIXQ, lists
+// with per-entry orders) or with the run of its cell. The row is written with
+// stride out_stride, zero-filled from nm(P) up to out_nm (the cell's full moment
+// count).
+// NEWTON: the items whose every record is served by Newtonian multipoles
+// (k_citem_flag). Their cotangents are those of the harmonic coefficients (1 + 3
+// P^2 of them, one multiply-add each per sink: about 380 issue slots at order 8
+// against 1210), turned into the raw moments' once per item.
+template <int P, typename T>
+constexpr int cell_adj_waves_per_simd() { return sizeof(T) == 4 && P == 6 ? 3 : 1; }
+
+template <int P, typename T, bool MIXQ, bool PER, bool K1, bool NEWTON>
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p_cell_adj(
+    const uint32_t* __restrict__ list, const uint32_t* __restrict__ first,
+    const uint32_t* __restrict__ last, const uint32_t* __restrict__ citem_rec, const int32_t* __restrict__ citem_cell,
+    const uint32_t* __restrict__ crec_off, const uint32_t* __restrict__ citem_end, int out_stride,
+    int out_nm,
     const uint64_t* __restrict__ mkey, double side, const uint32_t* __restrict__ mval,
     const int8_t* __restrict__ c_level, const int32_t* __restrict__ g_first,
     const int32_t* __restrict__ g_count, const int32_t* __restrict__ g_cell,
     const double* __restrict__ c_centre, const V4<T>* __restrict__ off,
     const V4<T>* __restrict__ ab4, double inv_side, double eps, T* __restrict__ part) {
   constexpr int NM = nm(P);
+  constexpr int NR = NEWTON ? 1 + 3 * P * P : NM;  // accumulated per lane
   const int lane = threadIdx.x;
-  if ((int64_t)blockIdx.x >= n_citems) return;
-  const int64_t it = MIXQ ? (int64_t)qitems[qbase + blockIdx.x] : (int64_t)blockIdx.x;
+  const uint32_t at = *first + blockIdx.x;
+  if (at >= *last) return;
+  const int64_t it = (int64_t)list[at];
   const int c = citem_cell[it];
   const uint32_t r0 = citem_rec[it];
   uint32_t r1;
@@ -839,17 +852,17 @@ __global__ __launch_bounds__(64) void k_m2p_cell_adj(
   }
   const double inv_s = ldexp(inv_side, (int)c_level[c]);
   const double es = eps * inv_s;
-  const T e2 = (T)(es * es);
+  const T e2 = NEWTON && K1 ? T(0) : (T)(es * es);
   const double ccx = c_centre[3 * c], ccy = c_centre[3 * c + 1], ccz = c_centre[3 * c + 2];
-  T row[NM];
+  T row[NR];
 #pragma unroll
-  for (int a = 0; a < NM; ++a) row[a] = T(0);
+  for (int a = 0; a < NR; ++a) row[a] = T(0);
   // The item's sinks, all its records' groups concatenated, in chunks of 64
   // lanes (groups of few sinks then fill the wavefront together: every sink
   // sees the same cell). Per record, staged in LDS by one lane each: the
   // running sink count, the group's first sink and the scaled difference of
   // the group centre from the (image of the) cell centre.
-  __shared__ int s_cum[kCellItemGroups + 1];
+  __shared__ int s_cum[65];  // padded past the last record
   __shared__ int s_first[kCellItemGroups];
   __shared__ T s_d[3][kCellItemGroups];
   const int nr = (int)(r1 - r0);  // at most kCellItemGroups < 64
@@ -873,56 +886,58 @@ __global__ __launch_bounds__(64) void k_m2p_cell_adj(
     const int y = __shfl_up(inc, o);
     if (lane >= o) inc += y;
   }
-  if (lane < nr) s_cum[lane + 1] = inc;
+  s_cum[lane + 1] = lane < nr ? inc : 0x7fffffff;
   if (lane == 0) s_cum[0] = 0;
   const int total = nr > 0 ? __shfl(inc, nr - 1) : 0;
   __syncthreads();
-  // sink t of the concatenation: record k with s_cum[k] <= t < s_cum[k + 1]
-  // (the same number of halvings on every lane), its offset and cotangent
+  // sink t of the concatenation: record k with s_cum[k] <= t < s_cum[k + 1],
+  // its offset and cotangent. No branches: the search and the loads of the next
+  // chunk are scheduled among the current one's arithmetic. Lanes past the end
+  // repeat the last sink with no cotangent.
   auto fetch = [&](int t, T& X, T& Y, T& Z, T& bx, T& by, T& bz) {
-    X = T(1);
-    Y = Z = bx = by = bz = T(0);
-    if (t < total) {
-      int lo = 0, hi = nr;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_cum[mid] <= t)
-          lo = mid;
-        else
-          hi = mid;
-      }
-      const int si = s_first[lo] + (t - s_cum[lo]);
-      const V4<T> me = off[si];
-      const V4<T> ab = ab4[si];
-      X = s_d[0][lo] + me.x * (T)inv_s;
-      Y = s_d[1][lo] + me.y * (T)inv_s;
-      Z = s_d[2][lo] + me.z * (T)inv_s;
-      bx = ab.x;
-      by = ab.y;
-      bz = ab.z;
-    }
+    const int u = t < total ? t : total - 1;
+    int lo = 0;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) lo += s_cum[lo + h] <= u ? h : 0;
+    const int si = s_first[lo] + (u - s_cum[lo]);
+    const V4<T> me = off[si];
+    const V4<T> ab = ab4[si];
+    X = hot_fma(me.x, (T)inv_s, s_d[0][lo]);
+    Y = hot_fma(me.y, (T)inv_s, s_d[1][lo]);
+    Z = hot_fma(me.z, (T)inv_s, s_d[2][lo]);
+    bx = u == t ? ab.x : T(0);
+    by = u == t ? ab.y : T(0);
+    bz = u == t ? ab.z : T(0);
   };
   // one loop over the chunks with the next chunk's data fetched ahead; a
   // single back edge keeps the row registers in place across iterations
   T X, Y, Z, bx, by, bz;
-  fetch(lane, X, Y, Z, bx, by, bz);
+  if (total > 0) fetch(lane, X, Y, Z, bx, by, bz);
   for (int t0 = 0; t0 < total; t0 += 64) {
     const T cX = X, cY = Y, cZ = Z, cbx = bx, cby = by, cbz = bz;
-    if (t0 + 64 < total) fetch(t0 + 64 + lane, X, Y, Z, bx, by, bz);
-    expansion_cell_adj<P, T, K1>(cX, cY, cZ, e2, cbx, cby, cbz, row);
+    fetch(t0 + 64 + lane, X, Y, Z, bx, by, bz);
+    if constexpr (NEWTON)
+      harm_cell_newton<P, T>(cX, cY, cZ, e2, cbx, cby, cbz, row);
+    else
+      expansion_cell_adj<P, T, K1>(cX, cY, cZ, e2, cbx, cby, cbz, row);
   }
   T* o = part + it * (int64_t)(MIXQ ? out_stride : nm_pad(P));
   // Sum the rows over the 64 lanes as a reduce-scatter: the row vector, padded
   // with zeros to 64 KR entries, is halved six times; at each step a lane keeps
   // one half (selected by its lane bit), receives the partner's copy of it and
-  // adds. Lane l ends with the sums of rows KR l .. KR l + KR - 1, after
-  // 32 KR + 16 KR + ... + KR exchanges instead of 6 per row.
-  constexpr int KR = (NM + 63) / 64;
+  // adds. Lane l ends with the sums of rows KR l .. KR l + KR - 1. The first two
+  // steps are swaps of half wavefronts and of rows of 16 lanes (two
+  // instructions per pair of values).
+  constexpr int KR = (NR + 63) / 64;
   T v[64 * KR];
 #pragma unroll
-  for (int a = 0; a < 64 * KR; ++a) v[a] = a < NM ? row[a] : T(0);
+  for (int a = 0; a < 64 * KR; ++a) v[a] = a < NR ? row[a] : T(0);
 #pragma unroll
-  for (int m = 32, h = 32 * KR; m > 0; m >>= 1, h >>= 1) {
+  for (int i = 0; i < 32 * KR; ++i) v[i] = fold32(v[i], v[i + 32 * KR]);
+#pragma unroll
+  for (int i = 0; i < 16 * KR; ++i) v[i] = fold16(v[i], v[i + 16 * KR]);
+#pragma unroll
+  for (int m = 8, h = 8 * KR; m > 0; m >>= 1, h >>= 1) {
     const bool up = (lane & m) != 0;
 #pragma unroll
     for (int i = 0; i < h; ++i) {
@@ -932,11 +947,99 @@ __global__ __launch_bounds__(64) void k_m2p_cell_adj(
       v[i] = keep + __shfl_xor(send, m);
     }
   }
+  if constexpr (!NEWTON) {
 #pragma unroll
-  for (int i = 0; i < KR; ++i)
-    if (KR * lane + i < NM) o[KR * lane + i] = v[i];
+    for (int i = 0; i < KR; ++i)
+      if (KR * lane + i < NM) o[KR * lane + i] = v[i];
+  } else {
+    __shared__ T s_h[64 * KR];
+#pragma unroll
+    for (int i = 0; i < KR; ++i) s_h[KR * lane + i] = v[i];
+    __syncthreads();
+    for (int a = lane; a < NM; a += 64) {
+      T t = T(0);
+      for (int j = kRows.start[a]; j < kRows.start[a + 1]; ++j)
+        t = hot_fma((T)kRows.val[j], s_h[kRows.idx[j]], t);
+      o[a] = t;
+    }
+  }
   if (MIXQ)
     for (int a = NM + lane; a < out_nm; a += 64) o[a] = T(0);
+}
+
+// Largest distance of a group's sinks from its centre (rounded up).
+template <typename T>
+__global__ __launch_bounds__(kB) void k_group_radius(const int32_t* __restrict__ g_first,
+                                                     const int32_t* __restrict__ g_count,
+                                                     int64_t G, const V4<T>* __restrict__ off,
+                                                     float* __restrict__ rad) {
+  const int lane = threadIdx.x & 63;
+  const int64_t g = (int64_t)blockIdx.x * kWPB + (threadIdx.x >> 6);
+  if (g >= G) return;
+  const int f = g_first[g], e = f + g_count[g];
+  T m = T(0);
+  for (int i = f + lane; i < e; i += 64) {
+    const V4<T> o = off[i];
+    const T r = hot_fma(o.x, o.x, hot_fma(o.y, o.y, o.z * o.z));
+    m = r > m ? r : m;
+  }
+  m = wave_max(m);
+  if (lane == 0) rad[g] = (float)sqrt((double)m) * 1.000001f;
+}
+
+// 1 for the items whose every record is served by Newtonian multipoles; one
+// wavefront per item (at most kCellItemGroups records), in list order.
+template <bool MIXQ, bool PER, bool K1>
+__global__ __launch_bounds__(kB) void k_citem_flag(
+    int64_t n, const uint32_t* __restrict__ qitems, const uint32_t* __restrict__ citem_rec,
+    const int32_t* __restrict__ citem_cell, const uint32_t* __restrict__ crec_off,
+    const uint32_t* __restrict__ citem_end, const uint64_t* __restrict__ mkey, double side,
+    const uint32_t* __restrict__ mval, const int32_t* __restrict__ g_cell,
+    const double* __restrict__ c_centre, const float* __restrict__ rad, NewtonRule rule,
+    uint32_t* __restrict__ flag) {
+  const int lane = threadIdx.x & 63;
+  const int64_t k = (int64_t)blockIdx.x * kWPB + (threadIdx.x >> 6);
+  if (k >= n) return;
+  const int64_t it = MIXQ ? (int64_t)qitems[k] : k;
+  const int c = citem_cell[it];
+  const uint32_t r0 = citem_rec[it];
+  uint32_t r1;
+  if (MIXQ) {
+    r1 = citem_end[it];
+  } else {
+    const uint32_t rc = crec_off[c + 1];
+    r1 = r0 + kCellItemGroups < rc ? r0 + kCellItemGroups : rc;
+  }
+  bool ok = true;
+  for (uint32_t r = r0 + lane; r < r1; r += 64) {
+    const int g = (int)mval[r], gc = g_cell[g];
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+    if (PER) image_shift((int)(mkey[r] & 127u), side, sx, sy, sz);
+    const double dx = c_centre[3 * gc] - (c_centre[3 * c] + sx);
+    const double dy = c_centre[3 * gc + 1] - (c_centre[3 * c + 1] + sy);
+    const double dz = c_centre[3 * gc + 2] - (c_centre[3 * c + 2] + sz);
+    const double d = sqrt(dx * dx + dy * dy + dz * dz) - (double)rad[g];
+    ok = ok && newton_ok<2, K1>(rule, d, c, false, 0.0);
+  }
+  const bool all = __ballot(!ok) == 0;
+  if (lane == 0) flag[k] = all ? 1u : 0u;
+}
+
+// the flagged items to the front list, the others to the other, in order
+__global__ void k_citem_split(int64_t n, const uint32_t* __restrict__ qitems,
+                              const uint32_t* __restrict__ flag, const uint32_t* __restrict__ pos,
+                              uint32_t* __restrict__ yes, uint32_t* __restrict__ no,
+                              uint32_t* __restrict__ pos_no) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k > n) return;
+  const uint32_t p = pos[k];
+  pos_no[k] = (uint32_t)k - p;
+  if (k == n) return;
+  const uint32_t it = qitems ? qitems[k] : (uint32_t)k;
+  if (flag[k])
+    yes[p] = it;
+  else
+    no[(uint32_t)k - p] = it;
 }
 
 // Mbar_alpha(c) = -w_alpha s^(-2-|alpha|) * sum over the cell's items (in order).
@@ -1246,35 +1349,70 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
   DBuf part;
   part.alloc(ctx, (size_t)std::max<int64_t>(1, t->n_citems) * nm_pad(P) * sizeof(T));
   tmark(ctx, HOT_T_ADJ_M2P_CELL, false);
-  if (t->n_citems > 0) {
-    auto cell = [&](auto kern, int64_t n, int64_t base) {
-      if (n <= 0) return;
-      kern<<<(unsigned)n, 64, 0, st>>>(
-          n, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(), t->mcell_rec.as<uint32_t>(),
-          t->qitems.as<uint32_t>(), base, t->citem_end.as<uint32_t>(), nm_pad(P), nm(P),
-          t->mrec_key.as<uint64_t>(), t->side, t->mrec_val.as<uint32_t>(), t->c_level.as<int8_t>(), t->g_first.as<int32_t>(),
-          t->g_count.as<int32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(), off, ab,
-          inv_side, eps, part.as<T>());
+  const int64_t NI = t->n_citems;
+  if (NI > 0) {
+    // the items by class, the counts left on the device: both classes launch a
+    // block per item, those past their class's end return at once
+    DBuf rad, flag, pos_y, pos_n, yes, no;
+    rad.alloc(ctx, (size_t)t->n_groups * sizeof(float));
+    flag.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+    pos_y.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
+    pos_n.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
+    yes.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+    no.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+    k_group_radius<T><<<grid_for(t->n_groups, kWPB), kB, 0, st>>>(
+        t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), t->n_groups, off, rad.as<float>());
+    HOT_CHECK_LAUNCH();
+    const NewtonRule rule = newton_rule<T>(t, eps, false);
+    const uint32_t* qi = mixq ? t->qitems.as<uint32_t>() : nullptr;
+    auto fk = mixq ? (t->periodic ? k_citem_flag<true, true, K1> : k_citem_flag<true, false, K1>)
+                   : (t->periodic ? k_citem_flag<false, true, K1> : k_citem_flag<false, false, K1>);
+    fk<<<grid_for(NI, kWPB), kB, 0, st>>>(
+        NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
+        t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
+        t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
+        rad.as<float>(), rule, flag.as<uint32_t>());
+    HOT_CHECK_LAUNCH();
+    uint32_t* py = pos_y.as<uint32_t>();
+    uint32_t* pn = pos_n.as<uint32_t>();
+    scan_u32(ctx, flag.as<uint32_t>(), py, NI, py + NI);
+    k_citem_split<<<grid_for(NI + 1, kB), kB, 0, st>>>(NI, qi, flag.as<uint32_t>(), py,
+                                                       yes.as<uint32_t>(), no.as<uint32_t>(), pn);
+    HOT_CHECK_LAUNCH();
+    // list positions [a, b)
+    auto cell = [&](auto kern, const uint32_t* list, const uint32_t* ends, int64_t a, int64_t b) {
+      if (b <= a) return;
+      kern<<<(unsigned)(b - a), 64, 0, st>>>(
+          list, ends + a, ends + b, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
+          t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), nm_pad(P), nm(P),
+          t->mrec_key.as<uint64_t>(), t->side, t->mrec_val.as<uint32_t>(),
+          t->c_level.as<int8_t>(), t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
+          t->g_cell.as<int32_t>(), t->c_centre.as<double>(), off, ab, inv_side, eps, part.as<T>());
       HOT_CHECK_LAUNCH();
     };
+    const uint32_t *ly = yes.as<uint32_t>(), *ln = no.as<uint32_t>();
     if (mixq) {
       // one launch per order present: each kernel holds only its order's row
       const int64_t* qo = t->qitem_off;
-#define HOT_CELL_Q(Q) \
-  if constexpr (Q <= P) {                                                       \
-    if (t->periodic)                                                            \
-      cell(k_m2p_cell_adj<Q, T, true, true, K1>, qo[Q + 1] - qo[Q], qo[Q]);         \
-    else                                                                        \
-      cell(k_m2p_cell_adj<Q, T, true, false, K1>, qo[Q + 1] - qo[Q], qo[Q]);        \
+#define HOT_CELL_Q(Q)                                                                    \
+  if constexpr (Q <= P) {                                                                \
+    if (t->periodic) {                                                                   \
+      cell(k_m2p_cell_adj<Q, T, true, true, K1, true>, ly, py, qo[Q], qo[Q + 1]);        \
+      cell(k_m2p_cell_adj<Q, T, true, true, K1, false>, ln, pn, qo[Q], qo[Q + 1]);       \
+    } else {                                                                             \
+      cell(k_m2p_cell_adj<Q, T, true, false, K1, true>, ly, py, qo[Q], qo[Q + 1]);       \
+      cell(k_m2p_cell_adj<Q, T, true, false, K1, false>, ln, pn, qo[Q], qo[Q + 1]);      \
+    }                                                                                    \
   }
       HOT_CELL_Q(0) HOT_CELL_Q(1) HOT_CELL_Q(2) HOT_CELL_Q(3) HOT_CELL_Q(4) HOT_CELL_Q(5)
       HOT_CELL_Q(6) HOT_CELL_Q(7) HOT_CELL_Q(8)
 #undef HOT_CELL_Q
+    } else if (t->periodic) {
+      cell(k_m2p_cell_adj<P, T, false, true, K1, true>, ly, py, 0, NI);
+      cell(k_m2p_cell_adj<P, T, false, true, K1, false>, ln, pn, 0, NI);
     } else {
-      if (t->periodic)
-        cell(k_m2p_cell_adj<P, T, false, true, K1>, t->n_citems, 0);
-      else
-        cell(k_m2p_cell_adj<P, T, false, false, K1>, t->n_citems, 0);
+      cell(k_m2p_cell_adj<P, T, false, false, K1, true>, ly, py, 0, NI);
+      cell(k_m2p_cell_adj<P, T, false, false, K1, false>, ln, pn, 0, NI);
     }
   }
   const int64_t tot = C * nm(P);

@@ -281,6 +281,22 @@ def gen_coefT(n):
     return L
 
 
+def gen_rows_table():
+    """Cotangents of the harmonic (k = 0) coefficients -> those of the weighted
+    raw moments, as sparse rows over the slots: start offsets, coefficient
+    indices and values (weights divided out)."""
+    start, idx, val = [0], [], []
+    for n in range(PMAX + 1):
+        rows = block_map(n, 0, False)
+        for al in monomials(n):
+            for j, row in enumerate(rows):
+                if al in row:
+                    idx.append(off_h(n) + j)
+                    val.append(float(row[al] / weight(al)))
+            start.append(len(idx))
+    return start, idx, val
+
+
 # ------------------------------------------------------------ kernels' bodies
 def yname(l, m, s):
     return f"Y{l}_{m}{'s' if s else 'c'}"
@@ -744,6 +760,12 @@ def main(path):
                   "T* __restrict__ h, T* __restrict__ t) {"] + gen_coef(n, True) + ["}"]
         parts += [f"__device__ __forceinline__ void harm_coefT{n}(const double* h, double* M) {{"] + \
             gen_coefT(n) + ["}"]
+    start, idx, val = gen_rows_table()
+    parts += ["struct HarmRows {", f"  short start[{len(start)}];", f"  short idx[{len(idx)}];",
+              f"  double val[{len(val)}];", "};",
+              "constexpr HarmRows kHarmRows = {",
+              "  {" + ", ".join(map(str, start)) + "},", "  {" + ", ".join(map(str, idx)) + "},",
+              "  {" + ", ".join(map(repr, val)) + "}};"]
     parts += ["", "}  // namespace hot"]
     os.makedirs(os.path.dirname(path), exist_ok=True)
     tmp = path + ".tmp"
