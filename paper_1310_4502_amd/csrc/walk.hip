@@ -4,13 +4,9 @@
 // Improving instruction-level parallelism section: one list per sink cell,
 // shared by all its sinks).
 //
-// One wavefront walks one group. The unit of work is a run of sibling cells
-// (contiguous in the canonical cell order): the lanes test the run against
-// the acceptance criterion at once, the cells before the first opened one are
-// emitted in order with ballot compaction, the rest of the run is kept on an
-// LDS stack and the opened cell's children become the next run. The output is
-// therefore exactly the depth-first preorder. The kernel runs twice: once to
-// count, once to fill at offsets from a scan of the counts.
+// One wavefront walks one group; lists come out in depth-first preorder. The
+// kernels run twice: once to count, once to fill at offsets from a scan of the
+// counts.
 //
 // Two acceptance tests: the theta criterion, and an absolute-error test that
 // also picks the expansion order of each accepted cell (Multipole Error
@@ -20,6 +16,8 @@
 //   E_q = M / (d - b)^2 * ((q + 2) - (q + 1) t) * t^(q + 1),  t = b / d,
 // with d the distance from the cell centre to the group's bounding sphere,
 // b the cell's b_max and M its particle count times the largest mass.
+#include <type_traits>
+
 #include "common.h"
 
 namespace hot {
@@ -126,12 +124,17 @@ __device__ __forceinline__ int accept_order(double dx, double dy, double dz, dou
   return -1;
 }
 
-template <bool FILL, bool ERR, bool PER, bool BG>
-__global__ __launch_bounds__(kB) void k_walk(
+// Walk with background subtraction. The unit of work is a run of sibling cells
+// (contiguous in the canonical cell order): the lanes test the run against the
+// acceptance criterion at once, the cells before the first opened one are
+// emitted in order with ballot compaction, the rest of the run is kept on an
+// LDS stack and the opened cell's children become the next run.
+template <bool FILL>
+__global__ __launch_bounds__(kB) void k_walk_bg(
     const int32_t* __restrict__ g_cell, int64_t G, const double* __restrict__ c_centre,
     const double* __restrict__ c_bmax, const int32_t* __restrict__ c_count,
     const uint8_t* __restrict__ c_leaf, const int32_t* __restrict__ c_child,
-    const int32_t* __restrict__ c_nchild, double theta, ErrMac em, Images im, Background bg,
+    const int32_t* __restrict__ c_nchild, double theta, Images im, Background bg,
     int direct_max,
     int64_t* __restrict__ cnt_p2p, int64_t* __restrict__ cnt_m2p, int64_t* __restrict__ pairs_p2p,
     const int64_t* __restrict__ off_p2p, const int64_t* __restrict__ off_m2p,
@@ -143,29 +146,24 @@ __global__ __launch_bounds__(kB) void k_walk(
   const int gc = g_cell[g];
   const double gx = c_centre[3 * gc], gy = c_centre[3 * gc + 1], gz = c_centre[3 * gc + 2];
   const double gb = c_bmax[gc];
-  const double mmax = ERR ? *em.mmax : 0.0;
   const uint64_t lt = lanemask_lt();
   int64_t np = 0, nmm = 0, npairs = 0, nbox = 0;
   int64_t bp = 0, bm = 0, bb = 0;
   if (FILL) {
     bp = off_p2p[g];
     bm = off_m2p[g];
-    if (BG) bb = bg.off_box[g];
+    bb = bg.off_box[g];
   }
   double nlo[3] = {0.0, 0.0, 0.0}, nhi[3] = {0.0, 0.0, 0.0};
-  if (BG) {
+  {
     const double h3 = (double)bg.width * ldexp(im.side, -((int)bg.c_level[gc] + 1));
     nlo[0] = gx - h3, nlo[1] = gy - h3, nlo[2] = gz - h3;
     nhi[0] = gx + h3, nhi[1] = gy + h3, nhi[2] = gz + h3;
   }
   bool bad = false;
-  for (int img = 0; img < (PER ? 125 : 1) && !bad; ++img) {
-  double shx = 0.0, shy = 0.0, shz = 0.0;
-  if (PER) {
-    shx = (double)(img / 25 - 2) * im.side;
-    shy = (double)((img / 5) % 5 - 2) * im.side;
-    shz = (double)(img % 5 - 2) * im.side;
-  }
+  for (int img = 0; img < 125 && !bad; ++img) {
+  double shx, shy, shz;
+  image_shift(img, im.side, shx, shy, shz);
   __builtin_amdgcn_wave_barrier();
   if (lane == 0) stk[w][0] = make_int2(0, 1);
   int top = 0;
@@ -181,40 +179,21 @@ __global__ __launch_bounds__(kB) void k_walk(
     const int c = lo + lane;
     int cls = CLS_NONE;
     int cnt = 0;
-    int q = -1;
     int rel = REL_IN;
     double blo[3], bhi[3];
     if (c < hi) {
-      double dx, dy, dz;
-      if (PER) {
-        const double cx = c_centre[3 * c] + shx;
-        const double cy = c_centre[3 * c + 1] + shy;
-        const double cz = c_centre[3 * c + 2] + shz;
-        dx = gx - cx;
-        dy = gy - cy;
-        dz = gz - cz;
-        if (BG) {
-          const double h = ldexp(im.side, -((int)bg.c_level[c] + 1));
-          blo[0] = cx - h, blo[1] = cy - h, blo[2] = cz - h;
-          bhi[0] = cx + h, bhi[1] = cy + h, bhi[2] = cz + h;
-          rel = box_rel(blo, bhi, nlo, nhi);
-        }
-      } else {
-        dx = gx - c_centre[3 * c];
-        dy = gy - c_centre[3 * c + 1];
-        dz = gz - c_centre[3 * c + 2];
-      }
+      const double cx = c_centre[3 * c] + shx;
+      const double cy = c_centre[3 * c + 1] + shy;
+      const double cz = c_centre[3 * c + 2] + shz;
+      const double dx = gx - cx, dy = gy - cy, dz = gz - cz;
+      const double h = ldexp(im.side, -((int)bg.c_level[c] + 1));
+      blo[0] = cx - h, blo[1] = cy - h, blo[2] = cz - h;
+      bhi[0] = cx + h, bhi[1] = cy + h, bhi[2] = cz + h;
+      rel = box_rel(blo, bhi, nlo, nhi);
       cnt = c_count[c];
-      bool acc;
-      if (ERR) {
-        q = accept_order(dx, dy, dz, gb, c_bmax[c], cnt, mmax, em.tol, em.pmax);
-        acc = q >= 0;
-      } else {
-        const double d2 = (dx * dx + dy * dy) + dz * dz;
-        const double rr = c_bmax[c] / theta + gb;
-        acc = d2 > rr * rr;
-      }
-      if (BG && rel == REL_STRADDLE) acc = false;
+      const double d2 = (dx * dx + dy * dy) + dz * dz;
+      const double rr = c_bmax[c] / theta + gb;
+      const bool acc = d2 > rr * rr && rel != REL_STRADDLE;
       if (acc)
         cls = cnt <= direct_max ? CLS_P2P : CLS_M2P;
       else
@@ -226,32 +205,28 @@ __global__ __launch_bounds__(kB) void k_walk(
     const uint64_t pm = __ballot(cls == CLS_P2P) & before;
     const uint64_t mm = __ballot(cls == CLS_M2P) & before;
     // boxes of the emitted P2P cells, in lane order (one or two per cell)
-    uint64_t b1 = 0, b2 = 0;
-    if (BG) {
-      const bool mine = (pm >> lane) & 1ull;
-      b1 = __ballot(mine && rel != REL_IN);
-      b2 = __ballot(mine && rel == REL_STRADDLE);
-    }
+    const bool mine = (pm >> lane) & 1ull;
+    const uint64_t b1 = __ballot(mine && rel != REL_IN);
+    const uint64_t b2 = __ballot(mine && rel == REL_STRADDLE);
     if (FILL) {
       if ((pm >> lane) & 1ull) {
         p2p[bp + np + __popcll(pm & lt)] = c;
-        if (PER) im.p2p_img[bp + np + __popcll(pm & lt)] = (int8_t)img;
-        if (BG && rel != REL_IN)
+        im.p2p_img[bp + np + __popcll(pm & lt)] = (int8_t)img;
+        if (rel != REL_IN)
           put_pieces(bg, bb + nbox + __popcll(b1 & lt) + __popcll(b2 & lt), blo, bhi, rel, nlo,
                      nhi);
       }
       if ((mm >> lane) & 1ull) {
         m2p[bm + nmm + __popcll(mm & lt)] = c;
-        if (ERR) em.m2p_q[bm + nmm + __popcll(mm & lt)] = (int8_t)q;
-        if (PER) im.m2p_img[bm + nmm + __popcll(mm & lt)] = (int8_t)img;
-        if (BG) bg.m2p_sub[bm + nmm + __popcll(mm & lt)] = (int8_t)(rel == REL_OUT);
+        im.m2p_img[bm + nmm + __popcll(mm & lt)] = (int8_t)img;
+        bg.m2p_sub[bm + nmm + __popcll(mm & lt)] = (int8_t)(rel == REL_OUT);
       }
     } else {
       if ((pm >> lane) & 1ull) npairs += cnt;
     }
     np += __popcll(pm);
     nmm += __popcll(mm);
-    if (BG) nbox += __popcll(b1) + __popcll(b2);
+    nbox += __popcll(b1) + __popcll(b2);
     if (om) {
       const int oc = lo + k;
       const int cf = c_child[oc], nc = c_nchild[oc];
@@ -261,7 +236,7 @@ __global__ __launch_bounds__(kB) void k_walk(
         bad = true;
         break;
       }
-      if (BG) {
+      {
         // the opened cell's empty octants (octant = the key's last digit,
         // 4 x + 2 y + z), one lane each
         const double ocx = c_centre[3 * oc] + shx;
@@ -313,7 +288,303 @@ __global__ __launch_bounds__(kB) void k_walk(
       cnt_p2p[g] = np;
       cnt_m2p[g] = nmm;
       pairs_p2p[g] = npairs;
-      if (BG) bg.cnt_box[g] = nbox;
+      bg.cnt_box[g] = nbox;
+    }
+  }
+}
+
+// ------------------------------------------------------- walk without background
+// The walk of lists without background subtraction. A wavefront expands a run of
+// siblings (first the root, or its 125 images) level by level: the cells of a
+// level are tested 64 at a time, the children of the opened ones, in order,
+// are the next level. In the fill pass the entries below every cell are then
+// counted from the deepest level up and turned into list positions from the top
+// down, which gives the depth-first preorder. Bound by VALU issue and the cell
+// records' latency. (Testing one run of at most eight siblings per step, as
+// above, leaves most of a wavefront idle: the lists of a 4.1 M-particle grid
+// took 15.3 ms that way, 5.3 ms now, the pair segments included.) A run whose cells
+// exceed the room in LDS is taken one step of the depth-first walk instead: its
+// cells before the first opened one are emitted, the rest of the run and the
+// opened cell's children wait on a stack, each to be expanded by itself.
+
+// What the walk reads of a cell; r: b_max / theta, or b_max for the error test.
+struct alignas(16) WalkCell {
+  double x, y, z, r;
+  int32_t child, count;
+  int32_t n_child;  // 0: a leaf
+  int32_t pad;
+};
+
+__global__ void k_walk_cells(int64_t C, const double* __restrict__ c_centre,
+                             const double* __restrict__ c_bmax,
+                             const int32_t* __restrict__ c_count,
+                             const uint8_t* __restrict__ c_leaf,
+                             const int32_t* __restrict__ c_child,
+                             const int32_t* __restrict__ c_nchild, double theta,
+                             WalkCell* __restrict__ out) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= C) return;
+  WalkCell r;
+  r.x = c_centre[3 * c];
+  r.y = c_centre[3 * c + 1];
+  r.z = c_centre[3 * c + 2];
+  r.r = theta > 0.0 ? c_bmax[c] / theta : c_bmax[c];
+  r.child = c_child[c];
+  r.count = c_count[c];
+  r.n_child = c_leaf[c] ? 0 : c_nchild[c];
+  r.pad = 0;
+  out[c] = r;
+}
+
+// Cells of one expansion. The count pass needs cells and images only; the fill
+// pass 12 bytes a cell (13 wavefronts per CU at 1024 cells; lists of about a
+// thousand entries and opened cells are common).
+template <bool FILL>
+constexpr int walk_room() { return FILL ? 1024 : 1536; }
+
+template <bool FILL, bool ERR, bool PER>
+__global__ __launch_bounds__(64) void k_walk_levels(
+    const int32_t* __restrict__ g_cell, int64_t G, const double* __restrict__ c_bmax,
+    const WalkCell* __restrict__ cells, ErrMac em, Images im, int direct_max,
+    int64_t* __restrict__ cnt_p2p, int64_t* __restrict__ cnt_m2p, int64_t* __restrict__ pairs_p2p,
+    const int64_t* __restrict__ off_p2p, const int64_t* __restrict__ off_m2p,
+    int32_t* __restrict__ p2p, int32_t* __restrict__ m2p, int64_t C, unsigned* __restrict__ flags) {
+  constexpr int kRoom = walk_room<FILL>(), kF = FILL ? kRoom : 1;
+  __shared__ int32_t s_cell[kRoom];
+  __shared__ uint8_t s_img[PER ? kRoom : 1];
+  __shared__ uint16_t s_kid[kF];   // first child's place
+  __shared__ uint8_t s_meta[kF];   // class; children or order above
+  __shared__ uint32_t s_cnt[kF];   // entries below, then list positions (P2P low, M2P high half)
+  __shared__ int s_lev[kMaxLevel + 3];
+  __shared__ int2 s_stk[kStack];
+  const int lane = threadIdx.x;
+  // neighbouring groups meet the same cells: consecutive groups on one XCD
+  const int64_t per = (G + kXcdCount - 1) / kXcdCount;
+  const int64_t g = (int64_t)(blockIdx.x % kXcdCount) * per + blockIdx.x / kXcdCount;
+  if (g >= G || (int64_t)(blockIdx.x / kXcdCount) >= per) return;
+  const int gc = g_cell[g];
+  const double gx = cells[gc].x, gy = cells[gc].y, gz = cells[gc].z;
+  const double gb = c_bmax[gc];
+  const double mmax = ERR ? *em.mmax : 0.0;
+  const uint64_t lt = lanemask_lt();
+  int64_t np = 0, nmm = 0, npairs = 0;
+  int64_t bp = 0, bm = 0;
+  if (FILL) {
+    bp = off_p2p[g];
+    bm = off_m2p[g];
+  }
+  // class of a cell (and its order, its record)
+  auto test = [&](int c, int img, int& q, WalkCell& r) -> int {
+    r = cells[c];
+    double dx, dy, dz;
+    if (PER) {
+      double tx, ty, tz;
+      image_shift(img, im.side, tx, ty, tz);
+      dx = gx - (r.x + tx);
+      dy = gy - (r.y + ty);
+      dz = gz - (r.z + tz);
+    } else {
+      dx = gx - r.x;
+      dy = gy - r.y;
+      dz = gz - r.z;
+    }
+    bool acc;
+    if (ERR) {
+      q = accept_order(dx, dy, dz, gb, r.r, r.count, mmax, em.tol, em.pmax);
+      acc = q >= 0;
+    } else {
+      const double d2 = (dx * dx + dy * dy) + dz * dz;
+      const double rr = r.r + gb;
+      acc = d2 > rr * rr;
+    }
+    if (acc) return r.count <= direct_max ? CLS_P2P : CLS_M2P;
+    return r.n_child == 0 ? CLS_P2P : CLS_OPEN;
+  };
+  auto put = [&](int cls, int64_t at_p, int64_t at_m, int c, int img, int q) {
+    if (cls == CLS_P2P) {
+      p2p[at_p] = c;
+      if (PER) im.p2p_img[at_p] = (int8_t)img;
+    } else if (cls == CLS_M2P) {
+      m2p[at_m] = c;
+      if (ERR) em.m2p_q[at_m] = (int8_t)q;
+      if (PER) im.m2p_img[at_m] = (int8_t)img;
+    }
+  };
+  // Expansion of the n cells already in s_cell (and s_img); false, and nothing
+  // counted or written, if they do not fit.
+  auto expand = [&](int n) -> bool {
+    int ls = 0, le = n, tail = n, lev = 0;
+    int64_t ep = 0, emm = 0, epairs = 0;
+    if (FILL && lane == 0) s_lev[0] = 0;
+    while (le > ls) {
+      if (FILL && lane == 0) s_lev[lev + 1] = le;
+      for (int b = ls; b < le; b += 64) {
+        const int i = b + lane;
+        int cls = CLS_NONE, q = 0, nc = 0, img = kCentreImage;
+        WalkCell r;
+        r.child = r.count = 0;
+        if (i < le) {
+          if (PER) img = s_img[i];
+          cls = test(s_cell[i], img, q, r);
+          if (cls == CLS_OPEN) nc = r.n_child;
+        }
+        // children of the lanes before this one: 4-bit numbers, bit by bit
+        const uint64_t b0 = __ballot(nc & 1), b1 = __ballot(nc & 2), b2 = __ballot(nc & 4),
+                       b3 = __ballot(nc & 8);
+        const int total = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2) + 8 * __popcll(b3);
+        if (tail + total > kRoom) return false;
+        const int kid = tail + __popcll(b0 & lt) + 2 * __popcll(b1 & lt) + 4 * __popcll(b2 & lt) +
+                        8 * __popcll(b3 & lt);
+        for (int j = 0; j < nc; ++j) {
+          s_cell[kid + j] = r.child + j;
+          if (PER) s_img[kid + j] = (uint8_t)img;
+        }
+        const uint64_t pm = __ballot(cls == CLS_P2P), mm = __ballot(cls == CLS_M2P);
+        ep += __popcll(pm);
+        emm += __popcll(mm);
+        if (!FILL && cls == CLS_P2P) epairs += r.count;
+        if (FILL && i < le) {
+          s_kid[i] = (uint16_t)kid;
+          s_meta[i] = (uint8_t)(cls | ((cls == CLS_OPEN ? nc : q) << 2));
+          s_cnt[i] = cls == CLS_P2P ? 1u : cls == CLS_M2P ? 0x10000u : 0u;
+        }
+        tail += total;
+      }
+      __syncthreads();
+      ls = le;
+      le = tail;
+      ++lev;  // at most the deepest level + 1
+    }
+    if (FILL) {
+      // entries below every opened cell, from the deepest level up
+      for (int l = lev - 2; l >= 0; --l) {
+        for (int i = s_lev[l] + lane; i < s_lev[l + 1]; i += 64) {
+          const int meta = s_meta[i];
+          if ((meta & 3) == CLS_OPEN) {
+            const int k = s_kid[i], nc = meta >> 2;
+            uint32_t t = 0u;
+            for (int j = 0; j < nc; ++j) t += s_cnt[k + j];
+            s_cnt[i] = t;
+          }
+        }
+        __syncthreads();
+      }
+      // positions of the first cells, then of every opened cell's children
+      uint32_t base = 0u;
+      for (int b = 0; b < n; b += 64) {
+        const uint32_t own = b + lane < n ? s_cnt[b + lane] : 0u;
+        uint32_t x = own;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const uint32_t y = __shfl_up(x, d);
+          if (lane >= d) x += y;
+        }
+        if (b + lane < n) s_cnt[b + lane] = base + x - own;
+        base += __shfl(x, 63);
+      }
+      __syncthreads();
+      for (int l = 0; l < lev; ++l) {
+        for (int i = s_lev[l] + lane; i < s_lev[l + 1]; i += 64) {
+          const int meta = s_meta[i];
+          uint32_t o = s_cnt[i];
+          if ((meta & 3) == CLS_OPEN) {
+            const int k = s_kid[i], nc = meta >> 2;
+            for (int j = 0; j < nc; ++j) {
+              const uint32_t t = s_cnt[k + j];
+              s_cnt[k + j] = o;
+              o += t;
+            }
+          } else {
+            put(meta & 3, bp + np + (o & 0xffffu), bm + nmm + (o >> 16), s_cell[i],
+                PER ? (int)s_img[i] : kCentreImage, meta >> 2);
+          }
+        }
+        __syncthreads();
+      }
+    }
+    np += ep;
+    nmm += emm;
+    npairs += epairs;
+    return true;
+  };
+  // all images at once, if they fit
+  bool done = false;
+  if (PER) {
+    for (int i = lane; i < 125; i += 64) {
+      s_cell[i] = 0;
+      s_img[i] = (uint8_t)i;
+    }
+    __syncthreads();
+    done = expand(125);
+    __syncthreads();
+  }
+  bool bad = false;
+  for (int img = PER ? 0 : kCentreImage; !done && !bad && img < (PER ? 125 : kCentreImage + 1);
+       ++img) {
+    if (lane == 0) s_stk[0] = make_int2(0, 1);
+    int top = 0;
+    while (top >= 0) {
+      __syncthreads();
+      const int2 run = s_stk[top];
+      const int lo = uniform_i32(run.x), hi = uniform_i32(run.y);
+      if (lo < 0 || hi > C || hi - lo > 8 || lo >= hi) {  // never true for a valid tree
+        if (lane == 0) atomicOr(flags, FLAG_INTERNAL);
+        bad = true;
+        break;
+      }
+      const int c = lo + lane;
+      if (c < hi) {
+        s_cell[lane] = c;
+        if (PER) s_img[lane] = (uint8_t)img;
+      }
+      __syncthreads();
+      if (expand(hi - lo)) {
+        --top;
+        continue;
+      }
+      // one step of the depth-first walk
+      int cls = CLS_NONE, q = 0;
+      WalkCell r;
+      r.child = r.count = r.n_child = 0;
+      if (c < hi) cls = test(c, img, q, r);
+      const uint64_t om = __ballot(cls == CLS_OPEN);
+      const int k = om ? (__ffsll((long long)om) - 1) : 64;
+      const uint64_t before = k >= 64 ? ~0ull : ((1ull << k) - 1ull);
+      const uint64_t pm = __ballot(cls == CLS_P2P) & before;
+      const uint64_t mm = __ballot(cls == CLS_M2P) & before;
+      if ((before >> lane) & 1ull) {
+        if (FILL)
+          put(cls, bp + np + __popcll(pm & lt), bm + nmm + __popcll(mm & lt), c, img, q);
+        else if (cls == CLS_P2P)
+          npairs += r.count;
+      }
+      np += __popcll(pm);
+      nmm += __popcll(mm);
+      if (!om) {
+        --top;
+        continue;
+      }
+      const int cf = __shfl(r.child, k), nc = __shfl(r.n_child, k);
+      if (nc < 1 || nc > 8 || cf < 0 || top + 2 >= kStack) {  // never true for a valid tree
+        if (lane == 0) atomicOr(flags, FLAG_INTERNAL);
+        bad = true;
+        break;
+      }
+      if (lo + k + 1 < hi) {
+        if (lane == 0) s_stk[top] = make_int2(lo + k + 1, hi);
+        ++top;
+      }
+      if (lane == 0) s_stk[top] = make_int2(cf, cf + nc);
+    }
+    __syncthreads();
+  }
+  if (!FILL) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) npairs += __shfl_xor(npairs, off);
+    if (lane == 0) {
+      cnt_p2p[g] = np;
+      cnt_m2p[g] = nmm;
+      pairs_p2p[g] = npairs;
     }
   }
 }
@@ -623,14 +894,34 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
   pairs.alloc(ctx, (G + 1) * sizeof(int64_t));
   mcount.alloc(ctx, (G + 1) * sizeof(int64_t));
   totals.alloc(ctx, 4 * sizeof(int64_t));
-  const unsigned grid = grid_for(G, kWavesPerBlock);
-  k_walk<false, ERR, PER, BG><<<grid, kB, 0, st>>>(
-      t->g_cell.as<int32_t>(), G, t->c_centre.as<double>(), t->c_bmax.as<double>(),
-      t->c_count.as<int32_t>(), t->c_leaf.as<uint8_t>(), t->c_child.as<int32_t>(),
-      t->c_nchild.as<int32_t>(), theta, em, im, bg, direct_max, t->p2p_off.as<int64_t>(),
-      t->m2p_off.as<int64_t>(), pairs.as<int64_t>(), nullptr, nullptr, nullptr, nullptr,
-      t->n_cells, ctx->d_flags + kFlagLocal);
-  HOT_CHECK_LAUNCH();
+  // the error test has no theta
+  DBuf wcells;
+  if (!BG) {
+    wcells.alloc(ctx, (size_t)t->n_cells * sizeof(WalkCell));
+    k_walk_cells<<<grid_for(t->n_cells, kB), kB, 0, st>>>(
+        t->n_cells, t->c_centre.as<double>(), t->c_bmax.as<double>(), t->c_count.as<int32_t>(),
+        t->c_leaf.as<uint8_t>(), t->c_child.as<int32_t>(), t->c_nchild.as<int32_t>(),
+        ERR ? 0.0 : theta, wcells.as<WalkCell>());
+    HOT_CHECK_LAUNCH();
+  }
+  auto walk = [&](auto fill_c, int64_t* cp, int64_t* cm, int64_t* pairs_out, const int64_t* op,
+                  const int64_t* om, int32_t* lp, int32_t* lm, unsigned* flag) {
+    constexpr bool FILL = decltype(fill_c)::value;
+    if constexpr (BG)
+      k_walk_bg<FILL><<<grid_for(G, kWavesPerBlock), kB, 0, st>>>(
+          t->g_cell.as<int32_t>(), G, t->c_centre.as<double>(), t->c_bmax.as<double>(),
+          t->c_count.as<int32_t>(), t->c_leaf.as<uint8_t>(), t->c_child.as<int32_t>(),
+          t->c_nchild.as<int32_t>(), theta, im, bg, direct_max, cp, cm, pairs_out, op, om, lp, lm,
+          t->n_cells, flag);
+    else
+      k_walk_levels<FILL, ERR, PER>
+          <<<(unsigned)((G + kXcdCount - 1) / kXcdCount * kXcdCount), 64, 0, st>>>(
+              t->g_cell.as<int32_t>(), G, t->c_bmax.as<double>(), wcells.as<WalkCell>(), em, im,
+              direct_max, cp, cm, pairs_out, op, om, lp, lm, t->n_cells, flag);
+    HOT_CHECK_LAUNCH();
+  };
+  walk(std::false_type{}, t->p2p_off.as<int64_t>(), t->m2p_off.as<int64_t>(), pairs.as<int64_t>(),
+       nullptr, nullptr, nullptr, nullptr, ctx->d_flags + kFlagLocal);
   // pair counts: P2P sources x sinks, M2P cells x sinks
   HOT_HIP(hipMemcpyAsync(mcount.p, t->m2p_off.p, G * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
   k_pair_weights<<<grid_for(G, kB), kB, 0, st>>>(t->g_count.as<int32_t>(), G, pairs.as<int64_t>(),
@@ -695,13 +986,9 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
     t->box_sign.release();
     t->m2p_sub.release();
   }
-  k_walk<true, ERR, PER, BG><<<grid, kB, 0, st>>>(
-      t->g_cell.as<int32_t>(), G, t->c_centre.as<double>(), t->c_bmax.as<double>(),
-      t->c_count.as<int32_t>(), t->c_leaf.as<uint8_t>(), t->c_child.as<int32_t>(),
-      t->c_nchild.as<int32_t>(), theta, em, im, bg, direct_max, nullptr, nullptr, nullptr,
-      t->p2p_off.as<int64_t>(), t->m2p_off.as<int64_t>(), t->p2p.as<int32_t>(),
-      t->m2p.as<int32_t>(), t->n_cells, ctx->d_flags + kFlagDeferred);
-  HOT_CHECK_LAUNCH();
+  walk(std::true_type{}, nullptr, nullptr, nullptr, t->p2p_off.as<int64_t>(),
+       t->m2p_off.as<int64_t>(), t->p2p.as<int32_t>(), t->m2p.as<int32_t>(),
+       ctx->d_flags + kFlagDeferred);
   t->theta = theta;
   t->direct_max = direct_max;
   t->list_p = ERR ? em.pmax : -1;
