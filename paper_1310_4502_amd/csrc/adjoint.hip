@@ -347,11 +347,11 @@ __global__ void k_abar(const double* __restrict__ abar, const uint32_t* __restri
 // The group's list comes as its pair segments, as in the forward pair kernel.
 template <typename T, bool EPS0, bool K1>
 __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
-    const int2* __restrict__ items, int64_t n_items, const int64_t* __restrict__ pseg_off,
-    const PairSeg* __restrict__ pseg, const int32_t* __restrict__ g_first,
+    const int4* __restrict__ units, int64_t n_units, const int2* __restrict__ items,
+    const int64_t* __restrict__ pseg_off, const PairSeg* __restrict__ pseg, const int32_t* __restrict__ g_first,
     const int32_t* __restrict__ g_count, const V4<T>* __restrict__ off,
     const V4<T>* __restrict__ ab4, T eps2, T ie, const unsigned* __restrict__ mdiff,
-    T* __restrict__ state) {
+    T* __restrict__ state, T* __restrict__ part) {
   __shared__ V4<T> stage[kWPB][64];
   // K1: eps2 is the squared kernel radius, ie its inverse radius
   const T ie2 = ie * ie, ie3 = ie * ie2, ie5t = (ie3 * ie2) * (T(1) / T(3));
@@ -360,9 +360,10 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
   const bool uni = *mdiff == 0u;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   V4<T>* slot = stage[w];
-  const int64_t it = (int64_t)blockIdx.x * kWPB + w;
-  if (it >= n_items) return;
-  const int2 item = items[it];
+  const int64_t iu = (int64_t)blockIdx.x * kWPB + w;
+  if (iu >= n_units) return;
+  const int4 unit = units[iu];
+  const int2 item = items[unit.x];
   const int g = uniform_i32(item.x);
   const int gend = g_first[g] + g_count[g];
   // m x n blocking with n = 2 as in the forward pair kernel: lane l holds
@@ -410,8 +411,8 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
     pB = qBx = qBy = qBz = T(0);                                                     \
     n_acc = 0;                                                                       \
   }
-  const int64_t q1 = pseg_off[g + 1];
-  for (int64_t q = pseg_off[g]; q < q1; ++q) {
+  const int64_t q0 = pseg_off[g], q1 = q0 + uniform_i32(unit.z);
+  for (int64_t q = q0 + uniform_i32(unit.y); q < q1; ++q) {
     {
       // a segment: the sources [j, jend) of one source group
       const PairSeg sgm = pseg[q];
@@ -512,7 +513,7 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
   if (n_acc > 0) HOT_SINK_FLUSH
 #undef HOT_SINK_FLUSH
   if (active) {
-    T* st = state + (int64_t)i * 8;
+    T* st = unit.w < 0 ? state + (int64_t)i * 8 : part + (int64_t)unit.w * kUnitSums + lane * 8;
     st[0] = sx;
     st[1] = sy;
     st[2] = sz;
@@ -1567,16 +1568,17 @@ void adjoint_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
   gather_sorted(ctx, t, pos, mass, spos.as<double>(), smass.as<double>(), 0);
   const T e2 = (T)(eps * eps);
   const T ie = k1 ? (T)(1.0 / eps) : T(0);
-  const unsigned gi = grid_for(t->n_items, kWPB);
   // pair terms
   auto sink_k = k1 ? k_p2p_sink_adj<T, false, true>
                     : (e2 > T(0) ? k_p2p_sink_adj<T, false, false> : k_p2p_sink_adj<T, true, false>);
   tmark(ctx, HOT_T_ADJ_P2P_SINK, false);
-  sink_k<<<gi, kB, 0, st>>>(t->items.as<int2>(), t->n_items, t->pseg_off.as<int64_t>(),
-                            t->pseg.as<PairSeg>(), t->g_first.as<int32_t>(),
-                            t->g_count.as<int32_t>(), off.as<V4<T>>(), ab.as<V4<T>>(), e2, ie,
-                            ctx->d_flags + kFlagMass, sink.as<T>());
+  sink_k<<<grid_for(t->n_punits, kWPB), kB, 0, st>>>(
+      t->punits.as<int4>(), t->n_punits, t->items.as<int2>(), t->pseg_off.as<int64_t>(),
+      t->pseg.as<PairSeg>(), t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
+      off.as<V4<T>>(), ab.as<V4<T>>(), e2, ie, ctx->d_flags + kFlagMass, sink.as<T>(),
+      t->unit_part.as<T>());
   HOT_CHECK_LAUNCH();
+  sum_units<T, 3, false>(ctx, t, t->pslots, t->n_pslots, sink.as<T>());
   tmark(ctx, HOT_T_ADJ_P2P_SINK, true);
   // expansion terms
   V4<T>* o4 = off.as<V4<T>>();

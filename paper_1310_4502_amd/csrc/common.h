@@ -272,9 +272,15 @@ struct hot_tree {
   // eval work items: (group, first sink) per wave
   int64_t n_items = 0;
   hot::DBuf items;
-  // items of at most 32 sinks and the others (split at tree build; -1: not yet)
-  int64_t n_items_small = -1, n_items_big = 0;
-  hot::DBuf items_small, items_big;
+  // work units of the pair kernels and of the expansion kernels over sinks
+  // (built with the lists): a part of an item's list, (item, first, end, slot);
+  // slot < 0: the item's only unit. munits: those of items of at most 32 sinks
+  // first (n_munits_small), then the others. pslots, mslots: what the partial
+  // sums of the divided items' units are added up from, (item, slot, units)
+  // for an item's first slot, units = 0 for the others; unit_part: 64 sinks x
+  // 8 sums per slot, of either kind (FP64 room)
+  int64_t n_punits = 0, n_munits = 0, n_munits_small = 0, n_pslots = 0, n_mslots = 0;
+  hot::DBuf punits, munits, pslots, mslots, unit_part;
   // adjoint caches built from the lists on first use
   bool has_transpose = false;
   // P2P by source item: records sorted by (item, group); rec_off per item
@@ -321,8 +327,8 @@ void scan_i64(hot_ctx* ctx, const int64_t* in, int64_t* out, int64_t n, int64_t*
 void radix_sort(hot_ctx* ctx, DBuf& keys, DBuf& vals, int64_t n, int bits, int lo = 0);
 
 void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box);
-// the work items split by sink count (at most 32, or more), at tree build
-void split_items(hot_ctx* ctx, hot_tree* t);
+// the work units of the current lists
+void build_units(hot_ctx* ctx, hot_tree* t);
 void gather_sorted(hot_ctx* ctx, const hot_tree* t, const double* pos, const double* mass,
                    double* spos, double* smass, int check_mass);
 void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, int p);
@@ -447,6 +453,9 @@ struct PairSeg {
   int32_t first, end, self, pad;
   double dx, dy, dz;
 };
+// Partial sums of a work unit that shares its item with others: 64 sinks x 8.
+constexpr int kUnitSums = 64 * 8;
+
 // sources summed in plain FP32 between two compensated adds of a pair kernel
 constexpr int kSumRun = 256;
 

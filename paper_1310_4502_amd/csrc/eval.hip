@@ -44,10 +44,11 @@ constexpr int p2p_waves_per_simd() { return (sizeof(T) == 4 && !K1) ? 8 : 1; }
 template <typename T, bool POT, bool EPS0, bool K1>
 __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(p2p_waves_per_simd<T, K1>())))
 void k_p2p(
-    const int2* __restrict__ items, int64_t n_items, const int64_t* __restrict__ pseg_off,
-    const PairSeg* __restrict__ pseg, const int32_t* __restrict__ g_first,
-    const int32_t* __restrict__ g_count, const V4<T>* __restrict__ off, T eps2, T ie,
-    const unsigned* __restrict__ mdiff, T* __restrict__ state, int64_t n) {
+    const int4* __restrict__ units, int64_t n_units, const int2* __restrict__ items,
+    const int64_t* __restrict__ pseg_off, const PairSeg* __restrict__ pseg,
+    const int32_t* __restrict__ g_first, const int32_t* __restrict__ g_count,
+    const V4<T>* __restrict__ off, T eps2, T ie, const unsigned* __restrict__ mdiff,
+    T* __restrict__ state, T* __restrict__ part) {
   __shared__ V4<T> stage[kWavesPerBlock][64];
   // K1: eps2 is the squared kernel radius, ie its inverse radius
   const T ie2 = ie * ie, ie3 = ie * ie2;
@@ -56,9 +57,10 @@ void k_p2p(
   const bool uni = *mdiff == 0u;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   V4<T>* slot = stage[w];
-  const int64_t it = (int64_t)blockIdx.x * kWavesPerBlock + w;
-  if (it >= n_items) return;
-  const int2 item = items[it];
+  const int64_t iu = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  if (iu >= n_units) return;
+  const int4 unit = units[iu];
+  const int2 item = items[unit.x];
   const int g = uniform_i32(item.x);
   const int gend = g_first[g] + g_count[g];
   // m x n blocking with n = 2: lane l holds the two sinks item.y + (l & 31)
@@ -103,8 +105,8 @@ void k_p2p(
     aBx = aBy = aBz = aBp = T(0);                                                    \
     n_acc = 0;                                                                       \
   }
-  const int64_t q1 = pseg_off[g + 1];
-  for (int64_t q = pseg_off[g]; q < q1; ++q) {
+  const int64_t q0 = pseg_off[g], q1 = q0 + uniform_i32(unit.z);
+  for (int64_t q = q0 + uniform_i32(unit.y); q < q1; ++q) {
     {
       // a segment: the sources [j, jend) of one source group
       const PairSeg sgm = pseg[q];
@@ -200,7 +202,7 @@ void k_p2p(
   if (n_acc > 0) HOT_FLUSH
 #undef HOT_FLUSH
   if (active) {
-    T* st = state + (int64_t)i * 8;
+    T* st = unit.w < 0 ? state + (int64_t)i * 8 : part + (int64_t)unit.w * kUnitSums + lane * 8;
     st[0] = sx;
     st[1] = sy;
     st[2] = sz;
@@ -212,25 +214,81 @@ void k_p2p(
   }
 }
 
-// split of the work items by sink count (at most 32, or more)
-__global__ void k_item_flags(const int2* __restrict__ items, int64_t n_items,
+// ------------------------------------------------------------------ work units
+// Length of a unit in list records: the whole list of an item unless that
+// leaves fewer than `want` units (few items: a wavefront would then run through
+// a long list alone while most of the chip idles), but at most twice the mean
+// list, so that the few long lists (outlying groups of widely spaced particles
+// pair with a large part of the set) do not keep one wavefront busy after the
+// others have ended: 2^24 grid with ten such groups 101 -> 68 ms in the pair
+// kernel (134 -> 98 ms in its sink-side adjoint); a 10 k Plummer sphere 0.72 ->
+// 0.10 ms in the expansion kernels.
+__host__ __device__ inline int64_t unit_length(int64_t records, int64_t G, int64_t NI, int64_t lo,
+                                               int64_t want) {
+  const int64_t mean = records / G + 1, all = mean * NI;
+  int64_t c = all / want + 1;
+  if (c > 2 * mean) c = 2 * mean;
+  if (c < lo) c = lo;
+  if (c > 64) c = (c + 63) / 64 * 64;
+  return c;
+}
+// pair units: eight wavefronts per SIMD, of at least 4 segments (some 250
+// sources); expansion units: four, of at least 16 entries
+constexpr int64_t kPairUnits = 8192, kPairUnitMin = 4, kExpUnits = 4096, kExpUnitMin = 16;
+
+// units and, in the high word, partial-sum slots of every item: its pair list,
+// its expansion list if it has at most 32 sinks, or more
+__global__ void k_unit_count(const int2* __restrict__ items, int64_t NI, int64_t G,
                              const int32_t* __restrict__ g_first,
-                             const int32_t* __restrict__ g_count, uint32_t* __restrict__ small) {
+                             const int32_t* __restrict__ g_count,
+                             const int64_t* __restrict__ pseg_off,
+                             const int64_t* __restrict__ m2p_off, int64_t* __restrict__ np,
+                             int64_t* __restrict__ nsmall, int64_t* __restrict__ nbig) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_items) return;
+  if (k >= NI) return;
   const int2 it = items[k];
-  small[k] = g_first[it.x] + g_count[it.x] - it.y <= 32 ? 1u : 0u;
+  const int64_t lp = unit_length(pseg_off[G], G, NI, kPairUnitMin, kPairUnits);
+  const int64_t lm = unit_length(m2p_off[G], G, NI, kExpUnitMin, kExpUnits);
+  auto units = [](int64_t n, int64_t l) {
+    const int64_t u = n > l ? (n + l - 1) / l : 1;
+    return u | (u > 1 ? u << 32 : 0);
+  };
+  np[k] = units(pseg_off[it.x + 1] - pseg_off[it.x], lp);
+  const int64_t m = units(m2p_off[it.x + 1] - m2p_off[it.x], lm);
+  const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
+  nsmall[k] = small ? m : 0;
+  nbig[k] = small ? 0 : m;
 }
 
-__global__ void k_item_split(const int2* __restrict__ items, int64_t n_items,
-                             const uint32_t* __restrict__ small, const uint32_t* __restrict__ pos,
-                             int2* __restrict__ out_small, int2* __restrict__ out_big) {
+// the units and slots from the scanned counts (totals: pair, small, big)
+__global__ void k_unit_fill(const int2* __restrict__ items, int64_t NI, int64_t G,
+                            const int32_t* __restrict__ g_first,
+                            const int32_t* __restrict__ g_count,
+                            const int64_t* __restrict__ pseg_off,
+                            const int64_t* __restrict__ m2p_off, const int64_t* __restrict__ np,
+                            const int64_t* __restrict__ nsmall, const int64_t* __restrict__ nbig,
+                            const int64_t* __restrict__ totals, int4* __restrict__ punits,
+                            int4* __restrict__ munits, int4* __restrict__ pslots,
+                            int4* __restrict__ mslots) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_items) return;
-  if (small[k])
-    out_small[pos[k]] = items[k];
-  else
-    out_big[k - (int64_t)pos[k]] = items[k];
+  if (k >= NI) return;
+  const int2 it = items[k];
+  auto fill = [&](int64_t n, int64_t l, int64_t unit, int64_t slot, int4* units, int4* slots) {
+    const int u = n > l ? (int)((n + l - 1) / l) : 1;
+    for (int j = 0; j < u; ++j) {
+      const int64_t end = (j + 1) * l < n ? (j + 1) * l : n;
+      units[unit + j] = make_int4((int)k, (int)(j * l), (int)end, u > 1 ? (int)slot + j : -1);
+      if (u > 1) slots[slot + j] = make_int4((int)k, (int)slot, j == 0 ? u : 0, 0);
+    }
+  };
+  fill(pseg_off[it.x + 1] - pseg_off[it.x],
+       unit_length(pseg_off[G], G, NI, kPairUnitMin, kPairUnits), np[k] & 0xffffffffll, np[k] >> 32,
+       punits, pslots);
+  // small items first
+  const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
+  const int64_t at = small ? nsmall[k] : nbig[k] + totals[1];
+  fill(m2p_off[it.x + 1] - m2p_off[it.x], unit_length(m2p_off[G], G, NI, kExpUnitMin, kExpUnits),
+       at & 0xffffffffll, at >> 32, munits, mslots);
 }
 
 template <typename T>
@@ -249,14 +307,14 @@ __global__ void k_finalize(const T* __restrict__ state, const uint32_t* __restri
 template <typename T, bool POT>
 void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1, T* state) {
   const unsigned* mdiff = ctx->d_flags + kFlagMass;
-  const unsigned grid = grid_for(t->n_items, kWavesPerBlock);
+  const unsigned grid = grid_for(t->n_punits, kWavesPerBlock);
   const T e2 = (T)(eps * eps);
   const T ie = k1 ? (T)(1.0 / eps) : T(0);
   auto go = [&](auto kern) {
-    kern<<<grid, kB, 0, ctx->stream>>>(t->items.as<int2>(), t->n_items,
+    kern<<<grid, kB, 0, ctx->stream>>>(t->punits.as<int4>(), t->n_punits, t->items.as<int2>(),
                                        t->pseg_off.as<int64_t>(), t->pseg.as<PairSeg>(),
                                        t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), off,
-                                       e2, ie, mdiff, state, t->n);
+                                       e2, ie, mdiff, state, t->unit_part.as<T>());
     HOT_CHECK_LAUNCH();
   };
   if (k1)
@@ -265,33 +323,51 @@ void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1
     go(k_p2p<T, POT, false, false>);
   else
     go(k_p2p<T, POT, true, false>);
+  sum_units<T, POT ? 4 : 3, false>(ctx, t, t->pslots, t->n_pslots, state);
 }
 
 }  // namespace
 
-// Items of at most 32 sinks and the others, listed apart (built with the tree)
-void split_items(hot_ctx* ctx, hot_tree* t) {
+// Needs the lists and the pair segments; synchronises once for the sizes.
+void build_units(hot_ctx* ctx, hot_tree* t) {
   hipStream_t st = ctx->stream;
-  const int64_t NI = t->n_items;
-  DBuf flag, pos;
-  flag.alloc(ctx, std::max<int64_t>(1, NI) * sizeof(uint32_t));
-  pos.alloc(ctx, (NI + 1) * sizeof(uint32_t));
-  k_item_flags<<<grid_for(NI, kB), kB, 0, st>>>(t->items.as<int2>(), NI, t->g_first.as<int32_t>(),
-                                               t->g_count.as<int32_t>(), flag.as<uint32_t>());
+  const int64_t NI = t->n_items, G = t->n_groups;
+  DBuf np, ns, nb, tot;
+  np.alloc(ctx, NI * sizeof(int64_t));
+  ns.alloc(ctx, NI * sizeof(int64_t));
+  nb.alloc(ctx, NI * sizeof(int64_t));
+  tot.alloc(ctx, 4 * sizeof(int64_t));
+  const int64_t *po = t->pseg_off.as<int64_t>(), *mo = t->m2p_off.as<int64_t>();
+  int64_t *cp = np.as<int64_t>(), *cs = ns.as<int64_t>(), *cb = nb.as<int64_t>(),
+          *dt = tot.as<int64_t>();
+  k_unit_count<<<grid_for(NI, kB), kB, 0, st>>>(t->items.as<int2>(), NI, G,
+                                               t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
+                                               po, mo, cp, cs, cb);
   HOT_CHECK_LAUNCH();
-  // exclusive offsets of the small items, their number in the last slot
-  uint32_t* pp = pos.as<uint32_t>();
-  scan_u32(ctx, flag.as<uint32_t>(), pp, NI, pp + NI);
-  uint32_t ns = 0;
-  HOT_HIP(hipMemcpyAsync(&ns, pp + NI, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+  scan_i64(ctx, cp, cp, NI, dt);
+  scan_i64(ctx, cs, cs, NI, dt + 1);
+  scan_i64(ctx, cb, cb, NI, dt + 2);
+  int64_t h[3] = {0, 0, 0};
+  HOT_HIP(hipMemcpyAsync(h, dt, sizeof(h), hipMemcpyDeviceToHost, st));
   HOT_HIP(hipStreamSynchronize(st));
-  t->items_small.alloc(ctx, std::max<int64_t>(1, (int64_t)ns) * sizeof(int2));
-  t->items_big.alloc(ctx, std::max<int64_t>(1, NI - (int64_t)ns) * sizeof(int2));
-  k_item_split<<<grid_for(NI, kB), kB, 0, st>>>(t->items.as<int2>(), NI, flag.as<uint32_t>(), pp,
-                                               t->items_small.as<int2>(), t->items_big.as<int2>());
+  const int64_t lo = 0xffffffffll;
+  t->n_punits = h[0] & lo;
+  t->n_pslots = h[0] >> 32;
+  t->n_munits_small = h[1] & lo;
+  t->n_munits = (h[1] & lo) + (h[2] & lo);
+  t->n_mslots = (h[1] >> 32) + (h[2] >> 32);
+  auto room = [](int64_t n) { return (size_t)std::max<int64_t>(1, n) * sizeof(int4); };
+  t->punits.alloc(ctx, room(t->n_punits));
+  t->munits.alloc(ctx, room(t->n_munits));
+  t->pslots.alloc(ctx, room(t->n_pslots));
+  t->mslots.alloc(ctx, room(t->n_mslots));
+  t->unit_part.alloc(ctx, (size_t)std::max<int64_t>(1, std::max(t->n_pslots, t->n_mslots)) *
+                              kUnitSums * sizeof(double));
+  k_unit_fill<<<grid_for(NI, kB), kB, 0, st>>>(
+      t->items.as<int2>(), NI, G, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), po, mo, cp,
+      cs, cb, dt, t->punits.as<int4>(), t->munits.as<int4>(), t->pslots.as<int4>(),
+      t->mslots.as<int4>());
   HOT_CHECK_LAUNCH();
-  t->n_items_small = ns;
-  t->n_items_big = NI - (int64_t)ns;
 }
 
 namespace {
@@ -342,7 +418,6 @@ void forces_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, 
     cf.hsub = t->hsub.as<T>();
     cf.tsub = t->tsub.as<T>();
   }
-  if (t->n_items_small < 0) ::hot::state("tree without its item split");
   if (stats) HOT_HIP(hipEventRecord(ctx->ev[0], st));
   {
     Phase ph(ctx, HOT_T_EVAL_P2P);

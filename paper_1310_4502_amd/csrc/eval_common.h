@@ -210,4 +210,53 @@ __device__ __forceinline__ bool newton_ok(const NewtonRule& r, double d, int c, 
   return d >= r.bmax[c] + (double)r.reach[c] * r.nq;
 }
 
+// Partial sums of the items whose lists are divided, added up in unit order,
+// one wavefront per first slot: into the sinks' sums (ADD), or as them.
+// NC: components, sums at [d], compensations at [4 + d].
+template <typename T, int NC, bool ADD>
+__global__ __launch_bounds__(64) void k_unit_sum(const int4* __restrict__ slots, int64_t n_slots,
+                                                 const int2* __restrict__ items,
+                                                 const int32_t* __restrict__ g_first,
+                                                 const int32_t* __restrict__ g_count,
+                                                 const T* __restrict__ part,
+                                                 T* __restrict__ state) {
+  const int64_t k = blockIdx.x;
+  if (k >= n_slots) return;
+  const int4 s = slots[k];
+  if (s.z == 0) return;
+  const int2 item = items[s.x];
+  const int i = item.y + (int)threadIdx.x;
+  if (i >= g_first[item.x] + g_count[item.x]) return;
+  T* st = state + (int64_t)i * 8;
+  T sum[NC], com[NC];
+#pragma unroll
+  for (int d = 0; d < NC; ++d) {
+    sum[d] = ADD ? st[d] : T(0);
+    com[d] = ADD ? st[4 + d] : T(0);
+  }
+  for (int u = 0; u < s.z; ++u) {
+    const T* p = part + (int64_t)(s.y + u) * kUnitSums + threadIdx.x * 8;
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {
+      kahan_add(sum[d], com[d], p[d]);
+      com[d] += p[4 + d];
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < NC; ++d) {
+    st[d] = sum[d];
+    st[4 + d] = com[d];
+  }
+}
+
+// adds up the divided items' partial sums after a kernel over work units
+template <typename T, int NC, bool ADD>
+inline void sum_units(hot_ctx* ctx, const hot_tree* t, const DBuf& slots, int64_t n, T* state) {
+  if (n <= 0) return;
+  k_unit_sum<T, NC, ADD><<<(unsigned)n, 64, 0, ctx->stream>>>(
+      slots.as<int4>(), n, t->items.as<int2>(), t->g_first.as<int32_t>(),
+      t->g_count.as<int32_t>(), t->unit_part.as<T>(), state);
+  HOT_CHECK_LAUNCH();
+}
+
 }  // namespace hot

@@ -29,6 +29,9 @@ struct FieldOp {
   // (at order 5 the spills cost more than the lanes gain: 2.2 against 1.2 ms)
   static constexpr bool fits(int p) { return sizeof(T) == 4 || p <= 4; }
   static constexpr bool one_sweep(int p) { return p <= 4; }
+  // FP64: for items of any size (24 k Plummer, order 4: 0.26 -> 0.16 ms); FP32
+  // items of more than 32 sinks are 20 % faster with a sink per lane
+  static constexpr bool any_size = sizeof(T) == 8;
   static constexpr int waves(int p) {
     return sizeof(T) == 8 ? (p <= 1 ? 4 : 2) : p <= 4 ? 4 : p <= 5 ? 3 : 2;
   }
@@ -62,6 +65,7 @@ struct JacobianOp {
   // the harmonic part takes 184 registers at order 7, 252 at order 8
   static constexpr bool fits(int p) { return sizeof(T) == 4 ? p <= 6 : p <= 3; }
   static constexpr bool one_sweep(int p) { return p <= 4; }
+  static constexpr bool any_size = false;
   static constexpr int waves(int p) {
     return sizeof(T) == 8 ? (p <= 1 ? 4 : 2) : p <= 4 ? 3 : 2;
   }
@@ -97,8 +101,9 @@ struct Coef {
 };
 
 struct ListArgs {
+  const int4* units;  // (item, first entry, end, slot of partial sums or -1)
+  int64_t n_units;
   const int2* items;
-  int64_t n_items;
   const int64_t* off;
   const int32_t* cell;
   const int8_t *order, *img, *sub;
@@ -161,14 +166,16 @@ template <int P, typename T, class Op, bool MIXQ, bool PER, bool BG>
 __global__ __launch_bounds__(64 * kExpandWaves) void k_expand(ListArgs A, Coef<T> cf,
                                                               const V4<T>* __restrict__ off,
                                                               const V4<T>* __restrict__ bar,
-                                                              T* __restrict__ state) {
+                                                              T* __restrict__ state,
+                                                              T* __restrict__ part) {
   constexpr int NC = Op::NC;
   __shared__ V4<T> s_rec[kExpandWaves][64];
   __shared__ T s_e2[kExpandWaves][64];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t it = (int64_t)blockIdx.x * kExpandWaves + w;
-  if (it >= A.n_items) return;
-  const int2 item = A.items[it];
+  const int64_t iu = (int64_t)blockIdx.x * kExpandWaves + w;
+  if (iu >= A.n_units) return;
+  const int4 unit = A.units[iu];
+  const int2 item = A.items[unit.x];
   const int g = uniform_i32(item.x);
   const int i = item.y + lane;
   const bool active = i < A.g_first[g] + A.g_count[g];
@@ -180,20 +187,26 @@ __global__ __launch_bounds__(64 * kExpandWaves) void k_expand(ListArgs A, Coef<T
   T sum[NC], com[NC];
 #pragma unroll
   for (int d = 0; d < NC; ++d) sum[d] = com[d] = T(0);
+  // an item's only unit continues its sums, others start at zero
+  const bool whole = uniform_i32(unit.w) < 0;
+  T* st = whole ? state + (int64_t)i * 8 : part + (int64_t)unit.w * kUnitSums + lane * 8;
   if (active) {
     me = off[i];
     if (Op::kBar) b = bar[i];
-    const T* st = state + (int64_t)i * 8;
+    if (whole) {
 #pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      sum[d] = st[d];
-      com[d] = st[4 + d];
+      for (int d = 0; d < NC; ++d) {
+        sum[d] = st[d];
+        com[d] = st[4 + d];
+      }
     }
   }
   const double bs = sink_radius<T>(me);  // idle lanes sit at the centre
   const T* __restrict__ hc = cf.h;
   const T* __restrict__ tc = cf.t;
-  const int64_t e0 = A.off[g], e1 = A.off[g + 1];
+  const T* __restrict__ hsub = cf.hsub;
+  const T* __restrict__ tsub = cf.tsub;
+  const int64_t e0 = A.off[g] + uniform_i32(unit.y), e1 = A.off[g] + uniform_i32(unit.z);
   for (int64_t eb = e0; eb < e1; eb += 64) {
     const int nb = e1 - eb < 64 ? (int)(e1 - eb) : 64;
     int cl = 0, fl = 0;  // cell; bit 0 Newtonian, bit 1 subtracted, order above
@@ -222,8 +235,8 @@ __global__ __launch_bounds__(64 * kExpandWaves) void k_expand(ListArgs A, Coef<T
       const int64_t c = __builtin_amdgcn_readlane(cl, k);
       const int f = __builtin_amdgcn_readlane(fl, k);
       const bool sub = BG && (f & 2);
-      const T* C = (sub ? cf.hsub : hc) + c * Op::hs(P);
-      const T* D = (sub ? cf.tsub : tc) + c * Op::ts(P);
+      const T* C = (sub ? hsub : hc) + c * Op::hs(P);
+      const T* D = (sub ? tsub : tc) + c * Op::ts(P);
       const T X = hot_fma(me.x, r.w, r.x);
       const T Y = hot_fma(me.y, r.w, r.y);
       const T Z = hot_fma(me.z, r.w, r.z);
@@ -258,7 +271,6 @@ __global__ __launch_bounds__(64 * kExpandWaves) void k_expand(ListArgs A, Coef<T
     }
   }
   if (active) {
-    T* st = state + (int64_t)i * 8;
 #pragma unroll
     for (int d = 0; d < NC; ++d) {
       st[d] = sum[d];
@@ -302,16 +314,18 @@ __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, Coef<T> cf,
                                                                     const V4<T>* __restrict__ off,
                                                                     const V4<T>* __restrict__ bar,
-                                                                    T* __restrict__ state) {
+                                                                    T* __restrict__ state,
+                                                                    T* __restrict__ part) {
   constexpr int NC = Op::NC, HS = Op::hs(P), TS = Op::ts(P), TR = TS > 0 ? TS : 4;
   constexpr int kRoom = 128;  // queue: fewer than 64 left over + 64 new
   __shared__ V4<T> q_rec[2][kRoom];
   __shared__ T q_e2[2][kRoom];
   __shared__ int q_cell[2][kRoom];
   const int lane = threadIdx.x;
-  const int64_t it = blockIdx.x;
-  if (it >= A.n_items) return;
-  const int2 item = A.items[it];
+  const int64_t iu = blockIdx.x;
+  if (iu >= A.n_units) return;
+  const int4 unit = A.units[iu];
+  const int2 item = A.items[unit.x];
   const int g = uniform_i32(item.x);
   const int ns = uniform_i32(min(64, A.g_first[g] + A.g_count[g] - item.y));
   const int gc = A.g_cell[g];
@@ -329,8 +343,10 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
   T sum[NC], com[NC];
 #pragma unroll
   for (int d = 0; d < NC; ++d) sum[d] = com[d] = T(0);
-  if (si < ns) {
-    const T* st = state + (int64_t)(item.y + si) * 8;
+  const bool whole = uniform_i32(unit.w) < 0;
+  T* st = whole ? state + (int64_t)(item.y + si) * 8
+                : part + (int64_t)unit.w * kUnitSums + si * 8;
+  if (whole && si < ns) {
 #pragma unroll
     for (int d = 0; d < NC; ++d) {
       sum[d] = st[d];
@@ -443,7 +459,7 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
       batch(full_c, n);
   };
   int have[2] = {0, 0};
-  const int64_t e0 = A.off[g], e1 = A.off[g + 1];
+  const int64_t e0 = A.off[g] + uniform_i32(unit.y), e1 = A.off[g] + uniform_i32(unit.z);
   for (int64_t eb = e0; eb < e1; eb += 64) {
     const bool in = eb + lane < e1;
     bool newton = false;
@@ -491,7 +507,6 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
     }
   }
   if (si < ns) {
-    T* st = state + (int64_t)(item.y + si) * 8;
 #pragma unroll
     for (int d = 0; d < NC; ++d) {
       st[d] = sum[d];
@@ -503,8 +518,9 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
 // ------------------------------------------------------------------ launches
 inline ListArgs list_args(const hot_tree* t, const NewtonRule& rule) {
   ListArgs A;
+  A.units = nullptr;
+  A.n_units = 0;
   A.items = t->items.as<int2>();
-  A.n_items = t->n_items;
   A.off = t->m2p_off.as<int64_t>();
   A.cell = t->m2p.as<int32_t>();
   A.order = t->m2p_q.as<int8_t>();
@@ -522,50 +538,46 @@ inline ListArgs list_args(const hot_tree* t, const NewtonRule& rule) {
 }
 
 // The expansion terms of every item added to state. Theta lists without
-// background subtraction whose items of at most 32 sinks are a tenth or more:
-// those with a cell per lane, the others with a sink per lane.
+// background subtraction where items of at most 32 sinks make a tenth of the
+// units or more: those with a cell per lane, the others with a sink per lane
+// (Op::any_size: all with a cell per lane).
 template <int P, typename T, class Op>
 void launch_expand(hot_ctx* ctx, const hot_tree* t, const V4<T>* off, const V4<T>* bar,
                    const Coef<T>& cf, double eps, T* state) {
   ListArgs A = list_args(t, newton_rule<T>(t, eps, Op::kBar));
-  auto go = [&](auto kern, const int2* items, int64_t n, int waves) {
+  auto go = [&](auto kern, int64_t first, int64_t n, int waves) {
     if (n <= 0) return;
-    A.items = items;
-    A.n_items = n;
-    kern<<<grid_for(n, waves), 64 * waves, 0, ctx->stream>>>(A, cf, off, bar, state);
+    A.units = t->munits.as<int4>() + first;
+    A.n_units = n;
+    kern<<<grid_for(n, waves), 64 * waves, 0, ctx->stream>>>(A, cf, off, bar, state,
+                                                             t->unit_part.as<T>());
     HOT_CHECK_LAUNCH();
   };
-  const int2* all = t->items.as<int2>();
+  const int64_t all = t->n_munits, small = t->n_munits_small;
   const int W = kExpandWaves;
   if (t->list_p >= 0) {
     if (t->periodic)
-      go(k_expand<P, T, Op, true, true, false>, all, t->n_items, W);
+      go(k_expand<P, T, Op, true, true, false>, 0, all, W);
     else
-      go(k_expand<P, T, Op, true, false, false>, all, t->n_items, W);
-    return;
-  }
-  if (t->bg) {
+      go(k_expand<P, T, Op, true, false, false>, 0, all, W);
+  } else if (t->bg) {
     // potentials are refused with background subtraction: no variant for them
-    if constexpr (Op::NC == 3) go(k_expand<P, T, Op, false, true, true>, all, t->n_items, W);
-    return;
-  }
-  if constexpr (Op::fits(P)) {
-    if (t->n_items_small >= 0 && t->n_items_small * 10 >= t->n_items) {
-      const int2 *big = t->items_big.as<int2>(), *small = t->items_small.as<int2>();
-      if (t->periodic) {
-        go(k_expand<P, T, Op, false, true, false>, big, t->n_items_big, W);
-        go(k_expand_cl<P, T, Op, true>, small, t->n_items_small, 1);
-      } else {
-        go(k_expand<P, T, Op, false, false, false>, big, t->n_items_big, W);
-        go(k_expand_cl<P, T, Op, false>, small, t->n_items_small, 1);
-      }
-      return;
+    if constexpr (Op::NC == 3) go(k_expand<P, T, Op, false, true, true>, 0, all, W);
+  } else {
+    int64_t cl = 0;  // units that take a cell per lane
+    if constexpr (Op::fits(P)) {
+      cl = Op::any_size ? all : small * 10 >= all ? small : 0;
+      if (t->periodic)
+        go(k_expand_cl<P, T, Op, true>, 0, cl, 1);
+      else
+        go(k_expand_cl<P, T, Op, false>, 0, cl, 1);
     }
+    if (t->periodic)
+      go(k_expand<P, T, Op, false, true, false>, cl, all - cl, W);
+    else
+      go(k_expand<P, T, Op, false, false, false>, cl, all - cl, W);
   }
-  if (t->periodic)
-    go(k_expand<P, T, Op, false, true, false>, all, t->n_items, W);
-  else
-    go(k_expand<P, T, Op, false, false, false>, all, t->n_items, W);
+  sum_units<T, Op::NC, true>(ctx, t, t->mslots, t->n_mslots, state);
 }
 
 template <typename T, class Op>

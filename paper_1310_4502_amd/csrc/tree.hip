@@ -700,7 +700,6 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
                                             t->g_count.as<int32_t>(), t->item_of.as<int32_t>());
   HOT_CHECK_LAUNCH();
   t->c_bmax2.release();
-  split_items(ctx, t);
 }
 
 void hash_lookup(hot_ctx* ctx, const hot_tree* t, const uint64_t* keys, int32_t* out, int64_t nq) {

@@ -996,6 +996,7 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
   t->bg = BG;
   t->bg_width = width;
   build_pair_segs(ctx, t);
+  build_units(ctx, t);
   t->has_lists = true;
 }
 
