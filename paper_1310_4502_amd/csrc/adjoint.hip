@@ -1178,6 +1178,7 @@ __global__ void k_adj_finalize(const T* __restrict__ sink, const T* __restrict__
 void build_transpose(hot_ctx* ctx, hot_tree* t) {
   hipStream_t st = ctx->stream;
   const int64_t G = t->n_groups, C = t->n_cells, NI = t->n_items;
+  Readback rb(ctx);
   // ---- pair records by source item
   {
     DBuf cnt, tot;
@@ -1189,8 +1190,8 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
     HOT_CHECK_LAUNCH();
     scan_i64(ctx, cnt.as<int64_t>(), cnt.as<int64_t>(), G, tot.as<int64_t>());
     int64_t nrec = 0;
-    HOT_HIP(hipMemcpyAsync(&nrec, tot.p, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HOT_HIP(hipStreamSynchronize(st));
+    rb.add(tot.p, &nrec, sizeof(int64_t));
+    rb.run();
     if (nrec >= (int64_t)INT32_MAX - 128) throw Error{HOT_E_CAPACITY, "too many P2P records"};
     t->n_srec = nrec;
     const int gbits = bits_for(G);
@@ -1223,8 +1224,8 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
     uint32_t* uoff = t->schunk_off.as<uint32_t>();
     scan_u32(ctx, ucnt.as<uint32_t>(), uoff, NI, uoff + NI);
     uint32_t nu = 0;
-    HOT_HIP(hipMemcpyAsync(&nu, uoff + NI, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HOT_HIP(hipStreamSynchronize(st));
+    rb.add(uoff + NI, &nu, sizeof(uint32_t));
+    rb.run();
     t->n_schunk = nu;
     t->schunk.alloc(ctx, std::max<int64_t>(1, (int64_t)nu) * sizeof(int4));
     k_sunit_fill<<<grid_for(NI, kB), kB, 0, st>>>(t->srec_off.as<uint32_t>(), NI, chunk,
@@ -1267,9 +1268,8 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
     scan_u32(ctx, t->mcell_item.as<uint32_t>(), t->mcell_item.as<uint32_t>(), C,
              t->mcell_item.as<uint32_t>() + C);
     uint32_t nci = 0;
-    HOT_HIP(hipMemcpyAsync(&nci, t->mcell_item.as<uint32_t>() + C, sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    HOT_HIP(hipStreamSynchronize(st));
+    rb.add(t->mcell_item.as<uint32_t>() + C, &nci, sizeof(uint32_t));
+    rb.run();
     t->n_citems = nci;
     t->citem_rec.alloc(ctx, std::max<int64_t>(1, nci) * sizeof(uint32_t));
     t->citem_cell.alloc(ctx, std::max<int64_t>(1, nci) * sizeof(int32_t));
@@ -1291,8 +1291,8 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
       k_lower_bound<<<1, kB, 0, st>>>(qkey.as<uint64_t>(), nci, 0, kMaxP + 1, qoff.as<uint32_t>());
       HOT_CHECK_LAUNCH();
       uint32_t h[kMaxP + 2];
-      HOT_HIP(hipMemcpyAsync(h, qoff.p, sizeof(h), hipMemcpyDeviceToHost, st));
-      HOT_HIP(hipStreamSynchronize(st));
+      rb.add(qoff.p, h, sizeof(h));
+      rb.run();
       for (int q = 0; q <= kMaxP + 1; ++q) t->qitem_off[q] = h[q];
     } else {
       t->citem_end.release();
@@ -1319,15 +1319,14 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
                                                   dmax.as<unsigned>());
       HOT_CHECK_LAUNCH();
       unsigned mx = 0;
-      HOT_HIP(hipMemcpyAsync(&mx, dmax.p, sizeof(unsigned), hipMemcpyDeviceToHost, st));
-      HOT_HIP(hipStreamSynchronize(st));
+      rb.add(dmax.p, &mx, sizeof(unsigned));
+      rb.run();
       if (mx <= (unsigned)kSegChunk) break;
       scan_u32(ctx, t->mred_off[lev].as<uint32_t>(), t->mred_off[lev].as<uint32_t>(), C,
                t->mred_off[lev].as<uint32_t>() + C);
       uint32_t n_out = 0;
-      HOT_HIP(hipMemcpyAsync(&n_out, t->mred_off[lev].as<uint32_t>() + C, sizeof(uint32_t),
-                             hipMemcpyDeviceToHost, st));
-      HOT_HIP(hipStreamSynchronize(st));
+      rb.add(t->mred_off[lev].as<uint32_t>() + C, &n_out, sizeof(uint32_t));
+      rb.run();
       t->mred_n[lev] = n_out;
       t->mred_levels = lev + 1;
       off = t->mred_off[lev].as<uint32_t>();

@@ -2,6 +2,7 @@
 // reporting, host-copy getters. The computation itself lives in the other
 // translation units.
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <new>
 
@@ -92,6 +93,29 @@ void* scratch_address(int device) {
 
 namespace hot {
 
+__global__ void k_readback(Readback::Args a, uint32_t* __restrict__ out) {
+  int at = 0;
+  for (int i = 0; i < a.n; ++i) {
+    for (int w = threadIdx.x; w < a.words[i]; w += blockDim.x) out[at + w] = a.src[i][w];
+    at += a.words[i];
+  }
+}
+
+void Readback::run() {
+  size_t words = 0;
+  for (int i = 0; i < a.n; ++i) words += (size_t)a.words[i];
+  if (words * 4 > kPinBytes) throw Error{HOT_E_DEVICE, "readback exceeds its page"};
+  k_readback<<<1, 64, 0, ctx->stream>>>(a, ctx->pin_dev);
+  HOT_CHECK_LAUNCH();
+  HOT_HIP(hipStreamSynchronize(ctx->stream));
+  const uint32_t* p = ctx->pin;
+  for (int i = 0; i < a.n; ++i) {
+    std::memcpy(dst[i], p, (size_t)a.words[i] * 4);
+    p += a.words[i];
+  }
+  a.n = 0;
+}
+
 void zero_flag_word(hot_ctx* ctx, int word) {
   k_zero_flags<<<1, 1, 0, ctx->stream>>>(ctx->d_flags + word);
   HOT_CHECK_LAUNCH();
@@ -141,6 +165,11 @@ int hot_ctx_create(int device, void* hip_stream, const hot_allocator* allocator,
     k_zero_flag_words<<<1, 16, 0, c->stream>>>(c->d_flags);
     HOT_CHECK_LAUNCH();
     for (auto& e : c->ev) HOT_HIP(hipEventCreate(&e));
+    void* pin = nullptr;
+    HOT_HIP(hipHostMalloc(&pin, hot::kPinBytes, hipHostMallocDefault));
+    c->pin = static_cast<uint32_t*>(pin);
+    HOT_HIP(hipHostGetDevicePointer(&pin, c->pin, 0));
+    c->pin_dev = static_cast<uint32_t*>(pin);
     HOT_HIP(hipStreamSynchronize(c->stream));
   });
   if (rc != HOT_OK) {
@@ -148,6 +177,7 @@ int hot_ctx_create(int device, void* hip_stream, const hot_allocator* allocator,
     for (auto& e : c->ev)
       if (e) (void)hipEventDestroy(e);
     if (c->d_flags) (void)hipFree(c->d_flags);
+    if (c->pin) (void)hipHostFree(c->pin);
     delete c;
     return rc;
   }
@@ -170,6 +200,7 @@ int hot_ctx_destroy(hot_ctx* ctx) {
   for (auto& e : ctx->tev)
     if (e) (void)hipEventDestroy(e);
   if (ctx->d_flags) (void)hipFree(ctx->d_flags);
+  if (ctx->pin) (void)hipHostFree(ctx->pin);
   delete ctx;
   return HOT_OK;
 }

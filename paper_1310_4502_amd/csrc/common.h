@@ -138,6 +138,9 @@ struct hot_ctx {
   // first use
   hipStream_t aux = nullptr;
   hipEvent_t xev[2]{};
+  // a page of pinned host memory that Readback's kernel writes to
+  uint32_t* pin = nullptr;
+  uint32_t* pin_dev = nullptr;
   // phase timers (hot_set_timing): start and end event of every phase, and
   // whether the phase has been recorded since timing was switched on
   bool timing = false;
@@ -172,6 +175,30 @@ struct Phase {
   }
   Phase(const Phase&) = delete;
   Phase& operator=(const Phase&) = delete;
+};
+
+// Small device values handed to the host together: one kernel writes them to
+// the context's pinned page and the stream is waited for once (a copy to
+// pageable memory each costs a round trip of its own, some 15 us).
+constexpr size_t kPinBytes = 4096;
+struct Readback {
+  static constexpr int kMax = 8;
+  struct Args {
+    const uint32_t* src[kMax];
+    int words[kMax];
+    int n = 0;
+  };
+  hot_ctx* ctx;
+  Args a;
+  void* dst[kMax];
+  explicit Readback(hot_ctx* c) : ctx(c) {}
+  // bytes: a multiple of 4
+  void add(const void* dev, void* host, size_t bytes) {
+    a.src[a.n] = static_cast<const uint32_t*>(dev);
+    a.words[a.n] = (int)(bytes / 4);
+    dst[a.n++] = host;
+  }
+  void run();  // waits for the context's stream
 };
 
 // A device allocation owned by a tree or by a call.
@@ -327,8 +354,10 @@ void scan_i64(hot_ctx* ctx, const int64_t* in, int64_t* out, int64_t n, int64_t*
 void radix_sort(hot_ctx* ctx, DBuf& keys, DBuf& vals, int64_t n, int bits, int lo = 0);
 
 void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box);
-// the work units of the current lists
-void build_units(hot_ctx* ctx, hot_tree* t);
+// the work units of the current lists: counts (sc: 3 n_items + 1 words) after
+// the pair segments' offsets, then the units from the counts read back (h)
+void count_units(hot_ctx* ctx, hot_tree* t, DBuf& sc, Readback& rb, int64_t* h);
+void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h);
 void gather_sorted(hot_ctx* ctx, const hot_tree* t, const double* pos, const double* mass,
                    double* spos, double* smass, int check_mass);
 void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, int p);

@@ -237,13 +237,12 @@ __host__ __device__ inline int64_t unit_length(int64_t records, int64_t G, int64
 constexpr int64_t kPairUnits = 8192, kPairUnitMin = 4, kExpUnits = 4096, kExpUnitMin = 16;
 
 // units and, in the high word, partial-sum slots of every item: its pair list,
-// its expansion list if it has at most 32 sinks, or more
+// its expansion list if it has at most 32 sinks, or more (three runs of NI)
 __global__ void k_unit_count(const int2* __restrict__ items, int64_t NI, int64_t G,
                              const int32_t* __restrict__ g_first,
                              const int32_t* __restrict__ g_count,
                              const int64_t* __restrict__ pseg_off,
-                             const int64_t* __restrict__ m2p_off, int64_t* __restrict__ np,
-                             int64_t* __restrict__ nsmall, int64_t* __restrict__ nbig) {
+                             const int64_t* __restrict__ m2p_off, int64_t* __restrict__ sc) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= NI) return;
   const int2 it = items[k];
@@ -253,27 +252,26 @@ __global__ void k_unit_count(const int2* __restrict__ items, int64_t NI, int64_t
     const int64_t u = n > l ? (n + l - 1) / l : 1;
     return u | (u > 1 ? u << 32 : 0);
   };
-  np[k] = units(pseg_off[it.x + 1] - pseg_off[it.x], lp);
   const int64_t m = units(m2p_off[it.x + 1] - m2p_off[it.x], lm);
   const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
-  nsmall[k] = small ? m : 0;
-  nbig[k] = small ? 0 : m;
+  sc[k] = units(pseg_off[it.x + 1] - pseg_off[it.x], lp);
+  sc[NI + k] = small ? m : 0;
+  sc[2 * NI + k] = small ? 0 : m;
 }
 
-// the units and slots from the scanned counts (totals: pair, small, big)
+// the units and slots from the scanned counts
 __global__ void k_unit_fill(const int2* __restrict__ items, int64_t NI, int64_t G,
                             const int32_t* __restrict__ g_first,
                             const int32_t* __restrict__ g_count,
                             const int64_t* __restrict__ pseg_off,
-                            const int64_t* __restrict__ m2p_off, const int64_t* __restrict__ np,
-                            const int64_t* __restrict__ nsmall, const int64_t* __restrict__ nbig,
-                            const int64_t* __restrict__ totals, int4* __restrict__ punits,
-                            int4* __restrict__ munits, int4* __restrict__ pslots,
-                            int4* __restrict__ mslots) {
+                            const int64_t* __restrict__ m2p_off, const int64_t* __restrict__ sc,
+                            int4* __restrict__ punits, int4* __restrict__ munits,
+                            int4* __restrict__ pslots, int4* __restrict__ mslots) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= NI) return;
   const int2 it = items[k];
-  auto fill = [&](int64_t n, int64_t l, int64_t unit, int64_t slot, int4* units, int4* slots) {
+  auto fill = [&](int64_t n, int64_t l, int64_t at, int4* units, int4* slots) {
+    const int64_t unit = at & 0xffffffffll, slot = at >> 32;
     const int u = n > l ? (int)((n + l - 1) / l) : 1;
     for (int j = 0; j < u; ++j) {
       const int64_t end = (j + 1) * l < n ? (j + 1) * l : n;
@@ -282,13 +280,11 @@ __global__ void k_unit_fill(const int2* __restrict__ items, int64_t NI, int64_t 
     }
   };
   fill(pseg_off[it.x + 1] - pseg_off[it.x],
-       unit_length(pseg_off[G], G, NI, kPairUnitMin, kPairUnits), np[k] & 0xffffffffll, np[k] >> 32,
-       punits, pslots);
+       unit_length(pseg_off[G], G, NI, kPairUnitMin, kPairUnits), sc[k], punits, pslots);
   // small items first
   const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
-  const int64_t at = small ? nsmall[k] : nbig[k] + totals[1];
   fill(m2p_off[it.x + 1] - m2p_off[it.x], unit_length(m2p_off[G], G, NI, kExpUnitMin, kExpUnits),
-       at & 0xffffffffll, at >> 32, munits, mslots);
+       sc[(small ? NI : 2 * NI) + k] - sc[NI], munits, mslots);
 }
 
 template <typename T>
@@ -328,34 +324,25 @@ void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1
 
 }  // namespace
 
-// Needs the lists and the pair segments; synchronises once for the sizes.
-void build_units(hot_ctx* ctx, hot_tree* t) {
-  hipStream_t st = ctx->stream;
-  const int64_t NI = t->n_items, G = t->n_groups;
-  DBuf np, ns, nb, tot;
-  np.alloc(ctx, NI * sizeof(int64_t));
-  ns.alloc(ctx, NI * sizeof(int64_t));
-  nb.alloc(ctx, NI * sizeof(int64_t));
-  tot.alloc(ctx, 4 * sizeof(int64_t));
-  const int64_t *po = t->pseg_off.as<int64_t>(), *mo = t->m2p_off.as<int64_t>();
-  int64_t *cp = np.as<int64_t>(), *cs = ns.as<int64_t>(), *cb = nb.as<int64_t>(),
-          *dt = tot.as<int64_t>();
-  k_unit_count<<<grid_for(NI, kB), kB, 0, st>>>(t->items.as<int2>(), NI, G,
-                                               t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
-                                               po, mo, cp, cs, cb);
+void count_units(hot_ctx* ctx, hot_tree* t, DBuf& sc, Readback& rb, int64_t* h) {
+  const int64_t NI = t->n_items;
+  sc.alloc(ctx, (3 * NI + 1) * sizeof(int64_t));
+  int64_t* c = sc.as<int64_t>();
+  k_unit_count<<<grid_for(NI, kB), kB, 0, ctx->stream>>>(
+      t->items.as<int2>(), NI, t->n_groups, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
+      t->pseg_off.as<int64_t>(), t->m2p_off.as<int64_t>(), c);
   HOT_CHECK_LAUNCH();
-  scan_i64(ctx, cp, cp, NI, dt);
-  scan_i64(ctx, cs, cs, NI, dt + 1);
-  scan_i64(ctx, cb, cb, NI, dt + 2);
-  int64_t h[3] = {0, 0, 0};
-  HOT_HIP(hipMemcpyAsync(h, dt, sizeof(h), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
-  const int64_t lo = 0xffffffffll;
+  scan_i64(ctx, c, c, 3 * NI, c + 3 * NI);
+  for (int k = 0; k < 3; ++k) rb.add(c + (k + 1) * NI, h + k, sizeof(int64_t));
+}
+
+void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h) {
+  const int64_t NI = t->n_items, lo = 0xffffffffll;
   t->n_punits = h[0] & lo;
   t->n_pslots = h[0] >> 32;
-  t->n_munits_small = h[1] & lo;
-  t->n_munits = (h[1] & lo) + (h[2] & lo);
-  t->n_mslots = (h[1] >> 32) + (h[2] >> 32);
+  t->n_munits_small = (h[1] - h[0]) & lo;
+  t->n_munits = (h[2] - h[0]) & lo;
+  t->n_mslots = (h[2] - h[0]) >> 32;
   auto room = [](int64_t n) { return (size_t)std::max<int64_t>(1, n) * sizeof(int4); };
   t->punits.alloc(ctx, room(t->n_punits));
   t->munits.alloc(ctx, room(t->n_munits));
@@ -363,10 +350,10 @@ void build_units(hot_ctx* ctx, hot_tree* t) {
   t->mslots.alloc(ctx, room(t->n_mslots));
   t->unit_part.alloc(ctx, (size_t)std::max<int64_t>(1, std::max(t->n_pslots, t->n_mslots)) *
                               kUnitSums * sizeof(double));
-  k_unit_fill<<<grid_for(NI, kB), kB, 0, st>>>(
-      t->items.as<int2>(), NI, G, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), po, mo, cp,
-      cs, cb, dt, t->punits.as<int4>(), t->munits.as<int4>(), t->pslots.as<int4>(),
-      t->mslots.as<int4>());
+  k_unit_fill<<<grid_for(NI, kB), kB, 0, ctx->stream>>>(
+      t->items.as<int2>(), NI, t->n_groups, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
+      t->pseg_off.as<int64_t>(), t->m2p_off.as<int64_t>(), sc.as<int64_t>(),
+      t->punits.as<int4>(), t->munits.as<int4>(), t->pslots.as<int4>(), t->mslots.as<int4>());
   HOT_CHECK_LAUNCH();
 }
 

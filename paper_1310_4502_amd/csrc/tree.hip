@@ -96,14 +96,21 @@ __global__ __launch_bounds__(kB) void k_bbox_partial(const double* __restrict__ 
 
 // Root cube: lo = per-axis minimum; side = the power of two at or above the
 // largest extent (1 if all points coincide). root = lo[3], side, 2^21/side.
-__global__ void k_bbox_final(const double* __restrict__ part, int nparts, double* __restrict__ root) {
-  if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ part, int nparts,
+                                                   double* __restrict__ root) {
   double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = 0; b < nparts; ++b)
+  for (int b = threadIdx.x; b < nparts; b += 64)
     for (int d = 0; d < 3; ++d) {
       mn[d] = fmin(mn[d], part[6 * b + d]);
       mx[d] = fmax(mx[d], part[6 * b + 3 + d]);
     }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+    for (int d = 0; d < 3; ++d) {
+      mn[d] = fmin(mn[d], __shfl_xor(mn[d], off));
+      mx[d] = fmax(mx[d], __shfl_xor(mx[d], off));
+    }
+  if (threadIdx.x != 0) return;
   double ext = 0.0;
   for (int d = 0; d < 3; ++d) ext = fmax(ext, mx[d] - mn[d]);
   double side = 1.0;
@@ -115,6 +122,14 @@ __global__ void k_bbox_final(const double* __restrict__ part, int nparts, double
   root[0] = mn[0];
   root[1] = mn[1];
   root[2] = mn[2];
+  root[3] = side;
+  root[4] = 2097152.0 / side;
+}
+
+__global__ void k_set_root(double x, double y, double z, double side, double* __restrict__ root) {
+  root[0] = x;
+  root[1] = y;
+  root[2] = z;
   root[3] = side;
   root[4] = 2097152.0 / side;
 }
@@ -517,8 +532,8 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
   // ---- root cube
   t->root.alloc(ctx, 8 * sizeof(double));
   if (box) {
-    double r[8] = {box[0], box[1], box[2], box[3], 2097152.0 / box[3], 0, 0, 0};
-    HOT_HIP(hipMemcpyAsync(t->root.p, r, sizeof(r), hipMemcpyHostToDevice, st));
+    k_set_root<<<1, 1, 0, st>>>(box[0], box[1], box[2], box[3], t->root.as<double>());
+    HOT_CHECK_LAUNCH();
     k_box_check<<<gb, kB, 0, st>>>(pos, n, t->root.as<double>(), lflags);
     HOT_CHECK_LAUNCH();
   } else {
@@ -562,10 +577,11 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
   int64_t lv[kMaxLevel + 2];
   double rootv[8];
   unsigned fw[2] = {0u, 0u};
-  HOT_HIP(hipMemcpyAsync(lv, tot.p, sizeof(lv), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(rootv, t->root.p, sizeof(rootv), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(fw, ctx->d_flags, sizeof(fw), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
+  Readback rb(ctx);
+  rb.add(tot.p, lv, sizeof(lv));
+  rb.add(t->root.p, rootv, sizeof(rootv));
+  rb.add(ctx->d_flags, fw, sizeof(fw));
+  rb.run();
   raise_deferred(ctx, fw[kFlagDeferred]);
   unsigned flags = fw[kFlagLocal];
   if (flags & FLAG_NONFINITE_POS) invalid("non-finite position");
@@ -625,8 +641,9 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
   k_fill<uint64_t><<<gc, kB, 0, st>>>(t->c_bmax2.as<uint64_t>(), C, 0ull);
   HOT_CHECK_LAUNCH();
   {
-    // chunks of at least 4096 particles, at most 2048 blocks
-    const int64_t nblk = std::max<int64_t>(1, std::min<int64_t>(2048, (n + 4095) / 4096));
+    // at most 2048 blocks (whose LDS slots save global atomics), of at least
+    // one round of particles: at 2^18 particles 64 blocks of 4096 took 158 us
+    const int64_t nblk = std::max<int64_t>(1, std::min<int64_t>(2048, (n + kB - 1) / kB));
     const int64_t chunk = ((n + nblk - 1) / nblk + kB - 1) / kB * kB;
     k_bmax<<<(unsigned)nblk, kB, 0, st>>>(t->key.as<uint64_t>(), t->lambda.as<uint8_t>(),
                                           t->spos.as<double>(), n, chunk, t->root.as<double>(),
@@ -651,9 +668,9 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
   HOT_CHECK_LAUNCH();
   scan_u32(ctx, gflag.as<uint32_t>(), gflag.as<uint32_t>(), n, gtot.as<uint32_t>());
   uint32_t G32 = 0;
-  HOT_HIP(hipMemcpyAsync(&G32, gtot.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&flags, lflags, sizeof(unsigned), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
+  rb.add(gtot.p, &G32, sizeof(uint32_t));
+  rb.add(lflags, &flags, sizeof(unsigned));
+  rb.run();
   if (flags & FLAG_HASH_FULL) throw Error{HOT_E_CAPACITY, "cell hash table full"};
   const int64_t G = G32;
   t->n_groups = G;
@@ -686,9 +703,9 @@ void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box)
                                     t->leaf_list.as<int32_t>());
   HOT_CHECK_LAUNCH();
   uint32_t NI = 0, NL = 0;
-  HOT_HIP(hipMemcpyAsync(&NI, ntot.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&NL, gtot.as<uint32_t>() + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
+  rb.add(ntot.p, &NI, sizeof(uint32_t));
+  rb.add(gtot.as<uint32_t>() + 1, &NL, sizeof(uint32_t));
+  rb.run();
   t->n_items = NI;
   t->n_leaves = NL;
   t->items.alloc(ctx, (size_t)NI * sizeof(int2));

@@ -589,33 +589,47 @@ __global__ __launch_bounds__(64) void k_walk_levels(
   }
 }
 
-__global__ void k_pair_weights(const int32_t* __restrict__ g_count, int64_t G,
-                               int64_t* __restrict__ pp, int64_t* __restrict__ mp) {
+// totals over the groups of sinks x pair-summed sources and of sinks x cells
+__global__ void k_pair_totals(const int32_t* __restrict__ g_count, int64_t G,
+                              const int64_t* __restrict__ pp, const int64_t* __restrict__ mp,
+                              unsigned long long* __restrict__ tot) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  pp[g] *= g_count[g];
-  mp[g] *= g_count[g];
+  int64_t a = 0, b = 0;
+  if (g < G) {
+    a = pp[g] * g_count[g];
+    b = mp[g] * g_count[g];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    a += __shfl_xor(a, off);
+    b += __shfl_xor(b, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(tot, (unsigned long long)a);
+    atomicAdd(tot + 1, (unsigned long long)b);
+  }
 }
 
 // largest particle mass (the bit patterns of non-negative doubles order as
 // their values); flags non-finite or negative masses
 __global__ void k_mass_max(const double* __restrict__ mass, int64_t n,
                            unsigned long long* __restrict__ out, unsigned* __restrict__ flags) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double m = 0.0;
-  if (i < n) {
-    m = mass[i];
-    if (!(isfinite(m) && m >= 0.0)) {
-      atomicOr(flags, FLAG_BAD_MASS);
-      m = 0.0;
-    }
+  bool bad = false;
+  for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
+    const double v = mass[i];
+    if (isfinite(v) && v >= 0.0)
+      m = fmax(m, v);
+    else
+      bad = true;
   }
+  if (bad) atomicOr(flags, FLAG_BAD_MASS);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
   if ((threadIdx.x & 63) == 0 && m > 0.0) atomicMax(out, (unsigned long long)__double_as_longlong(m));
 }
 
-__global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
+__global__ void k_zero_u64(unsigned long long* p) { p[threadIdx.x] = 0ull; }
 
 }  // namespace
 
@@ -824,8 +838,8 @@ __global__ __launch_bounds__(kB) void k_pair_segs_flat(
   if (COUNT && lane == 0) cnt[g] = k;
 }
 
-// The pair-segment table of the current P2P lists (count, scan, one host
-// sync for the total, fill).
+// The pair-segment table of the current P2P lists and the work units of both
+// lists (counts, scans, one host sync for the totals, fill).
 void build_pair_segs(hot_ctx* ctx, hot_tree* t) {
   hipStream_t st = ctx->stream;
   const int64_t G = t->n_groups;
@@ -849,12 +863,16 @@ void build_pair_segs(hot_ctx* ctx, hot_tree* t) {
   HOT_CHECK_LAUNCH();
   int64_t* so = t->pseg_off.as<int64_t>();
   scan_i64(ctx, so, so, G, so + G);
-  int64_t ns = 0;
+  int64_t ns = 0, hu[3] = {0, 0, 0};
   unsigned fl = 0;
-  HOT_HIP(hipMemcpyAsync(&ns, so + G, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&fl, ctx->d_flags + kFlagLocal, sizeof(unsigned), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
+  DBuf units;
+  Readback rb(ctx);
+  rb.add(so + G, &ns, sizeof(int64_t));
+  rb.add(ctx->d_flags + kFlagLocal, &fl, sizeof(unsigned));
+  count_units(ctx, t, units, rb, hu);
+  rb.run();
   if (fl & FLAG_INTERNAL) throw Error{HOT_E_DEVICE, "pair segment consistency check failed"};
+  build_units(ctx, t, units, hu);
   t->n_psegs = ns;
   t->pseg.alloc(ctx, (size_t)std::max<int64_t>(1, ns) * sizeof(PairSeg));
   if (flat)
@@ -890,9 +908,8 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
     bg.cnt_box = t->box_off.as<int64_t>();
   }
   t->m2p_off.alloc(ctx, (G + 1) * sizeof(int64_t));
-  DBuf pairs, mcount, totals;
+  DBuf pairs, totals;
   pairs.alloc(ctx, (G + 1) * sizeof(int64_t));
-  mcount.alloc(ctx, (G + 1) * sizeof(int64_t));
   totals.alloc(ctx, 4 * sizeof(int64_t));
   // the error test has no theta
   DBuf wcells;
@@ -923,13 +940,13 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
   walk(std::false_type{}, t->p2p_off.as<int64_t>(), t->m2p_off.as<int64_t>(), pairs.as<int64_t>(),
        nullptr, nullptr, nullptr, nullptr, ctx->d_flags + kFlagLocal);
   // pair counts: P2P sources x sinks, M2P cells x sinks
-  HOT_HIP(hipMemcpyAsync(mcount.p, t->m2p_off.p, G * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
-  k_pair_weights<<<grid_for(G, kB), kB, 0, st>>>(t->g_count.as<int32_t>(), G, pairs.as<int64_t>(),
-                                                 mcount.as<int64_t>());
-  HOT_CHECK_LAUNCH();
   int64_t* tot = totals.as<int64_t>();
-  scan_i64(ctx, pairs.as<int64_t>(), pairs.as<int64_t>(), G, tot + 2);
-  scan_i64(ctx, mcount.as<int64_t>(), mcount.as<int64_t>(), G, tot + 3);
+  k_zero_u64<<<1, 2, 0, st>>>(totals.as<unsigned long long>());
+  HOT_CHECK_LAUNCH();
+  k_pair_totals<<<grid_for(G, kB), kB, 0, st>>>(t->g_count.as<int32_t>(), G, pairs.as<int64_t>(),
+                                                t->m2p_off.as<int64_t>(),
+                                                totals.as<unsigned long long>());
+  HOT_CHECK_LAUNCH();
   scan_i64(ctx, t->p2p_off.as<int64_t>(), t->p2p_off.as<int64_t>(), G, t->p2p_off.as<int64_t>() + G);
   scan_i64(ctx, t->m2p_off.as<int64_t>(), t->m2p_off.as<int64_t>(), G, t->m2p_off.as<int64_t>() + G);
   if (BG)
@@ -937,14 +954,13 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
              t->box_off.as<int64_t>() + G);
   int64_t h[5] = {0, 0, 0, 0, 0};
   unsigned fw[2] = {0u, 0u};
-  HOT_HIP(hipMemcpyAsync(fw, ctx->d_flags, sizeof(fw), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&h[0], t->p2p_off.as<int64_t>() + G, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&h[1], t->m2p_off.as<int64_t>() + G, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipMemcpyAsync(&h[2], tot + 2, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  if (BG)
-    HOT_HIP(hipMemcpyAsync(&h[4], t->box_off.as<int64_t>() + G, sizeof(int64_t),
-                           hipMemcpyDeviceToHost, st));
-  HOT_HIP(hipStreamSynchronize(st));
+  Readback rb(ctx);
+  rb.add(ctx->d_flags, fw, sizeof(fw));
+  rb.add(t->p2p_off.as<int64_t>() + G, &h[0], sizeof(int64_t));
+  rb.add(t->m2p_off.as<int64_t>() + G, &h[1], sizeof(int64_t));
+  rb.add(tot, &h[2], 2 * sizeof(int64_t));
+  if (BG) rb.add(t->box_off.as<int64_t>() + G, &h[4], sizeof(int64_t));
+  rb.run();
   raise_deferred(ctx, fw[kFlagDeferred]);
   const unsigned flags = fw[kFlagLocal];
   if (flags & FLAG_INTERNAL) throw Error{HOT_E_DEVICE, "walk consistency check failed"};
@@ -996,7 +1012,6 @@ void walk_lists(hot_ctx* ctx, hot_tree* t, double theta, ErrMac em, int direct_m
   t->bg = BG;
   t->bg_width = width;
   build_pair_segs(ctx, t);
-  build_units(ctx, t);
   t->has_lists = true;
 }
 
@@ -1028,8 +1043,10 @@ void mass_max(hot_ctx* ctx, hot_tree* t, const double* mass, DBuf& mm) {
   mm.alloc(ctx, sizeof(unsigned long long));
   k_zero_u64<<<1, 1, 0, ctx->stream>>>(mm.as<unsigned long long>());
   HOT_CHECK_LAUNCH();
-  k_mass_max<<<grid_for(t->n, kB), kB, 0, ctx->stream>>>(mass, t->n, mm.as<unsigned long long>(),
-                                                         ctx->d_flags + kFlagLocal);
+  // one atomic per wavefront, all on one word: few wavefronts
+  const unsigned grid = std::min(grid_for(t->n, kB), 512u);
+  k_mass_max<<<grid, kB, 0, ctx->stream>>>(mass, t->n, mm.as<unsigned long long>(),
+                                           ctx->d_flags + kFlagLocal);
   HOT_CHECK_LAUNCH();
 }
 }  // namespace
@@ -1048,12 +1065,7 @@ void build_lists_err(hot_ctx* ctx, hot_tree* t, const double* mass, double tol, 
                      int direct_max) {
   zero_flag_word(ctx, kFlagLocal);
   DBuf mm;
-  mm.alloc(ctx, sizeof(unsigned long long));
-  k_zero_u64<<<1, 1, 0, ctx->stream>>>(mm.as<unsigned long long>());
-  HOT_CHECK_LAUNCH();
-  k_mass_max<<<grid_for(t->n, kB), kB, 0, ctx->stream>>>(mass, t->n, mm.as<unsigned long long>(),
-                                                         ctx->d_flags + kFlagLocal);
-  HOT_CHECK_LAUNCH();
+  mass_max(ctx, t, mass, mm);
   ErrMac em{tol, mm.as<double>(), p_max, nullptr};
   walk_lists<true, false>(ctx, t, 0.0, em, direct_max);
 }
