@@ -54,13 +54,48 @@ __global__ __launch_bounds__(kScanThreads) void k_block_scan(const T* in, T* out
     sh[tid] += t;
     __syncthreads();
   }
-  T run = sh[tid] - s + (offsets ? offsets[blockIdx.x] : T(0));
+  T run = sh[tid] - s + offsets[blockIdx.x];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (base + k < n) out[base + k] = run;
     run += v[k];
   }
   if (total && blockIdx.x == gridDim.x - 1 && tid == kScanThreads - 1) *total = run;
+}
+
+// Up to kOneScan elements by one block: a thread's run of consecutive
+// elements, wavefront scans of the runs' sums, one scan of the wavefronts'.
+constexpr int kOneThreads = 1024, kOneItems = 16, kOneScan = kOneThreads * kOneItems;
+template <typename T>
+__global__ __launch_bounds__(kOneThreads) void k_one_scan(const T* in, T* out, int n,
+                                                          T* __restrict__ total) {
+  __shared__ T ws[kOneThreads / 64];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int per = (n + kOneThreads - 1) / kOneThreads;  // at most kOneItems
+  const int b = tid * per;
+  T v[kOneItems];
+  T s = 0;
+#pragma unroll
+  for (int k = 0; k < kOneItems; ++k) {
+    v[k] = k < per && b + k < n ? in[b + k] : T(0);
+    s += v[k];
+  }
+  T x = s;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const T y = __shfl_up(x, d);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) ws[w] = x;
+  __syncthreads();  // every element has been read: out may be in
+  T run = x - s;
+  for (int q = 0; q < w; ++q) run += ws[q];
+#pragma unroll
+  for (int k = 0; k < kOneItems; ++k) {
+    if (k < per && b + k < n) out[b + k] = run;
+    run += v[k];
+  }
+  if (total && tid == kOneThreads - 1) *total = run;
 }
 
 template <typename T>
@@ -78,12 +113,13 @@ void scan_impl(hot_ctx* ctx, const T* in, T* out, int64_t n, T* total) {
     }
     return;
   }
-  const int64_t nb = (n + kScanTile - 1) / kScanTile;
-  if (nb == 1) {
-    k_block_scan<T><<<1, kScanThreads, 0, ctx->stream>>>(in, out, n, nullptr, total);
+  // one launch instead of three where one block does it in a few microseconds
+  if (n <= kOneScan) {
+    k_one_scan<T><<<1, kOneThreads, 0, ctx->stream>>>(in, out, (int)n, total);
     HOT_CHECK_LAUNCH();
     return;
   }
+  const int64_t nb = (n + kScanTile - 1) / kScanTile;
   DBuf sums;
   sums.alloc(ctx, nb * sizeof(T));
   k_block_reduce<T><<<(unsigned)nb, kScanThreads, 0, ctx->stream>>>(in, n, sums.as<T>());
@@ -220,6 +256,106 @@ __global__ __launch_bounds__(kRThreads) void k_radix_scatter(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Up to 1024 R pairs in one block: the same stable passes with the pairs in
+// registers between them and one LDS array to reorder through, keys first, then
+// values (launch-bound otherwise: 21 launches and about 150 us for 4096 keys).
+// Wavefront w holds positions [64 R w, 64 R (w + 1)), 64 a round. Pads sort
+// last: all ones, behind every pair they tie with.
+// ---------------------------------------------------------------------------
+constexpr int kSThreads = 1024, kSWaves = kSThreads / 64, kSMaxRounds = 16;
+
+template <int R>
+__global__ __launch_bounds__(kSThreads) void k_block_sort(uint64_t* __restrict__ keys,
+                                                          uint32_t* __restrict__ vals, int n,
+                                                          int lo, int bits) {
+  __shared__ uint64_t sk[kSThreads * R];
+  __shared__ uint16_t cnt[kSWaves][kRBins];
+  __shared__ uint32_t loc[kRBins];
+  __shared__ uint32_t wsum[kRBins / 64];
+  uint32_t* sv = reinterpret_cast<uint32_t*>(sk);
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int base = w * 64 * R + lane;
+  const uint64_t lt = lanemask_lt();
+  uint64_t kk[R];
+  uint32_t vv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = base + 64 * r;
+    kk[r] = i < n ? keys[i] : ~0ull;
+    vv[r] = i < n ? vals[i] : 0u;
+  }
+  for (int shift = lo; shift < bits; shift += kRBits) {
+    for (int i = tid; i < kSWaves * kRBins; i += kSThreads) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t rk[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const unsigned d = (unsigned)(kk[r] >> shift) & (kRBins - 1);
+      uint64_t m = ~0ull;
+#pragma unroll
+      for (int b = 0; b < kRBits; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bb = __ballot(bit);
+        m &= bit ? bb : ~bb;
+      }
+      const uint32_t before = cnt[w][d];
+      __builtin_amdgcn_wave_barrier();
+      rk[r] = before + (uint32_t)__popcll(m & lt);
+      if ((m & lt) == 0) cnt[w][d] = (uint16_t)(before + (uint32_t)__popcll(m));
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // exclusive prefixes over the wavefronts per digit, then over the digits
+    uint32_t tot = 0, x = 0;
+    if (tid < kRBins) {
+      for (int q = 0; q < kSWaves; ++q) {
+        const uint32_t c = cnt[q][tid];
+        cnt[q][tid] = (uint16_t)tot;
+        tot += c;
+      }
+      x = tot;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+      }
+      if (lane == 63) wsum[w] = x;
+    }
+    __syncthreads();
+    if (tid < kRBins) {
+      uint32_t o = x - tot;
+      for (int q = 0; q < w; ++q) o += wsum[q];
+      loc[tid] = o;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const unsigned d = (unsigned)(kk[r] >> shift) & (kRBins - 1);
+      rk[r] += loc[d] + cnt[w][d];
+      sk[rk[r]] = kk[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) kk[r] = sk[base + 64 * r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) sv[rk[r]] = vv[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) vv[r] = sv[base + 64 * r];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = base + 64 * r;
+    if (i < n) {
+      keys[i] = kk[r];
+      vals[i] = vv[r];
+    }
+  }
+}
+
 }  // namespace
 
 void scan_u32(hot_ctx* ctx, const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total) {
@@ -231,6 +367,16 @@ void scan_i64(hot_ctx* ctx, const int64_t* in, int64_t* out, int64_t n, int64_t*
 
 void radix_sort(hot_ctx* ctx, DBuf& keys, DBuf& vals, int64_t n, int bits, int lo) {
   if (n <= 1 || bits <= lo) return;
+  if (n <= (int64_t)kSThreads * kSMaxRounds) {
+    uint64_t* k = keys.as<uint64_t>();
+    uint32_t* v = vals.as<uint32_t>();
+    auto kern = n <= kSThreads * 4 ? k_block_sort<4>
+                : n <= kSThreads * 8 ? k_block_sort<8>
+                                     : k_block_sort<kSMaxRounds>;
+    kern<<<1, kSThreads, 0, ctx->stream>>>(k, v, (int)n, lo, bits);
+    HOT_CHECK_LAUNCH();
+    return;
+  }
   const int passes = (bits - lo + kRBits - 1) / kRBits;
   const int64_t ntiles = (n + kRTile - 1) / kRTile;
   if ((int64_t)kRBins * ntiles >= (int64_t)UINT32_MAX) throw Error{HOT_E_CAPACITY, "sort too large"};

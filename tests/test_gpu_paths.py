@@ -1,0 +1,104 @@
+"""The variants of the kernels at the sizes where they change: the one-block and
+the tiled key sort, items below and above the cell-per-lane limit, lists of one
+unit and of many, Newtonian multipoles and the full softened expansion, the
+level-wise walk and its depth-first fallback. Oracle: the CPU treecode."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1310_4502_amd import workloads as W
+from paper_1310_4502_amd.binding import HOT_FP64, HOT_MIXED, Tree
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 4096, 4097, 8191, 8193, 16384, 16385])
+def test_keys_around_the_one_block_sort(orc, n):
+    """Whole numbers: equal to the oracle's, ties in caller order (a tenth of
+    the points repeat others)."""
+    pos = W.uniform(n, 11)
+    pos[: n // 10] = pos[n - n // 10:]
+    k, p = Tree(torch.from_numpy(pos).cuda(), 16, 64, (0.0, 0.0, 0.0, 1.0)).keys()
+    ok, op = orc.Tree(pos, 16, 64, (0.0, 0.0, 0.0, 1.0)).keys()
+    assert np.array_equal(k, ok) and np.array_equal(p, op)
+
+
+# n_group: groups of a few particles, of about 32 (both sides of the limit) and
+# more than one item each
+@pytest.mark.parametrize("n_group", [3, 40, 200])
+@pytest.mark.parametrize("p", [0, 1, 2, 5, 8])
+@pytest.mark.parametrize("eps,kernel", [(0.0, "plummer"), (2e-4, "plummer"), (0.05, "plummer"),
+                                        (0.05, "k1")])
+def test_expansions_by_class_and_item_size(orc, n_group, p, eps, kernel):
+    """eps = 0: Newtonian multipoles only; 2e-4: they and the full expansion mixed;
+    0.05: softened at the distance of the nearest cells (K1: sinks on both sides
+    of the radius). FP64 to 1e-12 and mixed to 1e-5 of the oracle on the same
+    lists (1e-6 holds for a field; the gradient of few close pairs is worse
+    conditioned)."""
+    n = 1500
+    pos = W.clustered(n, 5, n_halos=8)
+    mass = np.random.default_rng(1).uniform(0.5, 1.5, n) / n
+    bar = W.cotangent(n, 9)
+    box = (0.0, 0.0, 0.0, 1.0) if pos.min() >= 0 and pos.max() <= 1 else None
+    ot = orc.Tree(pos, min(8, n_group), n_group, box)
+    ot.build_lists(0.6, 0)
+    ot.compute_moments(pos, mass, p)
+    oa, oph, _ = ot.eval(pos, mass, eps, kernel=kernel)
+    ox, om = ot.vjp(pos, mass, eps, bar, kernel=kernel)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, min(8, n_group), n_group, box)
+    t.build_interaction_lists(0.6, 0)
+    t.compute_moments(x, m, p)
+    for prec, tol in ((HOT_FP64, 1e-12), (HOT_MIXED, 1e-5)):
+        a, ph, _ = t.eval_forces(x, m, eps, prec, with_pot=True, kernel=kernel)
+        only, _, _ = t.eval_forces(x, m, eps, prec, kernel=kernel)
+        gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True, kernel=kernel)
+        assert rel(a.cpu().numpy(), oa) <= tol
+        assert torch.equal(a, only)
+        assert rel(ph.cpu().numpy(), oph) <= tol
+        assert rel(gx.cpu().numpy(), ox) <= tol * (10 if prec == HOT_MIXED else 1)
+        assert rel(gm.cpu().numpy(), om) <= tol * (10 if prec == HOT_MIXED else 1)
+
+
+@pytest.mark.parametrize("far", [0, 1, 6])
+def test_outlying_particles_divide_lists(orc, far):
+    """A compact set and a few particles far from it: their groups pair with
+    most of the set, so their lists take several units, the others one."""
+    rng = np.random.default_rng(3)
+    n = 6000
+    pos = 0.05 * rng.random((n, 3))
+    pos[:far] = 0.55 + 0.4 * rng.random((far, 3))
+    mass = np.full(n, 1.0 / n)
+    bar = W.cotangent(n, 2)
+    ot = orc.Tree(pos, 16, 96)
+    ot.build_lists(0.3, 64)
+    ot.compute_moments(pos, mass, 4)
+    oa, _, _ = ot.eval(pos, mass, 1e-4)
+    ox, _ = ot.vjp(pos, mass, 1e-4, bar)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, 16, 96)
+    t.build_interaction_lists(0.3, 64)
+    t.compute_moments(x, m, 4)
+    for prec, tol in ((HOT_FP64, 1e-12), (HOT_MIXED, 1e-5)):
+        a, _, _ = t.eval_forces(x, m, 1e-4, prec)
+        gx, _ = t.eval_forces_adjoint(x, m, 1e-4, b, prec)
+        assert rel(a.cpu().numpy(), oa) <= tol
+        assert rel(gx.cpu().numpy(), ox) <= tol * (10 if prec == HOT_MIXED else 1)
+
+
+@pytest.mark.parametrize("theta,n_leaf", [(0.7, 32), (0.25, 1), (0.12, 1)])
+def test_lists_beyond_the_walks_room(orc, theta, n_leaf):
+    """From lists that fit the level-wise walk's LDS to ones of several thousand
+    entries, which it takes in depth-first pieces: equal entry for entry."""
+    n = 5000
+    pos = W.uniform(n, 21)
+    t = Tree(torch.from_numpy(pos).cuda(), n_leaf, 64, (0.0, 0.0, 0.0, 1.0))
+    t.build_interaction_lists(theta, 4)
+    ot = orc.Tree(pos, n_leaf, 64, (0.0, 0.0, 0.0, 1.0))
+    ot.build_lists(theta, 4)
+    for a, b in zip(t.lists(), ot.lists()):
+        assert np.array_equal(a, b)
