@@ -194,18 +194,19 @@ inline NewtonRule newton_rule(const hot_tree* t, double eps, bool derivative) {
   return r;
 }
 // d: distance of the nearest sink from the cell's centre. K1 is Newtonian
-// beyond its radius. sub: cube-subtracted moments, whose error is held to a
-// 256th of the tolerance against a full cell's mass (the subtracted moments
-// of a near-uniform cell are that much smaller than its mass); b and the
-// trace are then bounded by the cell's cube.
+// beyond its radius. sub: cube-subtracted moments, held to the same tolerance
+// against a full cell's mass, b and the trace bounded by the cell's cube and
+// doubled for the cube's own (mixed error of subtracted lists against FP64
+// 4.91e-7 with this rule, 4.91e-7 with 256 times the strictness, 5.6e-7 by
+// Cartesian derivatives).
 template <int P, bool K1>
 __device__ __forceinline__ bool newton_ok(const NewtonRule& r, double d, int c, bool sub,
                                           double side_c) {
   if constexpr (K1) return d >= r.eps;
   if (P < 2 || r.eps == 0.0) return true;
   if (sub) {
-    // (kNewtonC * 1.5 * 256)^(1/4) s^(1/2), half diagonal 0.8661 s
-    return d >= 0.8661 * side_c + 5.623 * sqrt(side_c) * r.nq;
+    // (kNewtonC * 1.5)^(1/4) s^(1/2), half diagonal 0.8661 s
+    return d >= 0.8661 * side_c + 1.406 * sqrt(side_c) * r.nq;
   }
   return d >= r.bmax[c] + (double)r.reach[c] * r.nq;
 }
