@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
     const int64_t* __restrict__ pseg_off, const PairSeg* __restrict__ pseg, const int32_t* __restrict__ g_first,
     const int32_t* __restrict__ g_count, const V4<T>* __restrict__ off,
     const V4<T>* __restrict__ ab4, T eps2, T ie, const unsigned* __restrict__ mdiff,
-    T* __restrict__ state, T* __restrict__ part) {
+    const float* __restrict__ g_rad, T* __restrict__ state, T* __restrict__ part) {
   __shared__ V4<T> stage[kWPB][64];
   // K1: eps2 is the squared kernel radius, ie its inverse radius
   const T ie2 = ie * ie, ie3 = ie * ie2, ie5t = (ie3 * ie2) * (T(1) / T(3));
@@ -411,6 +411,7 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
     pB = qBx = qBy = qBz = T(0);                                                     \
     n_acc = 0;                                                                       \
   }
+  const T r_far = K1 ? far_radius(eps2, g_rad[g]) : T(0);
   const int64_t q0 = pseg_off[g], q1 = q0 + uniform_i32(unit.z);
   for (int64_t q = q0 + uniform_i32(unit.y); q < q1; ++q) {
     {
@@ -420,15 +421,16 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
       const int jend = uniform_i32(sgm.end);
       const bool self = uniform_i32(sgm.self) != 0;
       const T dx = (T)sgm.dx, dy = (T)sgm.dy, dz = (T)sgm.dz;
+      const bool far = K1 && beyond_kernel(dx, dy, dz, r_far, g_rad[sgm.group]);
       const T tAx = dx - mA.x, tAy = dy - mA.y, tAz = dz - mA.z;
       const T tBx = dx - mB.x, tBy = dy - mB.y, tBz = dz - mB.z;
       // sources in batches of 64 staged through the wavefront's LDS slot
       // (one coalesced load per lane, read back two sources a read)
-#define HOT_SINK_PAIR(SELF, UM, VALID, SINK_I, TX, TY, TZ, A3X, A3Y, A3Z, A, Bx, By, Bz) \
+#define HOT_SINK_PAIR(FAR, SELF, UM, VALID, SINK_I, TX, TY, TZ, A3X, A3Y, A3Z, A, Bx, By, Bz) \
   {                                                                                  \
     const T rx = s.x + TX, ry = s.y + TY, rz = s.z + TZ;                             \
-    if constexpr (!K1) {                                                             \
-      const T r2 = hot_fma(rx, rx, hot_fma(ry, ry, hot_fma(rz, rz, eps2)));          \
+    if constexpr (!K1 || FAR) {                                                      \
+      const T r2 = hot_fma(rx, rx, hot_fma(ry, ry, K1 ? rz * rz : hot_fma(rz, rz, eps2))); \
       T inv = (EPS0 && !(r2 > T(0))) ? T(0) : hot_rsq(r2);                           \
       if (!(VALID) || (SELF && jb + k == (SINK_I))) inv = T(0);                      \
       const T inv2 = inv * inv;                                                      \
@@ -467,20 +469,20 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
       Bz = hot_fma(q, rz, Bz);                                                       \
     }                                                                                \
   }
-#define HOT_SINK_BATCH(UM, SELF)                                                     \
+#define HOT_SINK_BATCH(FAR, UM, SELF)                                                \
   {                                                                                  \
     int k2 = 0;                                                                      \
     _Pragma("unroll 2") for (; k2 + 1 < nbt; k2 += 2) {                              \
       const int k = k2 + h;                                                          \
       const V4<T> s = slot[k];                                                       \
-      HOT_SINK_PAIR(SELF, UM, true, iA, tAx, tAy, tAz, a3Ax, a3Ay, a3Az, pA, qAx, qAy, qAz) \
-      HOT_SINK_PAIR(SELF, UM, true, iB, tBx, tBy, tBz, a3Bx, a3By, a3Bz, pB, qBx, qBy, qBz) \
+      HOT_SINK_PAIR(FAR, SELF, UM, true, iA, tAx, tAy, tAz, a3Ax, a3Ay, a3Az, pA, qAx, qAy, qAz) \
+      HOT_SINK_PAIR(FAR, SELF, UM, true, iB, tBx, tBy, tBz, a3Bx, a3By, a3Bz, pB, qBx, qBy, qBz) \
     }                                                                                \
     if (k2 < nbt) {                                                                  \
       const int k = k2 + h;                                                          \
       const V4<T> s = slot[k2];                                                      \
-      HOT_SINK_PAIR(SELF, UM, h == 0, iA, tAx, tAy, tAz, a3Ax, a3Ay, a3Az, pA, qAx, qAy, qAz) \
-      HOT_SINK_PAIR(SELF, UM, h == 0, iB, tBx, tBy, tBz, a3Bx, a3By, a3Bz, pB, qBx, qBy, qBz) \
+      HOT_SINK_PAIR(FAR, SELF, UM, h == 0, iA, tAx, tAy, tAz, a3Ax, a3Ay, a3Az, pA, qAx, qAy, qAz) \
+      HOT_SINK_PAIR(FAR, SELF, UM, h == 0, iB, tBx, tBy, tBz, a3Bx, a3By, a3Bz, pB, qBx, qBy, qBz) \
     }                                                                                \
   }
       for (int jb = j; jb < jend; jb += 64) {
@@ -491,17 +493,26 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
         __builtin_amdgcn_wave_barrier();
         slot[lane] = v;
         __builtin_amdgcn_wave_barrier();
-        if (uni) {
+        if (K1 && far) {
+          if constexpr (K1) {
+            if (uni) {
+              HOT_SINK_BATCH(true, true, false)
+              mseg = slot[0].w;
+            } else {
+              HOT_SINK_BATCH(true, false, false)
+            }
+          }
+        } else if (uni) {
           if (self)
-            HOT_SINK_BATCH(true, true)
+            HOT_SINK_BATCH(false, true, true)
           else
-            HOT_SINK_BATCH(true, false)
+            HOT_SINK_BATCH(false, true, false)
           mseg = slot[0].w;
         } else {
           if (self)
-            HOT_SINK_BATCH(false, true)
+            HOT_SINK_BATCH(false, false, true)
           else
-            HOT_SINK_BATCH(false, false)
+            HOT_SINK_BATCH(false, false, false)
         }
       }
 #undef HOT_SINK_BATCH
@@ -968,26 +979,6 @@ __attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p
     for (int a = NM + lane; a < out_nm; a += 64) o[a] = T(0);
 }
 
-// Largest distance of a group's sinks from its centre (rounded up).
-template <typename T>
-__global__ __launch_bounds__(kB) void k_group_radius(const int32_t* __restrict__ g_first,
-                                                     const int32_t* __restrict__ g_count,
-                                                     int64_t G, const V4<T>* __restrict__ off,
-                                                     float* __restrict__ rad) {
-  const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * kWPB + (threadIdx.x >> 6);
-  if (g >= G) return;
-  const int f = g_first[g], e = f + g_count[g];
-  T m = T(0);
-  for (int i = f + lane; i < e; i += 64) {
-    const V4<T> o = off[i];
-    const T r = hot_fma(o.x, o.x, hot_fma(o.y, o.y, o.z * o.z));
-    m = r > m ? r : m;
-  }
-  m = wave_max(m);
-  if (lane == 0) rad[g] = (float)sqrt((double)m) * 1.000001f;
-}
-
 // 1 for the items whose every record is served by Newtonian multipoles; one
 // wavefront per item (at most kCellItemGroups records), in list order.
 template <bool MIXQ, bool PER, bool K1>
@@ -1353,16 +1344,13 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
   if (NI > 0) {
     // the items by class, the counts left on the device: both classes launch a
     // block per item, those past their class's end return at once
-    DBuf rad, flag, pos_y, pos_n, yes, no;
-    rad.alloc(ctx, (size_t)t->n_groups * sizeof(float));
+    DBuf flag, pos_y, pos_n, yes, no;
     flag.alloc(ctx, (size_t)NI * sizeof(uint32_t));
     pos_y.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
     pos_n.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
     yes.alloc(ctx, (size_t)NI * sizeof(uint32_t));
     no.alloc(ctx, (size_t)NI * sizeof(uint32_t));
-    k_group_radius<T><<<grid_for(t->n_groups, kWPB), kB, 0, st>>>(
-        t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), t->n_groups, off, rad.as<float>());
-    HOT_CHECK_LAUNCH();
+    group_radius<T>(ctx, t, off);
     const NewtonRule rule = newton_rule<T>(t, eps, false);
     const uint32_t* qi = mixq ? t->qitems.as<uint32_t>() : nullptr;
     auto fk = mixq ? (t->periodic ? k_citem_flag<true, true, K1> : k_citem_flag<true, false, K1>)
@@ -1371,7 +1359,7 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
         NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
         t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
         t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
-        rad.as<float>(), rule, flag.as<uint32_t>());
+        t->g_rad.as<float>(), rule, flag.as<uint32_t>());
     HOT_CHECK_LAUNCH();
     uint32_t* py = pos_y.as<uint32_t>();
     uint32_t* pn = pos_n.as<uint32_t>();
@@ -1571,11 +1559,12 @@ void adjoint_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
   auto sink_k = k1 ? k_p2p_sink_adj<T, false, true>
                     : (e2 > T(0) ? k_p2p_sink_adj<T, false, false> : k_p2p_sink_adj<T, true, false>);
   tmark(ctx, HOT_T_ADJ_P2P_SINK, false);
+  if (k1) group_radius<T>(ctx, t, off.as<V4<T>>());
   sink_k<<<grid_for(t->n_punits, kWPB), kB, 0, st>>>(
       t->punits.as<int4>(), t->n_punits, t->items.as<int2>(), t->pseg_off.as<int64_t>(),
       t->pseg.as<PairSeg>(), t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
-      off.as<V4<T>>(), ab.as<V4<T>>(), e2, ie, ctx->d_flags + kFlagMass, sink.as<T>(),
-      t->unit_part.as<T>());
+      off.as<V4<T>>(), ab.as<V4<T>>(), e2, ie, ctx->d_flags + kFlagMass, t->g_rad.as<float>(),
+      sink.as<T>(), t->unit_part.as<T>());
   HOT_CHECK_LAUNCH();
   sum_units<T, 3, false>(ctx, t, t->pslots, t->n_pslots, sink.as<T>());
   tmark(ctx, HOT_T_ADJ_P2P_SINK, true);

@@ -308,6 +308,9 @@ struct hot_tree {
   // 8 sums per slot, of either kind (FP64 room)
   int64_t n_punits = 0, n_munits = 0, n_munits_small = 0, n_pslots = 0, n_mslots = 0;
   hot::DBuf punits, munits, pslots, mslots, unit_part;
+  // per group, the largest distance of its particles from its centre, filled by
+  // the calls that need it from their positions
+  hot::DBuf g_rad;
   // adjoint caches built from the lists on first use
   bool has_transpose = false;
   // P2P by source item: records sorted by (item, group); rec_off per item
@@ -479,7 +482,7 @@ constexpr int kCentreImage = 62;  // n = (0, 0, 0)
 // - sink group centre in FP64 (rounded to the kernel's type where used);
 // self = 1 when the sources are the sink group itself in the central image.
 struct PairSeg {
-  int32_t first, end, self, pad;
+  int32_t first, end, self, group;  // group: the source group
   double dx, dy, dz;
 };
 // Partial sums of a work unit that shares its item with others: 64 sinks x 8.

@@ -48,7 +48,7 @@ void k_p2p(
     const int64_t* __restrict__ pseg_off, const PairSeg* __restrict__ pseg,
     const int32_t* __restrict__ g_first, const int32_t* __restrict__ g_count,
     const V4<T>* __restrict__ off, T eps2, T ie, const unsigned* __restrict__ mdiff,
-    T* __restrict__ state, T* __restrict__ part) {
+    const float* __restrict__ g_rad, T* __restrict__ state, T* __restrict__ part) {
   __shared__ V4<T> stage[kWavesPerBlock][64];
   // K1: eps2 is the squared kernel radius, ie its inverse radius
   const T ie2 = ie * ie, ie3 = ie * ie2;
@@ -105,6 +105,7 @@ void k_p2p(
     aBx = aBy = aBz = aBp = T(0);                                                    \
     n_acc = 0;                                                                       \
   }
+  const T r_far = K1 ? far_radius(eps2, g_rad[g]) : T(0);
   const int64_t q0 = pseg_off[g], q1 = q0 + uniform_i32(unit.z);
   for (int64_t q = q0 + uniform_i32(unit.y); q < q1; ++q) {
     {
@@ -114,14 +115,15 @@ void k_p2p(
       const int jend = uniform_i32(sgm.end);
       const bool self = uniform_i32(sgm.self) != 0;
       const T dx = (T)sgm.dx, dy = (T)sgm.dy, dz = (T)sgm.dz;
+      const bool far = K1 && beyond_kernel(dx, dy, dz, r_far, g_rad[sgm.group]);
       const T tAx = dx - mA.x, tAy = dy - mA.y, tAz = dz - mA.z;
       const T tBx = dx - mB.x, tBy = dy - mB.y, tBz = dz - mB.z;
       // one pair of a sink (T*) with source s, into accumulators A*
-#define HOT_PAIR1(SELF, UM, VALID, SINK_I, TX, TY, TZ, AX, AY, AZ, AP)               \
+#define HOT_PAIR1(FAR, SELF, UM, VALID, SINK_I, TX, TY, TZ, AX, AY, AZ, AP)          \
   {                                                                                  \
     const T rx = s.x + TX, ry = s.y + TY, rz = s.z + TZ;                             \
-    if constexpr (!K1) {                                                             \
-      const T r2 = hot_fma(rx, rx, hot_fma(ry, ry, hot_fma(rz, rz, eps2)));          \
+    if constexpr (!K1 || FAR) {                                                      \
+      const T r2 = hot_fma(rx, rx, hot_fma(ry, ry, K1 ? rz * rz : hot_fma(rz, rz, eps2))); \
       T inv = (EPS0 && !(r2 > T(0))) ? T(0) : hot_rsq(r2);                           \
       if (!(VALID) || (SELF && jb + k == (SINK_I))) inv = T(0);                      \
       const T mi = UM ? inv : s.w * inv;                                             \
@@ -156,20 +158,20 @@ void k_p2p(
   }
       // sources k2 + h for k2 = 0, 2, 4, ...: full pairs of sources first, then
       // the odd last one (half 0 only)
-#define HOT_BATCH(UM, SELF)                                                          \
+#define HOT_BATCH(FAR, UM, SELF)                                                     \
   {                                                                                  \
     int k2 = 0;                                                                      \
     _Pragma("unroll 4") for (; k2 + 1 < nbt; k2 += 2) {                              \
       const int k = k2 + h;                                                          \
       const V4<T> s = slot[k];                                                       \
-      HOT_PAIR1(SELF, UM, true, iA, tAx, tAy, tAz, aAx, aAy, aAz, aAp)               \
-      HOT_PAIR1(SELF, UM, true, iB, tBx, tBy, tBz, aBx, aBy, aBz, aBp)               \
+      HOT_PAIR1(FAR, SELF, UM, true, iA, tAx, tAy, tAz, aAx, aAy, aAz, aAp)          \
+      HOT_PAIR1(FAR, SELF, UM, true, iB, tBx, tBy, tBz, aBx, aBy, aBz, aBp)          \
     }                                                                                \
     if (k2 < nbt) {                                                                  \
       const int k = k2 + h;                                                          \
       const V4<T> s = slot[k2];                                                      \
-      HOT_PAIR1(SELF, UM, h == 0, iA, tAx, tAy, tAz, aAx, aAy, aAz, aAp)             \
-      HOT_PAIR1(SELF, UM, h == 0, iB, tBx, tBy, tBz, aBx, aBy, aBz, aBp)             \
+      HOT_PAIR1(FAR, SELF, UM, h == 0, iA, tAx, tAy, tAz, aAx, aAy, aAz, aAp)        \
+      HOT_PAIR1(FAR, SELF, UM, h == 0, iB, tBx, tBy, tBz, aBx, aBy, aBz, aBp)        \
     }                                                                                \
   }
       for (int jb = j; jb < jend; jb += 64) {
@@ -180,17 +182,26 @@ void k_p2p(
         __builtin_amdgcn_wave_barrier();
         slot[lane] = v;
         __builtin_amdgcn_wave_barrier();
-        if (uni) {
+        if (K1 && far) {
+          if constexpr (K1) {
+            if (uni) {
+              HOT_BATCH(true, true, false)
+              mseg = slot[0].w;
+            } else {
+              HOT_BATCH(true, false, false)
+            }
+          }
+        } else if (uni) {
           if (self)
-            HOT_BATCH(true, true)
+            HOT_BATCH(false, true, true)
           else
-            HOT_BATCH(true, false)
+            HOT_BATCH(false, true, false)
           mseg = slot[0].w;
         } else {
           if (self)
-            HOT_BATCH(false, true)
+            HOT_BATCH(false, false, true)
           else
-            HOT_BATCH(false, false)
+            HOT_BATCH(false, false, false)
         }
       }
 #undef HOT_BATCH
@@ -310,12 +321,14 @@ void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1
     kern<<<grid, kB, 0, ctx->stream>>>(t->punits.as<int4>(), t->n_punits, t->items.as<int2>(),
                                        t->pseg_off.as<int64_t>(), t->pseg.as<PairSeg>(),
                                        t->g_first.as<int32_t>(), t->g_count.as<int32_t>(), off,
-                                       e2, ie, mdiff, state, t->unit_part.as<T>());
+                                       e2, ie, mdiff, t->g_rad.as<float>(), state,
+                                       t->unit_part.as<T>());
     HOT_CHECK_LAUNCH();
   };
-  if (k1)
+  if (k1) {
+    group_radius<T>(ctx, t, off);
     go(k_p2p<T, POT, false, true>);
-  else if (e2 > T(0))
+  } else if (e2 > T(0))
     go(k_p2p<T, POT, false, false>);
   else
     go(k_p2p<T, POT, true, false>);
@@ -346,6 +359,7 @@ void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h) {
   auto room = [](int64_t n) { return (size_t)std::max<int64_t>(1, n) * sizeof(int4); };
   t->punits.alloc(ctx, room(t->n_punits));
   t->munits.alloc(ctx, room(t->n_munits));
+  t->g_rad.alloc(ctx, (size_t)t->n_groups * sizeof(float));
   t->pslots.alloc(ctx, room(t->n_pslots));
   t->mslots.alloc(ctx, room(t->n_mslots));
   t->unit_part.alloc(ctx, (size_t)std::max<int64_t>(1, std::max(t->n_pslots, t->n_mslots)) *

@@ -690,7 +690,7 @@ __global__ __launch_bounds__(kB) void k_pair_segs(
         r.first = j;
         r.end = jend;
         r.self = (sg == g && im == kCentreImage) ? 1 : 0;
-        r.pad = 0;
+        r.group = sg;
         if (p2p_img) {
           r.dx = (c_centre[3 * sc] + shx) - cgx;
           r.dy = (c_centre[3 * sc + 1] + shy) - cgy;
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(kB) void k_pair_segs_flat(
         PairSeg* r = seg + idx;
         r->first = f;
         r->self = (sg == g && im == kCentreImage) ? 1 : 0;
-        r->pad = 0;
+        r->group = sg;
         if (p2p_img) {
           r->dx = (c_centre[3 * sc] + shx) - cgx;
           r->dy = (c_centre[3 * sc + 1] + shy) - cgy;

@@ -64,6 +64,32 @@ def test_expansions_by_class_and_item_size(orc, n_group, p, eps, kernel):
         assert rel(gm.cpu().numpy(), om) <= tol * (10 if prec == HOT_MIXED else 1)
 
 
+@pytest.mark.parametrize("equal", [True, False])
+@pytest.mark.parametrize("eps", [1e-3, 0.05, 0.3])
+def test_k1_segments_beyond_the_radius(orc, eps, equal):
+    """Source groups all beyond the kernel's radius but the nearest, both kinds,
+    hardly any; equal masses (left out of the pair loop) and distinct ones."""
+    n = 2000
+    pos = W.uniform(n, 17)
+    mass = np.full(n, 1.0 / n) if equal else np.random.default_rng(2).uniform(0.5, 1.5, n) / n
+    bar = W.cotangent(n, 4)
+    ot = orc.Tree(pos, 8, 40, (0.0, 0.0, 0.0, 1.0))
+    ot.build_lists(0.4, 0)
+    ot.compute_moments(pos, mass, 2)
+    oa, oph, _ = ot.eval(pos, mass, eps, kernel="k1")
+    ox, _ = ot.vjp(pos, mass, eps, bar, kernel="k1")
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, 8, 40, (0.0, 0.0, 0.0, 1.0))
+    t.build_interaction_lists(0.4, 0)
+    t.compute_moments(x, m, 2)
+    for prec, tol in ((HOT_FP64, 1e-12), (HOT_MIXED, 1e-5)):
+        a, ph, _ = t.eval_forces(x, m, eps, prec, with_pot=True, kernel="k1")
+        gx, _ = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True, kernel="k1")
+        assert rel(a.cpu().numpy(), oa) <= tol
+        assert rel(ph.cpu().numpy(), oph) <= tol
+        assert rel(gx.cpu().numpy(), ox) <= tol * (10 if prec == HOT_MIXED else 1)
+
+
 @pytest.mark.parametrize("far", [0, 1, 6])
 def test_outlying_particles_divide_lists(orc, far):
     """A compact set and a few particles far from it: their groups pair with
