@@ -64,36 +64,42 @@ def comb(n, k):
 # code is written:
 #  pair forward: r = x_j - x_i (3), r^2 + eps^2 (3 FMA), rsq, m s^-3/2 (3 mul),
 #    a += f r (3 FMA): the count of 20 per pair;
-#  expansion forward at order p: derivatives of G to order p + 1 by the Hermite
-#    recursion, 2 C(p+5, 4); the contraction with the moments, 3 components of
-#    n_m(p) FMAs, 6 n_m(p); powers and rsq, p + 4;
+#  expansion forward at order p: basis of the solid harmonics to degree p - 1
+#    on the unit vector, 3 p^2 FMAs with the gradient coefficients, six FMAs per
+#    degree with its radial factor, the field from them;
 #  pair adjoint, sink side: r, s, rsq as above (10), s^-3/2, s^-5/2, m s^-3/2
 #    (3 mul), r . abar (1 mul + 2 FMA = 5), the r r^T coefficient (2 mul), the
 #    running sums of m s^-3/2 (1) and of the r r^T term (3 FMA): 28;
 #  pair adjoint, source side: r, s, rsq (10), s^-1, s^-3/2 (2 mul), r . b (5),
 #    its coefficient (2 mul), the Hessian row (3 x 2 FMA = 12), the mass
 #    cotangent (1 FMA): 33;
-#  expansion adjoint, sink side: derivatives to order p + 2, 2 C(p+6, 4); the
-#    six Hessian entries contracted with the moments, 6 n_m(p) FMAs = 12 n_m(p);
-#    the Hessian times abar (9 mul-adds as 3 x (1 mul + 2 FMA) = 15); powers
-#    and rsq, p + 5;
-#  expansion adjoint, cell side: derivatives to order p + 1, 2 C(p+5, 4); the
-#    moment cotangent row, n_m(p) entries of 3 FMAs, 6 n_m(p); p + 4.
+#  expansion adjoint, sink side: the same with the 5 (2l - 3) second-derivative
+#    coefficients per degree, and the Hessian times abar;
+#  expansion adjoint, cell side: the basis and the (p + 1)^2 harmonic cotangents.
+# The expansion counts are those of the generated expressions by order, in the
+# Newtonian form that nearly every entry takes; the softened form of the close
+# entries (1569, 2120 operations at p = 8) is not counted, so the rates
+# reported are lower bounds where it is used.
 FLOPS_P2P = 20
 FLOPS_P2P_SINK_ADJ = 28
 FLOPS_P2P_SRC_ADJ = 33
 
 
+FLOPS_M2P = (16, 38, 67, 118, 188, 276, 382, 506, 648)
+FLOPS_M2P_SINK_ADJ = (32, 60, 204, 262, 350, 465, 606, 773, 966)
+FLOPS_M2P_CELL_ADJ = (18, 34, 62, 112, 181, 268, 373, 496, 637)
+
+
 def flops_m2p(p):
-    return 2 * comb(p + 5, 4) + 6 * nm(p) + (p + 4)
+    return FLOPS_M2P[p]
 
 
 def flops_m2p_sink_adj(p):
-    return 2 * comb(p + 6, 4) + 12 * nm(p) + 15 + (p + 5)
+    return FLOPS_M2P_SINK_ADJ[p]
 
 
 def flops_m2p_cell_adj(p):
-    return 2 * comb(p + 5, 4) + 6 * nm(p) + (p + 4)
+    return FLOPS_M2P_CELL_ADJ[p]
 
 
 def git_head():

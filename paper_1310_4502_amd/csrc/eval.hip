@@ -17,8 +17,9 @@
 // Mixed precision: every position enters as an FP32 offset from its own
 // group's FP64 centre; the FP64 difference of two centres is formed once per
 // (group, entry) and rounded to FP32. Expansions run on coordinates scaled by
-// the source cell side s (a power of two): R/s, eps/s and the weighted moments
-// M_alpha / s^|alpha| are all O(1), and the result is rescaled by s^-2.
+// the source cell side s (a power of two): R/s, eps/s and the harmonic
+// coefficients, of M_alpha / s^|alpha|, are all O(1), and the result is
+// rescaled by s^-2.
 #include "common.h"
 #include "eval_common.h"
 #include "expand.h"

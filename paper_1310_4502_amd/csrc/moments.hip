@@ -14,8 +14,6 @@
 
 namespace hot {
 
-static __constant__ AlphaTable kAlpha = make_alpha_table();
-
 namespace {
 
 constexpr int kB = 256;
