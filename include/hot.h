@@ -9,8 +9,8 @@
  * a hash table (Tree Construction and Traversal section), moments about
  * geometric cell centres (Background Subtraction and Multipole Error Bounds
  * sections), a multipole acceptance walk per sink cell with m x n blocking
- * (Improving instruction-level parallelism section) and the Cartesian
- * expansion with Delta = 0 (Multipole Error Bounds section). It also gives
+ * (Improving instruction-level parallelism section) and the
+ * cell-body expansion with Delta = 0 (Multipole Error Bounds section). It also gives
  * the reverse derivative (vector-Jacobian product) of that evaluation with the
  * tree topology held fixed.
  *

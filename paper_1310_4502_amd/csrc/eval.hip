@@ -2,7 +2,7 @@
 //
 // Pair kernel: the softened Newtonian pair force (eq. "eom" at a = 1, G = 1,
 // with the Plummer smoothing of the Force Smoothing section). Expansion
-// kernel: the cell-body Cartesian multipole expansion with Delta = 0 of the
+// kernel: the cell-body multipole expansion (solid harmonics), Delta = 0, of the
 // Multipole Error Bounds section, with the softened Green's function.
 //
 // m x n blocking (Improving instruction-level parallelism section): one

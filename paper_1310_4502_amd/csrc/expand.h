@@ -300,9 +300,9 @@ __attribute__((amdgpu_waves_per_eu(Op::sink_waves(P)))) void k_expand(
 // (its harmonic and trace parts in two sweeps where the registers do not hold
 // the coefficients of both). What is left in a queue at the end, when it holds
 // fewer entries than there are sinks, is evaluated a sink per lane. 4.1 M grid,
-// 16 sinks per item, order 8: 66.6 -> 22.2 ms against slices of a wavefront
-// that read the coefficients from LDS (bound by its bandwidth); now bound by
-// VALU issue at two waves per SIMD.
+// 16 sinks per item, order 8: 66.6 -> 22.2 ms against the Cartesian form on
+// slices of a wavefront that read the coefficients from LDS (bound by its
+// bandwidth); now bound by VALU issue at two waves per SIMD.
 template <typename T, int N>
 __device__ __forceinline__ void load_row(const T* __restrict__ src, T* dst) {
   constexpr int V = 16 / sizeof(T);  // rows are padded to 16-byte multiples
