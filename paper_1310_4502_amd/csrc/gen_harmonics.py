@@ -349,7 +349,9 @@ def emit_row(L, names, arr, off, deg, comps, tag):
 def gen_fwd_newton(P):
     """Newtonian multipoles on the unit vector x = R u (rho = 1): with
     v_l = u^(l+2) and g_l = grad H_l(x), G = sum v g, Q = sum (v/l) g,
-      a = G + x (-H_0 u^2 - 2 x.G - x.Q),  phi = (x.Q + H_0 u^2) / u."""
+      a = G + x (-H_0 u^2 - 2 x.G - x.Q),  phi = R.Q + H_0 u
+    (R.Q, not x.Q / u: the monopole's potential then carries one reciprocal square
+    root's rounding instead of two, and no s u where s overflows)."""
     L = ["  const T s_ = hot_fma(X, X, hot_fma(Y, Y, hot_fma(Z, Z, e2)));",
          "  const T u = hot_rsq(s_);",
          "  const T x = X * u, y = Y * u, z = Z * u;",
@@ -373,7 +375,7 @@ def gen_fwd_newton(P):
           "  const T xG = hot_fma(x, Gx, hot_fma(y, Gy, z * Gz));",
           "  const T W = hot_fma(T(-2.0), xG, -(q0 + xQ));",
           "  ax += hot_fma(x, W, Gx); ay += hot_fma(y, W, Gy); az += hot_fma(z, W, Gz);",
-          "  if constexpr (POT) ph = hot_fma(xQ + q0, s_ * u, ph);"]
+          "  if constexpr (POT) ph = hot_fma(X, Qx, hot_fma(Y, Qy, hot_fma(Z, Qz, hot_fma(C[0], u, ph))));"]
     return L
 
 

@@ -128,3 +128,19 @@ def test_lists_beyond_the_walks_room(orc, theta, n_leaf):
     ot.build_lists(theta, 4)
     for a, b in zip(t.lists(), ot.lists()):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n_group", [256])
+@pytest.mark.parametrize("p", [0, 2])
+def test_mixed_potential_of_low_orders(n_group, p):
+    """The potential of mixed precision carries the rounding of one reciprocal
+    square root per term: 2^-25 of the FP64 one in the mean, half a rounding."""
+    n = 40000
+    pos = W.uniform(n, 29)
+    x, m = torch.from_numpy(pos).cuda(), torch.full((n,), 1.0 / n, dtype=torch.float64).cuda()
+    t = Tree(x, min(16, n_group), n_group)
+    t.build_interaction_lists(0.6, 0)
+    t.compute_moments(x, m, p)
+    ref = t.eval_forces(x, m, 1e-5, HOT_FP64, with_pot=True)[1].cpu().numpy()
+    pot = t.eval_forces(x, m, 1e-5, HOT_MIXED, with_pot=True)[1].cpu().numpy()
+    assert rel(pot, ref) <= 2.0 ** -25, rel(pot, ref)
