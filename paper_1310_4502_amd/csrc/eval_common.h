@@ -136,9 +136,10 @@ __device__ __forceinline__ T dpp(T v) {
   for (int i = 0; i < a.n; ++i) a.w[i] = __builtin_amdgcn_update_dpp(0, a.w[i], CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(T, a);
 }
-// sum of a over its lanes' partner half in the lower 32 lanes, of b in the upper
+// a's upper 32 lanes and b's lower 32 change places; the same for the odd rows of
+// 16 lanes of a and the even ones of b
 template <typename T>
-__device__ __forceinline__ T fold32(T a, T b) {
+__device__ __forceinline__ void swap32(T& a, T& b) {
   Words<T> x = __builtin_bit_cast(Words<T>, a), y = __builtin_bit_cast(Words<T>, b);
 #pragma unroll
   for (int i = 0; i < x.n; ++i) {
@@ -146,11 +147,11 @@ __device__ __forceinline__ T fold32(T a, T b) {
     x.w[i] = r[0];
     y.w[i] = r[1];
   }
-  return __builtin_bit_cast(T, x) + __builtin_bit_cast(T, y);
+  a = __builtin_bit_cast(T, x);
+  b = __builtin_bit_cast(T, y);
 }
-// the same for neighbouring rows of 16 lanes: a in the even rows, b in the odd
 template <typename T>
-__device__ __forceinline__ T fold16(T a, T b) {
+__device__ __forceinline__ void swap16(T& a, T& b) {
   Words<T> x = __builtin_bit_cast(Words<T>, a), y = __builtin_bit_cast(Words<T>, b);
 #pragma unroll
   for (int i = 0; i < x.n; ++i) {
@@ -158,20 +159,125 @@ __device__ __forceinline__ T fold16(T a, T b) {
     x.w[i] = r[0];
     y.w[i] = r[1];
   }
-  return __builtin_bit_cast(T, x) + __builtin_bit_cast(T, y);
+  a = __builtin_bit_cast(T, x);
+  b = __builtin_bit_cast(T, y);
 }
-// Wavefront sums of four values at once, in 10 instructions instead of 24:
-// row r of 16 lanes ends with the sum of v[kFoldRow[r]], on all its lanes.
+// sum of a over its lanes' partner half in the lower 32 lanes, of b in the upper;
+// for neighbouring rows of 16 lanes, a in the even rows, b in the odd
 template <typename T>
-__device__ __forceinline__ T fold4(const T* v) {
-  T t = fold16(fold32(v[0], v[1]), fold32(v[2], v[3]));
-  t += dpp<0xB1>(t);   // quad_perm(1,0,3,2)
-  t += dpp<0x4E>(t);   // quad_perm(2,3,0,1)
-  t += dpp<0x141>(t);  // row_half_mirror
-  t += dpp<0x140>(t);  // row_mirror
-  return t;
+__device__ __forceinline__ T fold32(T a, T b) {
+  swap32(a, b);
+  return a + b;
 }
-__device__ __forceinline__ int fold_row(int row) { return (row & 1) * 2 + (row >> 1); }  // 0 2 1 3
+template <typename T>
+__device__ __forceinline__ T fold16(T a, T b) {
+  swap16(a, b);
+  return a + b;
+}
+// Wavefront sums of a value per lane of four sinks (put, sum), found on the lanes
+// that here() names; sink(lane) is the one a lane keeps. The 64 terms enter a
+// compensated sum with one add, so their own sum carries no rounding of T: FP32
+// terms are summed in FP64, on the matrix cores as far as the layout reaches (the
+// forces of a 4.1 M grid of 16-sink items at order 8 take 51.5 ms, 49.0 with plain
+// FP32 sums, whose error at order 2 is a tenth to a fifth larger), FP64 terms with
+// the rounding of every add kept.
+template <typename T>
+struct Fold;
+// The four blocks of v_mfma_f64_4x4x4: lane 16 k + 4 b + i holds entry (i, k) of block
+// b as the left, (k, i) as the right operand and as the result. Each value times a
+// column of ones leaves its sums over k in that column, ones times those the block's
+// sums; the blocks, quads of a row of lanes, are then added.
+template <>
+struct Fold<float> {
+  double t = 0.0;
+  __device__ __forceinline__ void put(int u, float v) {
+    int q = (int)threadIdx.x & 3;
+    asm("" : "+v"(q));  // the columns are made where they are used: no registers for four
+    t = __builtin_amdgcn_mfma_f64_4x4x4f64((double)v, q == u ? 1.0 : 0.0, t, 0, 0, 0);
+  }
+  __device__ __forceinline__ double sum() const {
+    double x = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, 0.0, 0, 0, 0);
+    x += dpp<0x124>(x);  // row_ror:4
+    x += dpp<0x128>(x);  // row_ror:8
+    return x;
+  }
+  __device__ static int sink(int lane) { return lane; }
+  __device__ static bool here(int lane, int j) { return (lane >> 2) == j; }
+};
+struct Twice {
+  double s, e;  // the value s + e
+};
+__device__ __forceinline__ Twice two_sum(double a, double b) {
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+template <int CTRL>
+__device__ __forceinline__ void dpp_add(Twice& t) {
+  const double oe = dpp<CTRL>(t.e);
+  const Twice r = two_sum(t.s, dpp<CTRL>(t.s));
+  t.s = r.s;
+  t.e = r.e + (t.e + oe);
+}
+template <>
+struct Fold<double> {
+  double v[4];
+  __device__ __forceinline__ void put(int u, double x) { v[u] = x; }
+  __device__ __forceinline__ Twice sum() const {
+    double x[2] = {v[0], v[2]}, y[2] = {v[1], v[3]};
+    swap32(x[0], y[0]);
+    swap32(x[1], y[1]);
+    Twice a = two_sum(x[0], y[0]), b = two_sum(x[1], y[1]);
+    swap16(a.s, b.s);
+    Twice t = two_sum(a.s, b.s);
+    t.e += fold16(a.e, b.e);
+    dpp_add<0xB1>(t);   // quad_perm(1,0,3,2)
+    dpp_add<0x4E>(t);   // quad_perm(2,3,0,1)
+    dpp_add<0x141>(t);  // row_half_mirror
+    dpp_add<0x140>(t);  // row_mirror
+    return t;
+  }
+  // rows 0, 2, 1, 3 of lanes hold the four sinks
+  __device__ static int sink(int lane) {
+    const int r = lane >> 4;
+    return 4 * (lane & 15) + (r & 1) * 2 + (r >> 1);
+  }
+  __device__ static bool here(int lane, int j) { return (lane & 15) == j; }
+};
+// A lane's compensated sum (s - c) that such sums are added to: FP32 in one FP64 value.
+template <typename T>
+struct FoldSum;
+template <>
+struct FoldSum<float> {
+  double v = 0.0;
+  __device__ void load(const float* st, int d) { v = (double)st[d] - (double)st[4 + d]; }
+  __device__ void add(bool b, double x) { v += b ? x : 0.0; }
+  __device__ void add(float s, float c) { v += (double)s - (double)c; }
+  __device__ void store(float* st, int d) const {
+    const float hi = (float)v;
+    st[d] = hi;
+    st[4 + d] = (float)((double)hi - v);
+  }
+};
+template <>
+struct FoldSum<double> {
+  double s = 0.0, c = 0.0;
+  __device__ void load(const double* st, int d) {
+    s = st[d];
+    c = st[4 + d];
+  }
+  __device__ void add(bool b, const Twice& x) {
+    kahan_add(s, c, b ? x.s : 0.0);
+    c -= b ? x.e : 0.0;
+  }
+  __device__ void add(double o, double oc) {
+    kahan_add(s, c, o);
+    c += oc;
+  }
+  __device__ void store(double* st, int d) const {
+    st[d] = s;
+    st[4 + d] = c;
+  }
+};
 
 // What the expansion kernels need to choose between a cell's Newtonian
 // multipoles and its full softened expansion (kNewtonC): the softening and

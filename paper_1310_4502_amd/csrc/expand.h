@@ -293,7 +293,8 @@ __attribute__((amdgpu_waves_per_eu(Op::sink_waves(P)))) void k_expand(
 // the item's sinks are swept uniformly, four at a time, so that every lane works
 // whatever the number of sinks (one sink per lane leaves most of a wavefront
 // idle there). A sink's 64 terms are summed across the lanes in a fixed tree
-// and enter its compensated sums with one add per batch.
+// without rounding of their own type (Fold) and enter its compensated sums with
+// one add per batch.
 //
 // The entries are queued by class, so that batches are full: those served by
 // their Newtonian multipoles, and those that need the full softened expansion
@@ -346,28 +347,21 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
   V4<T> b = me;
   if (Op::kBar) b = bar[mine];
   const double bs = sink_radius<T>(me);
-  // the compensated sums of sink 4 j + fold_row(row) on lane j of that row
-  const int si = 4 * (lane & 15) + fold_row(lane >> 4);
-  T sum[NC], com[NC];
-#pragma unroll
-  for (int d = 0; d < NC; ++d) sum[d] = com[d] = T(0);
+  // the sink whose compensated sums this lane keeps
+  const int si = Fold<T>::sink(lane);
+  FoldSum<T> sum[NC];
   const bool whole = uniform_i32(unit.w) < 0;
   T* st = whole ? state + (int64_t)(item.y + si) * 8
                 : part + (int64_t)unit.w * kUnitSums + si * 8;
   if (whole && si < ns) {
 #pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      sum[d] = st[d];
-      com[d] = st[4 + d];
-    }
+    for (int d = 0; d < NC; ++d) sum[d].load(st, d);
   }
   // One sweep over the item's sinks: F(X, Y, Z, b, a) adds a sink's terms of
-  // this lane's cell. got: each sink's sums on its lane.
-  auto sweep = [&](const V4<T>& r, bool on, T* got, auto F) {
-#pragma unroll
-    for (int d = 0; d < NC; ++d) got[d] = T(0);
+  // this lane's cell; each sink's sums go to its lane.
+  auto sweep = [&](const V4<T>& r, bool on, auto F) {
     for (int j = 0; 4 * j < ns; ++j) {
-      T v[NC][4];
+      Fold<T> four[NC];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int k = 4 * j + u;
@@ -382,13 +376,12 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
         F(hot_fma(read_lane(me.x, k), r.w, r.x), hot_fma(read_lane(me.y, k), r.w, r.y),
           hot_fma(read_lane(me.z, k), r.w, r.z), kb, a);
 #pragma unroll
-        for (int d = 0; d < NC; ++d) v[d][u] = a[d] * (on ? Op::scale(d, r.w) : T(0));
+        for (int d = 0; d < NC; ++d) four[d].put(u, a[d] * (on ? Op::scale(d, r.w) : T(0)));
         __builtin_amdgcn_sched_barrier(0);  // one sink's temporaries at a time
       }
 #pragma unroll
       for (int d = 0; d < NC; ++d) {
-        const T t = fold4(v[d]);
-        got[d] = (lane & 15) == j ? t : got[d];
+        sum[d].add(Fold<T>::here(lane, j), four[d].sum());
       }
     }
   };
@@ -400,38 +393,32 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
     const V4<T> r = q_rec[FULL][slot];
     const T e2 = q_e2[FULL][slot];
     const int64_t c = q_cell[FULL][slot];
-    T got[NC];
     if constexpr (!FULL || Op::one_sweep(P)) {
       T C[HS], D[FULL ? TR : 4];
       load_row<T, HS>(hc + c * HS, C);
       if constexpr (FULL) load_row<T, TS>(tc + c * TS, D);
-      sweep(r, on, got, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
+      sweep(r, on, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
         if constexpr (FULL)
           Op::template full<P>(X, Y, Z, e2, kb, C, D, a);
         else
           Op::template newton<P>(X, Y, Z, e2, kb, C, a);
       });
     } else {
-      T more[NC];
       {
         T C[HS];
         load_row<T, HS>(hc + c * HS, C);
-        sweep(r, on, got, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
+        sweep(r, on, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
           Op::template full_h<P>(X, Y, Z, e2, kb, C, a);
         });
       }
       {
         T D[TR];
         load_row<T, TS>(tc + c * TS, D);
-        sweep(r, on, more, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
+        sweep(r, on, [&](T X, T Y, T Z, const V4<T>& kb, T* a) {
           Op::template full_t<P>(X, Y, Z, e2, kb, D, a);
         });
       }
-#pragma unroll
-      for (int d = 0; d < NC; ++d) got[d] += more[d];
     }
-#pragma unroll
-    for (int d = 0; d < NC; ++d) kahan_add(sum[d], com[d], got[d]);
   };
   // n entries one after another, a sink per lane as in k_expand
   auto single = [&](auto full_c, int n) {
@@ -456,8 +443,7 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
 #pragma unroll
     for (int d = 0; d < NC; ++d) {
       const T o = __shfl(fs[d], si), oc = __shfl(fc[d], si);
-      kahan_add(sum[d], com[d], o);
-      com[d] += oc;
+      sum[d].add(o, oc);
     }
   };
   auto flush = [&](auto full_c, int n) {
@@ -516,10 +502,7 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
   }
   if (si < ns) {
 #pragma unroll
-    for (int d = 0; d < NC; ++d) {
-      st[d] = sum[d];
-      st[4 + d] = com[d];
-    }
+    for (int d = 0; d < NC; ++d) sum[d].store(st, d);
   }
 }
 

@@ -130,7 +130,7 @@ def test_lists_beyond_the_walks_room(orc, theta, n_leaf):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("n_group", [256])
+@pytest.mark.parametrize("n_group", [12, 40, 256])
 @pytest.mark.parametrize("p", [0, 2])
 def test_mixed_potential_of_low_orders(n_group, p):
     """The potential of mixed precision carries the rounding of one reciprocal
