@@ -987,7 +987,7 @@ __global__ __launch_bounds__(kB) void k_citem_flag(
     const int32_t* __restrict__ citem_cell, const uint32_t* __restrict__ crec_off,
     const uint32_t* __restrict__ citem_end, const uint64_t* __restrict__ mkey, double side,
     const uint32_t* __restrict__ mval, const int32_t* __restrict__ g_cell,
-    const double* __restrict__ c_centre, const float* __restrict__ rad, NewtonRule rule,
+    const double* __restrict__ c_centre, const float* __restrict__ rad, NewtonRule rule, int p,
     uint32_t* __restrict__ flag) {
   const int lane = threadIdx.x & 63;
   const int64_t k = (int64_t)blockIdx.x * kWPB + (threadIdx.x >> 6);
@@ -1011,7 +1011,8 @@ __global__ __launch_bounds__(kB) void k_citem_flag(
     const double dy = c_centre[3 * gc + 1] - (c_centre[3 * c + 1] + sy);
     const double dz = c_centre[3 * gc + 2] - (c_centre[3 * c + 2] + sz);
     const double d = sqrt(dx * dx + dy * dy + dz * dz) - (double)rad[g];
-    ok = ok && newton_ok<2, K1>(rule, d, c, false, 0.0);
+    // below order 2 there are no trace parts (nor reaches) under Plummer softening
+    ok = ok && ((!K1 && p < 2) || newton_ok<2, K1>(rule, d, c, false, 0.0));
   }
   const bool all = __ballot(!ok) == 0;
   if (lane == 0) flag[k] = all ? 1u : 0u;
@@ -1359,7 +1360,7 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
         NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
         t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
         t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
-        t->g_rad.as<float>(), rule, flag.as<uint32_t>());
+        t->g_rad.as<float>(), rule, P, flag.as<uint32_t>());
     HOT_CHECK_LAUNCH();
     uint32_t* py = pos_y.as<uint32_t>();
     uint32_t* pn = pos_n.as<uint32_t>();

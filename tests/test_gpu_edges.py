@@ -1,0 +1,86 @@
+"""Edges of the kernels' ranges: separations that overflow, masses that vanish,
+orders without trace parts, memory that holds anything before it is written.
+Oracle: the CPU treecode."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1310_4502_amd import binding
+from paper_1310_4502_amd import workloads as W
+from paper_1310_4502_amd.binding import HOT_FP64, HOT_MIXED, Tree
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def filled_context(byte):
+    """A context whose allocator hands out memory that holds `byte` throughout."""
+    ctx = binding.Context(0, torch.cuda.current_stream(), torch_alloc=False)
+    L = binding.load()
+    L.hot_ctx_destroy(ctx.h)
+    main = torch.cuda.current_stream().cuda_stream
+    blocks, side = {}, {}
+
+    def _a(user, nbytes, stream):
+        if stream and stream != main:
+            if stream not in side:
+                side[stream] = torch.cuda.ExternalStream(stream)
+            with torch.cuda.stream(side[stream]):
+                t = torch.full((int(nbytes),), byte, dtype=torch.uint8, device="cuda")
+        else:
+            t = torch.full((int(nbytes),), byte, dtype=torch.uint8, device="cuda")
+        blocks[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def _f(user, ptr, stream):
+        blocks.pop(ptr, None)
+
+    ctx._fns = binding.ALLOC_FN(_a), binding.FREE_FN(_f), blocks
+    ctx._alloc = binding._Allocator(ctx._fns[0], ctx._fns[1], None)
+    h = ctypes.c_void_p()
+    assert L.hot_ctx_create(0, ctypes.c_void_p(main), ctypes.byref(ctx._alloc),
+                            ctypes.byref(h)) == 0
+    ctx.h = h
+    return ctx
+
+
+@pytest.mark.parametrize("lists", ["theta", "err", "periodic", "background"])
+@pytest.mark.parametrize("p", [0, 1, 2, 5])
+def test_results_do_not_depend_on_what_fresh_memory_holds(p, lists):
+    """Bit for bit the same from memory of zeros and of NaNs: nothing is read that
+    was not written."""
+    n = 3000
+    pos = W.clustered(n, 8, n_halos=6)
+    pos = pos - np.floor(pos)
+    mass, bar = np.random.default_rng(3).uniform(0.5, 1.5, n) / n, W.cotangent(n, 4)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    got = []
+    for byte in (0, 255):
+        ctx = filled_context(byte)
+        t = Tree(x, 8, 48, (0.0, 0.0, 0.0, 1.0), ctx=ctx)
+        t.compute_moments(x, m, p)
+        if lists == "theta":
+            t.build_interaction_lists(0.6, 8)
+        elif lists == "err":
+            t.build_interaction_lists_err(m, 1e-2, p, 8)
+        elif lists == "periodic":
+            t.build_interaction_lists_periodic(0.6, 8)
+        else:
+            t.build_interaction_lists_periodic_bs(0.6, 8)
+        out = []
+        for prec in (HOT_MIXED, HOT_FP64):
+            for kernel in ("plummer", "k1"):
+                a, ph, _ = t.eval_forces(x, m, 1e-3, prec, with_pot=lists != "background",
+                                         kernel=kernel)
+                gx, gm = t.eval_forces_adjoint(x, m, 1e-3, b, prec, with_mass=True, kernel=kernel)
+                out += [v.clone() for v in (a, ph, gx, gm) if v is not None]
+        got.append(out)
+        t.close()
+        ctx.close()
+    for u, v in zip(*got):
+        assert torch.equal(u, v)
