@@ -493,16 +493,17 @@ constexpr int kSumRun = 256;
 
 __device__ __forceinline__ float hot_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double hot_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
-// s^(-1/2) for 0 < s < infinity: the hardware reciprocal square root in FP32; in
-// FP64 it gives some 23 bits, which one third-order step (of y (1 - e)^(-1/2),
-// e = 1 - s y^2) takes to the last: 7 operations where an IEEE square root and
-// divide take about 60 (FP64 pair kernel 4.2 -> 2.0 ms at 1.6e9 pairs), with a
-// smaller error (1.0 ulp at most, 0.28 on average, against 1.5 and 0.34 over 4e6
-// values).
+// s^(-1/2), zero at infinity (separations whose square overflows): the hardware
+// reciprocal square root in FP32; in FP64 it gives some 23 bits, which one
+// third-order step (of y (1 - e)^(-1/2), e = 1 - s y^2) takes to the last: 8
+// operations where an IEEE square root and divide take about 60 (FP64 pair
+// kernel 4.2 -> 2.0 ms at 1.6e9 pairs), with a smaller error (1.0 ulp at most,
+// 0.28 on average, against 1.5 and 0.34 over 4e6 values). The minimum takes the
+// 1 where s y^2 is infinity times zero.
 __device__ __forceinline__ float hot_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double hot_rsq(double x) {
   const double y = __builtin_amdgcn_rsq(x);
-  const double e = hot_fma(-(x * y), y, 1.0);
+  const double e = __builtin_fmin(hot_fma(-(x * y), y, 1.0), 1.0);
   return hot_fma(y * e, hot_fma(0.375, e, 0.5), y);
 }
 

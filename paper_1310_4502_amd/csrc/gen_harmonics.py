@@ -450,10 +450,13 @@ def emit_g(L, lmax_of, P):
                                 for l in range(lmax_of(k) + 1)) + ";")
     for k1 in (False, True):
         L.append("  if constexpr (K1) {" if k1 else "  if constexpr (!K1) {")
+        var = "rho" if k1 else "e2"
+        # finite, so that it leaves an f_n that has vanished at zero
+        L.append(f"  const T vf_ = {var} < T(1e38) ? {var} : T(1e38);")
+        var = "vf_"
         for k in range(1, kmax + 1):
             for l in range(lmax_of(k) + 1):
                 terms = general_terms(l, k) if k1 else plummer_terms(l, k)
-                var = "rho" if k1 else "e2"
                 by = {}
                 for (i, n), c in terms.items():
                     by.setdefault(i, []).append((n, c * fnorm(n) / norm(l)))

@@ -84,3 +84,43 @@ def test_results_do_not_depend_on_what_fresh_memory_holds(p, lists):
         ctx.close()
     for u, v in zip(*got):
         assert torch.equal(u, v)
+
+
+def zero(*v):
+    return all(bool((x == 0).all()) for x in v)
+
+
+@pytest.mark.parametrize("eps,kernel", [(0.0, "plummer"), (1e-3, "plummer"), (1e-3, "k1")])
+def test_separations_whose_square_overflows(eps, kernel):
+    """Pairs 1e160 (FP32: 1e30) apart exert no force: s^(-1/2) of infinity is zero,
+    not NaN. Pair lists only; the tree is built where its cube has a side."""
+    n = 600
+    pos = W.uniform(n, 3)
+    mass, bar = np.full(n, 1.0 / n), W.cotangent(n, 4)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, 4, 8, (0.0, 0.0, 0.0, 1.0))
+    t.build_interaction_lists(1e-3, 0)
+    assert t.counts()["n_m2p"] == 0
+    t.compute_moments(x, m, 0)
+    for prec, scale in ((HOT_FP64, 1e160), (HOT_MIXED, 1e30)):
+        far = (x * scale).contiguous()
+        a, ph, _ = t.eval_forces(far, m, eps, prec, with_pot=True, kernel=kernel)
+        gx, gm = t.eval_forces_adjoint(far, m, eps, b, prec, with_mass=True, kernel=kernel)
+        assert zero(a, ph, gx, gm)
+
+
+@pytest.mark.parametrize("n_group", [4, 200])
+@pytest.mark.parametrize("prec,eps", [(HOT_FP64, 1e170), (HOT_MIXED, 1e30)])
+def test_softening_whose_square_overflows(n_group, prec, eps):
+    """An infinite eps^2 leaves no force, potential or gradient."""
+    n = 900
+    pos = W.uniform(n, 5)
+    mass, bar = np.full(n, 1.0 / n), W.cotangent(n, 6)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, min(8, n_group), n_group, (0.0, 0.0, 0.0, 1.0))
+    t.build_interaction_lists(0.6, 0)
+    for p in (0, 2, 5, 8):
+        t.compute_moments(x, m, p)
+        a, ph, _ = t.eval_forces(x, m, eps, prec, with_pot=True)
+        gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True)
+        assert zero(a, ph, gx, gm)
