@@ -829,7 +829,7 @@ __global__ void k_src_unit_sum(const int2* __restrict__ items, int64_t n_items,
 // stride out_stride, zero-filled from nm(P) up to out_nm (the cell's full moment
 // count).
 // NEWTON: the items whose every record is served by Newtonian multipoles
-// (k_citem_flag). Their cotangents are those of the harmonic coefficients (1 + 3
+// (SourceRule). Their cotangents are those of the harmonic coefficients (1 + 3
 // P^2 of them, one multiply-add each per sink: about 380 issue slots at order 8
 // against 1210), turned into the raw moments' once per item.
 template <int P, typename T>
@@ -979,15 +979,33 @@ __attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p
     for (int a = NM + lane; a < out_nm; a += 64) o[a] = T(0);
 }
 
-// 1 for the items whose every record is served by Newtonian multipoles; one
-// wavefront per item (at most kCellItemGroups records), in list order.
+// Where a cell's Newtonian multipoles serve its cotangents. These go back to the
+// masses and positions of its particles, each by itself whatever its mass, so the
+// bound is that of a mass at b_max (kNewtonCS), not the mass-weighted one of the
+// forward's rule: a massless particle has a mass gradient. k: kNewtonCS eps^2 /
+// tolerance, negative where nothing is left out at any distance. K1 is Newtonian
+// beyond its radius.
+struct SourceRule {
+  double eps, k;
+  const double* bmax;  // per cell
+};
+template <bool K1>
+__device__ __forceinline__ bool source_newton(const SourceRule& r, double d, int c) {
+  if (K1) return d >= r.eps;
+  if (r.k < 0.0) return true;
+  const double b = r.bmax[c], h = d - b;
+  return h > 0.0 && (h * h) * (h * h) >= r.k * b * d;
+}
+
+// 1 for the items whose every record it serves; one wavefront per item (at most
+// kCellItemGroups records), in list order.
 template <bool MIXQ, bool PER, bool K1>
 __global__ __launch_bounds__(kB) void k_citem_flag(
     int64_t n, const uint32_t* __restrict__ qitems, const uint32_t* __restrict__ citem_rec,
     const int32_t* __restrict__ citem_cell, const uint32_t* __restrict__ crec_off,
     const uint32_t* __restrict__ citem_end, const uint64_t* __restrict__ mkey, double side,
     const uint32_t* __restrict__ mval, const int32_t* __restrict__ g_cell,
-    const double* __restrict__ c_centre, const float* __restrict__ rad, NewtonRule rule, int p,
+    const double* __restrict__ c_centre, const float* __restrict__ rad, SourceRule rule,
     uint32_t* __restrict__ flag) {
   const int lane = threadIdx.x & 63;
   const int64_t k = (int64_t)blockIdx.x * kWPB + (threadIdx.x >> 6);
@@ -1011,8 +1029,7 @@ __global__ __launch_bounds__(kB) void k_citem_flag(
     const double dy = c_centre[3 * gc + 1] - (c_centre[3 * c + 1] + sy);
     const double dz = c_centre[3 * gc + 2] - (c_centre[3 * c + 2] + sz);
     const double d = sqrt(dx * dx + dy * dy + dz * dz) - (double)rad[g];
-    // below order 2 there are no trace parts (nor reaches) under Plummer softening
-    ok = ok && ((!K1 && p < 2) || newton_ok<2, K1>(rule, d, c, false, 0.0));
+    ok = ok && source_newton<K1>(rule, d, c);
   }
   const bool all = __ballot(!ok) == 0;
   if (lane == 0) flag[k] = all ? 1u : 0u;
@@ -1352,7 +1369,9 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
     yes.alloc(ctx, (size_t)NI * sizeof(uint32_t));
     no.alloc(ctx, (size_t)NI * sizeof(uint32_t));
     group_radius<T>(ctx, t, off);
-    const NewtonRule rule = newton_rule<T>(t, eps, false);
+    // there are no trace parts below order 2 or without softening
+    const SourceRule rule{eps, P < 2 || eps == 0.0 ? -1.0 : kNewtonCS * eps * eps / newton_tol<T>(),
+                          t->c_bmax.as<double>()};
     const uint32_t* qi = mixq ? t->qitems.as<uint32_t>() : nullptr;
     auto fk = mixq ? (t->periodic ? k_citem_flag<true, true, K1> : k_citem_flag<true, false, K1>)
                    : (t->periodic ? k_citem_flag<false, true, K1> : k_citem_flag<false, false, K1>);
@@ -1360,7 +1379,7 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
         NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
         t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
         t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
-        t->g_rad.as<float>(), rule, P, flag.as<uint32_t>());
+        t->g_rad.as<float>(), rule, flag.as<uint32_t>());
     HOT_CHECK_LAUNCH();
     uint32_t* py = pos_y.as<uint32_t>();
     uint32_t* pn = pos_n.as<uint32_t>();

@@ -23,10 +23,13 @@ constexpr int kWave = 64;
 // one by at most kNewtonC eps^2 b^2 / (d - b)^4 of the monopole's field for a
 // mass at distance b from the centre and a sink at distance d, and a cell is a
 // positive sum of those. The expansion kernels take them where that is below
-// one FP32 (FP64) epsilon; kNewtonCH is the same constant for the field's
-// derivatives (against the monopole's).
+// 2^-21 in FP32, 2^-50 in FP64 (four epsilons); kNewtonCH is the same constant for
+// the field's derivatives by the sink's position (against the monopole's).
+// kNewtonCS: for the derivatives by the mass's own position, which lose a power of
+// b, at most kNewtonCS eps^2 b d / (d - b)^4; that covers the field, too.
 constexpr double kNewtonC = 2.6;
 constexpr double kNewtonCH = 9.0;
+constexpr double kNewtonCS = 5.0;
 
 __host__ __device__ constexpr int nm(int p) { return (p + 1) * (p + 2) * (p + 3) / 6; }
 // moment slot of (a, b, c): by order, then a descending, then b descending

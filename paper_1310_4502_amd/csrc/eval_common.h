@@ -281,7 +281,7 @@ struct FoldSum<double> {
 
 // What the expansion kernels need to choose between a cell's Newtonian
 // multipoles and its full softened expansion (kNewtonC): the softening and
-// nq = (eps^2 / tolerance)^(1/4), tolerance one epsilon of the arithmetic.
+// nq = (eps^2 / tolerance)^(1/4), the tolerance four epsilons of the arithmetic.
 // c_reach carries kNewtonC; the derivative kernels fold (kNewtonCH /
 // kNewtonC)^(1/4) into nq.
 struct NewtonRule {
@@ -290,8 +290,10 @@ struct NewtonRule {
   const float* reach;   // per cell
 };
 template <typename T>
+constexpr double newton_tol() { return sizeof(T) == 4 ? 0x1p-21 : 0x1p-50; }
+template <typename T>
 inline NewtonRule newton_rule(const hot_tree* t, double eps, bool derivative) {
-  const double tol = sizeof(T) == 4 ? 0x1p-21 : 0x1p-50;
+  const double tol = newton_tol<T>();
   NewtonRule r;
   r.eps = eps;
   r.nq = sqrt(eps) * pow((derivative ? kNewtonCH / kNewtonC : 1.0) / tol, 0.25);

@@ -10,6 +10,7 @@ import torch
 from paper_1310_4502_amd import binding
 from paper_1310_4502_amd import workloads as W
 from paper_1310_4502_amd.binding import HOT_FP64, HOT_MIXED, Tree
+from gpu_util import assert_sinks
 
 pytestmark = pytest.mark.gpu
 
@@ -124,3 +125,47 @@ def test_softening_whose_square_overflows(n_group, prec, eps):
         a, ph, _ = t.eval_forces(x, m, eps, prec, with_pot=True)
         gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True)
         assert zero(a, ph, gx, gm)
+
+
+@pytest.mark.parametrize("lists", ["theta", "periodic"])
+@pytest.mark.parametrize("eps", [3e-3, 2e-2])
+@pytest.mark.parametrize("p", [2, 5, 8])
+def test_gradients_of_massless_and_light_particles(orc, p, eps, lists):
+    """A part of space without mass, a third of the rest massless and a third with
+    a thousandth: every particle's gradients, each against its own value (the
+    denominator held at a tenth of the typical one); eps about a leaf's side and a
+    tenth of it. FP64 to 1e-11, mixed to 1e-3, the repository's bounds per
+    particle with a margin of ten taken off FP64's."""
+    n = 2500
+    rng = np.random.default_rng(7)
+    pos = W.clustered(n, 5, n_halos=8)
+    pos = pos - np.floor(pos)
+    mass = rng.uniform(0.5, 1.5, n) / n
+    third = rng.integers(0, 3, n)
+    mass[third == 0] = 0.0
+    mass[third == 1] *= 1e-3
+    mass[pos[:, 0] < 0.35] = 0.0
+    bar = W.cotangent(n, 9)
+    bar[mass == 0] = 0.0  # their position gradient is zero, their mass gradient is not
+    bar[mass < 1e-2 / n] = 0.0  # of light ones only the source part is left
+    box = (0.0, 0.0, 0.0, 1.0)
+    ot = orc.Tree(pos, 8, 24, box)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, 8, 24, box)
+    if lists == "theta":
+        ot.build_lists(0.6, 0)
+        t.build_interaction_lists(0.6, 0)
+    else:
+        ot.build_lists_periodic(0.6, 0)
+        t.build_interaction_lists_periodic(0.6, 0)
+    ot.compute_moments(pos, mass, p)
+    t.compute_moments(x, m, p)
+    ox, om = ot.vjp(pos, mass, eps, bar)
+    light = (mass > 0) & (mass < 1e-2 / n)
+    for prec, tol in ((HOT_FP64, 1e-11), (HOT_MIXED, 1e-3)):
+        gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True)
+        gx, gm = gx.cpu().numpy(), gm.cpu().numpy()
+        assert_sinks(gm, om, tol, "mass gradient")
+        # per unit mass, so that light particles count
+        assert_sinks(gx[light] / mass[light, None], ox[light] / mass[light, None], tol, "light")
+        assert not gx[(mass == 0)].any()

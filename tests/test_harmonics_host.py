@@ -145,3 +145,55 @@ def test_newtonian_rule_bounds_what_it_leaves_out(orc, shim, p):
             rel = np.linalg.norm(full[:3] - newt[:3]) * r * r
             worst = max(worst, rel / (eps * eps * b * b / (r - b) ** 4))
     assert worst <= c, worst
+
+
+def newton_constant(name):
+    import re
+    return float(re.search(name + r" = ([0-9.]+)", open(os.path.join(CSRC, "common.h")).read()).group(1))
+
+
+@pytest.mark.parametrize("p", range(2, 9))
+@pytest.mark.parametrize("ratio", [1.05, 1.3, 1.7, 2.0, 2.5, 4.0, 10.0, 60.0])
+def test_newtonian_rules_of_the_derivatives(orc, shim, p, ratio):
+    """What Newtonian multipoles leave out of a unit mass's field, as derivatives
+    by the sink's position (kNewtonCH eps^2 b^2 / (d - b)^4 of the monopole's
+    2 / d^3) and by the mass's own (kNewtonCS eps^2 b d / (d - b)^4, for every
+    softening; its mass gradient, the field itself, is within that too)."""
+    ch, cs = newton_constant("kNewtonCH"), newton_constant("kNewtonCS")
+    rng = np.random.default_rng(11)
+    idx = np.array(orc.multi_indices(p))
+    b, worst_h, worst_s, worst_m = 0.5, 0.0, 0.0, 0.0
+
+    def left_out(M, R, e2):
+        h, t = coef(shim, p, np.ascontiguousarray(M))
+        full, newt = np.zeros(4), np.zeros(4)
+        shim.shim_fwd(p, 1, P(h), P(t), P(R), e2, P(full))
+        shim.shim_fwd(p, 0, P(h), P(t), P(R), e2, P(newt))
+        return full[:3] - newt[:3]
+
+    for trial in range(24):
+        u, e = rng.normal(size=3), rng.normal(size=3)
+        if trial < 10:
+            e = u * (1 if trial % 2 else -1) + 0.1 * e  # along and against the offset
+        x, d = u / np.linalg.norm(u) * b, b * ratio
+        R = e / np.linalg.norm(e) * d
+        M = np.prod(x ** idx, axis=1)
+        for eps in (1e-3 * b, 0.1 * b, b):
+            e2 = eps * eps
+            unit = e2 / (d - b) ** 4
+            h, t = coef(shim, p, M, 1)
+            J = np.zeros((3, 3))
+            for k in range(3):
+                bar, full, newt = np.eye(3)[k], np.zeros(3), np.zeros(3)
+                shim.shim_sink(p, 1, P(h), P(t), P(R), e2, P(bar), P(full))
+                shim.shim_sink(p, 0, P(h), P(t), P(R), e2, P(bar), P(newt))
+                J[k] = full - newt
+            worst_h = max(worst_h, np.linalg.norm(J, 2) * d ** 3 / 2 / (unit * b * b))
+            S = np.zeros((3, 3))
+            for k in range(3):
+                low = idx.copy()
+                low[:, k] = np.maximum(low[:, k] - 1, 0)
+                S[k] = left_out(idx[:, k] * np.prod(x ** low, axis=1), R, e2)
+            worst_s = max(worst_s, np.linalg.norm(S, 2) * d ** 3 / 2 / (unit * b * d))
+            worst_m = max(worst_m, np.linalg.norm(left_out(M, R, e2)) * d * d / (unit * b * d))
+    assert worst_h <= ch and worst_s <= cs and worst_m <= cs, (worst_h, worst_s, worst_m)
