@@ -1597,10 +1597,17 @@ void adjoint_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
   {
     // second-derivative coefficients, for this call only
     constexpr bool f64 = sizeof(T) == 8;
-    DBuf hh, ht, hhs, hts;
-    harmonics_hess(ctx, t, f64, false, hh, ht);
+    DBuf hh, ht, hhs, hts, w32;
+    if (!cart_only<JacobianOp<T, false>>(t)) harmonics_hess(ctx, t, f64, false, hh, ht);
     if (t->bg) harmonics_hess(ctx, t, f64, true, hhs, hts);
-    const Coef<T> cf{hh.as<T>(), ht.as<T>(), hhs.as<T>(), hts.as<T>()};
+    Coef<T> cf{hh.as<T>(), ht.as<T>(), hhs.as<T>(), hts.as<T>(), nullptr};
+    if (cart_items<JacobianOp<T, false>>(t)) {
+      if constexpr (f64)
+        weighted_fp64(ctx, t);
+      else
+        weighted_fp32(ctx, t, w32);
+      cf.w = f64 ? t->mw64.as<T>() : w32.as<T>();
+    }
     if (k1)
       launch_expand_p<T, JacobianOp<T, true>>(ctx, t, o4, a4, cf, eps, S);
     else

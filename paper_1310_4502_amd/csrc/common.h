@@ -268,6 +268,10 @@ struct hot_tree {
   // (kNewtonC trace / mass)^(1/4) per cell, for the Newtonian-multipole rule
   hot::DBuf hc32, tc32, hc64, tc64, c_reach;
   bool harm64_valid = false;
+  // the weighted scaled moments in FP64 (w_alpha M_alpha / s^|alpha|, stride
+  // nm_pad), on first use
+  hot::DBuf mw64;
+  bool mw64_valid = false;
   // P2P / M2P pair counts of the current lists (host copies)
   int64_t p2p_pairs = 0, m2p_pairs = 0;
   // lists
@@ -304,12 +308,13 @@ struct hot_tree {
   hot::DBuf items;
   // work units of the pair kernels and of the expansion kernels over sinks
   // (built with the lists): a part of an item's list, (item, first, end, slot);
-  // slot < 0: the item's only unit. munits: those of items of at most 32 sinks
-  // first (n_munits_small), then the others. pslots, mslots: what the partial
+  // slot < 0: the item's only unit. munits: those of items of at most 16 sinks
+  // first (n_munits_tiny), of at most 32 (n_munits_small with them), then the
+  // others. pslots, mslots: what the partial
   // sums of the divided items' units are added up from, (item, slot, units)
   // for an item's first slot, units = 0 for the others; unit_part: 64 sinks x
   // 8 sums per slot, of either kind (FP64 room)
-  int64_t n_punits = 0, n_munits = 0, n_munits_small = 0, n_pslots = 0, n_mslots = 0;
+  int64_t n_punits = 0, n_munits = 0, n_munits_tiny = 0, n_munits_small = 0, n_pslots = 0, n_mslots = 0;
   hot::DBuf punits, munits, pslots, mslots, unit_part;
   // per group, the largest distance of its particles from its centre, filled by
   // the calls that need it from their positions
@@ -360,7 +365,7 @@ void scan_i64(hot_ctx* ctx, const int64_t* in, int64_t* out, int64_t n, int64_t*
 void radix_sort(hot_ctx* ctx, DBuf& keys, DBuf& vals, int64_t n, int bits, int lo = 0);
 
 void build_tree(hot_ctx* ctx, hot_tree* t, const double* pos, const double* box);
-// the work units of the current lists: counts (sc: 3 n_items + 1 words) after
+// the work units of the current lists: counts (sc: 4 n_items + 1 words) after
 // the pair segments' offsets, then the units from the counts read back (h)
 void count_units(hot_ctx* ctx, hot_tree* t, DBuf& sc, Readback& rb, int64_t* h);
 void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h);
@@ -371,6 +376,10 @@ void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* m
 // matter minus each cell's uniform cube of the mean density (hsub, tsub); of
 // the negated cubes per unit density (the caller's arrays)
 void harmonics_fp64(hot_ctx* ctx, hot_tree* t);
+// the weighted scaled moments, FP64 kept with the tree (mw64), FP32 into the
+// caller's buffer
+void weighted_fp64(hot_ctx* ctx, hot_tree* t);
+void weighted_fp32(hot_ctx* ctx, hot_tree* t, DBuf& w);
 void harmonics_sub(hot_ctx* ctx, hot_tree* t, bool fp64);
 void harmonics_cube(hot_ctx* ctx, hot_tree* t, bool fp64, void* h, void* tr);
 // second-derivative form (sink-side adjoint) into the caller's buffers: of the

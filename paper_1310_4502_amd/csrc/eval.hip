@@ -248,8 +248,11 @@ __host__ __device__ inline int64_t unit_length(int64_t records, int64_t G, int64
 // sources); expansion units: four, of at least 16 entries
 constexpr int64_t kPairUnits = 8192, kPairUnitMin = 4, kExpUnits = 4096, kExpUnitMin = 16;
 
-// units and, in the high word, partial-sum slots of every item: its pair list,
-// its expansion list if it has at most 32 sinks, or more (three runs of NI)
+// expansion class of an item by its sinks: at most 16, at most 32, more
+__device__ inline int unit_class(int sinks) { return sinks <= 16 ? 0 : sinks <= 32 ? 1 : 2; }
+
+// units and, in the high word, partial-sum slots of every item: its pair list and
+// its expansion list in the run of its class (four runs of NI)
 __global__ void k_unit_count(const int2* __restrict__ items, int64_t NI, int64_t G,
                              const int32_t* __restrict__ g_first,
                              const int32_t* __restrict__ g_count,
@@ -265,10 +268,9 @@ __global__ void k_unit_count(const int2* __restrict__ items, int64_t NI, int64_t
     return u | (u > 1 ? u << 32 : 0);
   };
   const int64_t m = units(m2p_off[it.x + 1] - m2p_off[it.x], lm);
-  const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
+  const int cls = unit_class(g_first[it.x] + g_count[it.x] - it.y);
   sc[k] = units(pseg_off[it.x + 1] - pseg_off[it.x], lp);
-  sc[NI + k] = small ? m : 0;
-  sc[2 * NI + k] = small ? 0 : m;
+  for (int q = 0; q < 3; ++q) sc[(q + 1) * NI + k] = q == cls ? m : 0;
 }
 
 // the units and slots from the scanned counts
@@ -293,10 +295,10 @@ __global__ void k_unit_fill(const int2* __restrict__ items, int64_t NI, int64_t 
   };
   fill(pseg_off[it.x + 1] - pseg_off[it.x],
        unit_length(pseg_off[G], G, NI, kPairUnitMin, kPairUnits), sc[k], punits, pslots);
-  // small items first
-  const bool small = g_first[it.x] + g_count[it.x] - it.y <= 32;
+  // class by class
+  const int cls = unit_class(g_first[it.x] + g_count[it.x] - it.y);
   fill(m2p_off[it.x + 1] - m2p_off[it.x], unit_length(m2p_off[G], G, NI, kExpUnitMin, kExpUnits),
-       sc[(small ? NI : 2 * NI) + k] - sc[NI], munits, mslots);
+       sc[(cls + 1) * NI + k] - sc[NI], munits, mslots);
 }
 
 template <typename T>
@@ -340,23 +342,24 @@ void launch_p2p(hot_ctx* ctx, hot_tree* t, const V4<T>* off, double eps, bool k1
 
 void count_units(hot_ctx* ctx, hot_tree* t, DBuf& sc, Readback& rb, int64_t* h) {
   const int64_t NI = t->n_items;
-  sc.alloc(ctx, (3 * NI + 1) * sizeof(int64_t));
+  sc.alloc(ctx, (4 * NI + 1) * sizeof(int64_t));
   int64_t* c = sc.as<int64_t>();
   k_unit_count<<<grid_for(NI, kB), kB, 0, ctx->stream>>>(
       t->items.as<int2>(), NI, t->n_groups, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
       t->pseg_off.as<int64_t>(), t->m2p_off.as<int64_t>(), c);
   HOT_CHECK_LAUNCH();
-  scan_i64(ctx, c, c, 3 * NI, c + 3 * NI);
-  for (int k = 0; k < 3; ++k) rb.add(c + (k + 1) * NI, h + k, sizeof(int64_t));
+  scan_i64(ctx, c, c, 4 * NI, c + 4 * NI);
+  for (int k = 0; k < 4; ++k) rb.add(c + (k + 1) * NI, h + k, sizeof(int64_t));
 }
 
 void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h) {
   const int64_t NI = t->n_items, lo = 0xffffffffll;
   t->n_punits = h[0] & lo;
   t->n_pslots = h[0] >> 32;
-  t->n_munits_small = (h[1] - h[0]) & lo;
-  t->n_munits = (h[2] - h[0]) & lo;
-  t->n_mslots = (h[2] - h[0]) >> 32;
+  t->n_munits_tiny = (h[1] - h[0]) & lo;
+  t->n_munits_small = (h[2] - h[0]) & lo;
+  t->n_munits = (h[3] - h[0]) & lo;
+  t->n_mslots = (h[3] - h[0]) >> 32;
   auto room = [](int64_t n) { return (size_t)std::max<int64_t>(1, n) * sizeof(int4); };
   t->punits.alloc(ctx, room(t->n_punits));
   t->munits.alloc(ctx, room(t->n_munits));
@@ -410,10 +413,14 @@ void forces_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, 
   HOT_CHECK_LAUNCH();
   Coef<T> cf{};
   if constexpr (sizeof(T) == 4) {
-    cf = {t->hc32.as<T>(), t->tc32.as<T>(), nullptr, nullptr};
+    cf = {t->hc32.as<T>(), t->tc32.as<T>(), nullptr, nullptr, nullptr};
   } else {
-    harmonics_fp64(ctx, t);
-    cf = {t->hc64.as<T>(), t->tc64.as<T>(), nullptr, nullptr};
+    if (!cart_only<FieldOp<T, false, false>>(t)) harmonics_fp64(ctx, t);
+    cf = {t->hc64.as<T>(), t->tc64.as<T>(), nullptr, nullptr, nullptr};
+    if (cart_items<FieldOp<T, false, false>>(t)) {
+      weighted_fp64(ctx, t);
+      cf.w = t->mw64.as<T>();
+    }
   }
   if (t->bg) {
     harmonics_sub(ctx, t, sizeof(T) == 8);
@@ -486,7 +493,7 @@ void cube_field_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* ma
   k_zero_t<T><<<grid_for(std::max(nh, nt), kB), kB, 0, st>>>(zero.as<T>(), std::max(nh, nt));
   HOT_CHECK_LAUNCH();
   harmonics_cube(ctx, t, sizeof(T) == 8, cube.p, tcube.p);
-  const Coef<T> cf{zero.as<T>(), zero.as<T>(), cube.as<T>(), tcube.as<T>()};
+  const Coef<T> cf{zero.as<T>(), zero.as<T>(), cube.as<T>(), tcube.as<T>(), nullptr};
   launch_m2p<T, false>(ctx, t, off.as<V4<T>>(), cf, eps, k1, state.as<T>());
   k_finalize<T><<<grid_for(n, kB), kB, 0, st>>>(state.as<T>(), t->perm.as<uint32_t>(), n, out,
                                                 nullptr);

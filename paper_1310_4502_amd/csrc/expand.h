@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "eval_common.h"
+#include "generated/expansions.h"
 #include "generated/harmonics.h"
 
 namespace hot {
@@ -37,9 +38,11 @@ struct FieldOp {
   }
   // waves per SIMD of k_expand: its scalar loads wait on memory, and 80
   // registers (six waves instead of four or five) cost no spills: 2^20
-  // background-subtracted lists, order 8, 44.8 -> 37.2 ms
-  static constexpr int sink_waves(int p) {
-    return sizeof(T) == 4 && p >= 7 ? 6 : 1;
+  // background-subtracted lists, order 8, 44.8 -> 37.2 ms. FP64, order 8: three
+  // instead of two for plain theta lists (150 k Plummer, groups of 256, 6.4 -> 4.7
+  // ms); the images of periodic ones then spill (7.4 -> 9.6 ms)
+  static constexpr int sink_waves(int p, bool plain) {
+    return sizeof(T) == 4 ? (p >= 7 ? 6 : 1) : p == 8 && plain ? 3 : 1;
   }
   __device__ static __forceinline__ T scale(int d, T inv) { return d == 3 ? inv : -(inv * inv); }
   template <int Q>
@@ -59,6 +62,11 @@ struct FieldOp {
   __device__ static __forceinline__ void full_t(T X, T Y, T Z, T e2, const V4<T>&, const T* D, T* a) {
     harm_fwd_full_t<Q, T, POT_, K1>(X, Y, Z, e2, D, a[0], a[1], a[2], a[3]);
   }
+  // Cartesian derivatives, M the weighted moments
+  template <int Q>
+  __device__ static __forceinline__ void cart(T X, T Y, T Z, T e2, const V4<T>&, const T* M, T* a) {
+    expansion_fwd<Q, T, POT_, K1>(X, Y, Z, e2, M, a[0], a[1], a[2], a[3]);
+  }
 };
 
 // sink part of the adjoint: b the sink's cotangent
@@ -75,9 +83,7 @@ struct JacobianOp {
   static constexpr int waves(int p) {
     return sizeof(T) == 8 ? (p <= 1 ? 4 : 2) : p <= 4 ? 3 : 2;
   }
-  static constexpr int sink_waves(int p) {
-    return sizeof(T) == 4 && p >= 7 ? 5 : 1;
-  }
+  static constexpr int sink_waves(int p, bool) { return sizeof(T) == 4 && p >= 7 ? 5 : 1; }
   __device__ static __forceinline__ T scale(int, T inv) { return -(inv * inv * inv); }
   template <int Q>
   __device__ static __forceinline__ void newton(T X, T Y, T Z, T e2, const V4<T>& b, const T* C,
@@ -99,14 +105,19 @@ struct JacobianOp {
                                                 T* a) {
     harm_sink_full_t<Q, T, K1>(X, Y, Z, e2, D, b.x, b.y, b.z, a[0], a[1], a[2]);
   }
+  template <int Q>
+  __device__ static __forceinline__ void cart(T X, T Y, T Z, T e2, const V4<T>& b, const T* M, T* a) {
+    expansion_sink_adj<Q, T, K1>(X, Y, Z, e2, M, b.x, b.y, b.z, a[0], a[1], a[2]);
+  }
 };
 
 // ------------------------------------------------------------------- arguments
 // A cell's coefficients: harmonic and trace parts, and (background
-// subtraction) those of the cube-subtracted moments.
+// subtraction) those of the cube-subtracted moments; w: the weighted moments
+// themselves, where cart_items asks for them.
 template <typename T>
 struct Coef {
-  const T *h, *t, *hsub, *tsub;
+  const T *h, *t, *hsub, *tsub, *w;
 };
 
 struct ListArgs {
@@ -167,18 +178,31 @@ __device__ __forceinline__ double sink_radius(const V4<T>& me) {
 // Cartesian form), 70 % of the issue slots used (2^21 grid, 64-sink items:
 // 13.8 -> 4.6 ms).
 //
+// FP64 rows of more than 400 bytes exceed the scalar registers and caches: the
+// wavefront stages them in LDS, an entry ahead (expand_staged; 48^3 grid, 64-sink
+// items, order 8: field 2.7 -> 1.8 ms, Jacobian 4.5 -> 1.9, background-subtracted
+// lists 11.8 -> 7.4 and 19.8 -> 10.3).
+//
 // MIXQ: every entry carries its own order q <= P, error-bound lists. PER: every
 // entry carries the image of its cell (periodic lists). BG: background
 // subtraction; a flagged entry takes its cell's coefficients minus those of its
 // uniform cube.
+typedef unsigned Chunk __attribute__((ext_vector_type(4)));
+template <typename T>
+constexpr bool expand_staged(int row) { return sizeof(T) == 8 && row * 8 > 400; }
+
 template <int P, typename T, class Op, bool MIXQ, bool PER, bool BG>
 __global__ __launch_bounds__(64 * kExpandWaves)
-__attribute__((amdgpu_waves_per_eu(Op::sink_waves(P)))) void k_expand(
+__attribute__((amdgpu_waves_per_eu(Op::sink_waves(P, !MIXQ && !PER)))) void k_expand(
     ListArgs A, Coef<T> cf, const V4<T>* __restrict__ off, const V4<T>* __restrict__ bar,
     T* __restrict__ state, T* __restrict__ part) {
-  constexpr int NC = Op::NC;
+  constexpr int NC = Op::NC, HS = Op::hs(P), TS = Op::ts(P);
+  constexpr bool kStage = expand_staged<T>(HS);
+  constexpr int kHc = HS * (int)sizeof(T) / 16, kChunks = (HS + TS) * (int)sizeof(T) / 16;
+  constexpr int kPre = kStage ? (kChunks + 63) / 64 : 1;
   __shared__ V4<T> s_rec[kExpandWaves][64];
   __shared__ T s_e2[kExpandWaves][64];
+  __shared__ Chunk s_row[kStage ? kExpandWaves : 1][kStage ? kChunks : 1];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t iu = (int64_t)blockIdx.x * kExpandWaves + w;
   if (iu >= A.n_units) return;
@@ -235,6 +259,24 @@ __attribute__((amdgpu_waves_per_eu(Op::sink_waves(P)))) void k_expand(
     __builtin_amdgcn_wave_barrier();
     V4<T> nr = s_rec[w][0];
     T ne2 = s_e2[w][0];
+    // the next entry's rows, 16 bytes a lane and step, on their way while the
+    // current one is evaluated
+    Chunk pre[kPre];
+    auto fetch = [&](int k) __attribute__((always_inline)) {
+      const int64_t c = __builtin_amdgcn_readlane(cl, k);
+      const int f = __builtin_amdgcn_readlane(fl, k);
+      const bool sub = BG && (f & 2);
+      const Chunk* hp = reinterpret_cast<const Chunk*>((sub ? hsub : hc) + c * HS);
+      const Chunk* tp = reinterpret_cast<const Chunk*>((sub ? tsub : tc) + c * TS);
+      const int n = f & 1 ? kHc : kChunks;
+#pragma unroll
+      for (int q = 0; q < kPre; ++q) {
+        const int ch = lane + 64 * q;
+        const Chunk* src = ch < kHc ? hp + ch : tp + (ch - kHc);
+        pre[q] = ch < n ? *src : Chunk(0);
+      }
+    };
+    if constexpr (kStage) fetch(0);
     for (int k = 0; k < nb; ++k) {
       const V4<T> r = nr;
       const T ke2 = ne2;
@@ -243,8 +285,21 @@ __attribute__((amdgpu_waves_per_eu(Op::sink_waves(P)))) void k_expand(
       const int64_t c = __builtin_amdgcn_readlane(cl, k);
       const int f = __builtin_amdgcn_readlane(fl, k);
       const bool sub = BG && (f & 2);
-      const T* C = (sub ? hsub : hc) + c * Op::hs(P);
-      const T* D = (sub ? tsub : tc) + c * Op::ts(P);
+      const T* C = (sub ? hsub : hc) + c * HS;
+      const T* D = (sub ? tsub : tc) + c * TS;
+      if constexpr (kStage) {
+        Chunk* row = s_row[w];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < kPre; ++q) {
+          const int ch = lane + 64 * q;
+          if (ch < kChunks) row[ch] = pre[q];
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (k + 1 < nb) fetch(k + 1);
+        C = reinterpret_cast<const T*>(row);
+        D = C + HS;
+      }
       const T X = hot_fma(me.x, r.w, r.x);
       const T Y = hot_fma(me.y, r.w, r.y);
       const T Z = hot_fma(me.z, r.w, r.z);
@@ -506,7 +561,135 @@ __attribute__((amdgpu_waves_per_eu(Op::waves(P)))) void k_expand_cl(ListArgs A, 
   }
 }
 
+// --------------------------------------------------- slices of a wavefront
+// Items of at most 16 sinks whose order's coefficients exceed the registers of
+// k_expand_cl (FP64 fields above order 4, Jacobians above 3; FP32 Jacobians above
+// 6): the wavefront splits into S = 64 / W slices of W = 8 or 16 lanes, slice s
+// taking entry e0 + round S + s. The round's S cells have their weighted moments
+// staged together in LDS. Bound by the LDS reads, of which the Cartesian form needs
+// the fewest (165 values at order 8, each used three times, against 365 harmonic and
+// trace coefficients in FP64, where nearly every entry takes the full expansion).
+// 48^3 grid, 12-sink items, against a sink per lane: FP64 field at order 6 10.1 ->
+// 2.0 ms, at order 8 26.9 -> 6.0, Jacobian at order 8 42.8 -> 7.1, FP32 Jacobian at
+// order 8 6.1 to 11.9 (few or many full expansions) -> 3.1. With 27 sinks, two
+// slices, the sink per lane is ahead (FP32 Jacobian 1.8 against 4.0, FP64 5.6 against
+// 6.8, field 5.3 against 6.4). Every cross-lane read is executed by all lanes.
+template <int P, typename T, class Op, bool PER>
+__global__ __launch_bounds__(64) void k_expand_sl(ListArgs A, const T* __restrict__ mw,
+                                                  const V4<T>* __restrict__ off,
+                                                  const V4<T>* __restrict__ bar,
+                                                  T* __restrict__ state, T* __restrict__ part) {
+  constexpr int NC = Op::NC, kStride = nm_pad(P), kChunks = kStride * (int)sizeof(T) / 16;
+  constexpr int kMaxS = 8, kRounds = (kMaxS * kChunks + 63) / 64;
+  __shared__ uint4 smom[kMaxS * kChunks];
+  const int lane = threadIdx.x;
+  const int64_t iu = blockIdx.x;
+  if (iu >= A.n_units) return;
+  const int4 unit = A.units[iu];
+  const int2 item = A.items[unit.x];
+  const int g = uniform_i32(item.x);
+  const int ns = uniform_i32(min(16, A.g_first[g] + A.g_count[g] - item.y));
+  const int lw = ns <= 8 ? 3 : 32 - __clz(ns - 1);
+  const int S = 64 >> lw;
+  const int p = lane & ((1 << lw) - 1), sl = lane >> lw;
+  const int i = item.y + p;
+  const bool active = p < ns;
+  const int gc = A.g_cell[g];
+  const double gx = A.c_centre[3 * gc], gy = A.c_centre[3 * gc + 1], gz = A.c_centre[3 * gc + 2];
+  V4<T> me, b;
+  me.x = me.y = me.z = me.w = T(0);
+  b = me;
+  T sum[NC], com[NC];
+#pragma unroll
+  for (int d = 0; d < NC; ++d) sum[d] = com[d] = T(0);
+  const bool whole = uniform_i32(unit.w) < 0;
+  T* st = whole ? state + (int64_t)i * 8 : part + (int64_t)unit.w * kUnitSums + p * 8;
+  if (active) {
+    me = off[i];
+    if (Op::kBar) b = bar[i];
+    if (whole && sl == 0) {
+#pragma unroll
+      for (int d = 0; d < NC; ++d) {
+        sum[d] = st[d];
+        com[d] = st[4 + d];
+      }
+    }
+  }
+  const int64_t e0 = A.off[g] + uniform_i32(unit.y), e1 = A.off[g] + uniform_i32(unit.z);
+  for (int64_t eb = e0; eb < e1; eb += S) {
+    // the round's cells (and images), one per lane
+    int cl = -1, il = kCentreImage;
+    if (lane < S && eb + lane < e1) {
+      cl = A.cell[eb + lane];
+      if (PER) il = A.img[eb + lane];
+    }
+    // chunk k of slice s at smom[s kChunks + k]
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int ch = lane + 64 * r;
+      const int s2 = ch / kChunks;
+      const int cs = __shfl(cl, s2 < kMaxS ? s2 : 0);
+      if (s2 < S && cs >= 0)
+        smom[ch] = reinterpret_cast<const uint4*>(mw + (int64_t)cs * kStride)[ch - s2 * kChunks];
+    }
+    __builtin_amdgcn_wave_barrier();
+    // slices without an entry this round evaluate slice 0's and add nothing
+    const int cme = __shfl(cl, sl);
+    const int c0 = __shfl(cl, 0);  // valid in every round
+    const bool ok = cme >= 0;
+    const int c = ok ? cme : c0;
+    double nx = A.c_centre[3 * c], ny = A.c_centre[3 * c + 1], nz = A.c_centre[3 * c + 2];
+    if (PER) {
+      const int ime = __shfl(il, sl), i0m = __shfl(il, 0);
+      double tx, ty, tz;
+      image_shift(ok ? ime : i0m, A.side, tx, ty, tz);
+      nx += tx;
+      ny += ty;
+      nz += tz;
+    }
+    const double inv_s = ldexp(A.inv_side, (int)A.c_level[c]);
+    const T w = (T)inv_s;
+    const double es = A.rule.eps * inv_s;
+    const T* M = reinterpret_cast<const T*>(smom) + (ok ? sl : 0) * kStride;
+    T a[4] = {T(0), T(0), T(0), T(0)};
+    Op::template cart<P>(hot_fma(me.x, w, (T)((gx - nx) * inv_s)),
+                         hot_fma(me.y, w, (T)((gy - ny) * inv_s)),
+                         hot_fma(me.z, w, (T)((gz - nz) * inv_s)), (T)(es * es), b, M, a);
+#pragma unroll
+    for (int d = 0; d < NC; ++d) kahan_scaled(sum[d], com[d], a[d], ok ? Op::scale(d, w) : T(0));
+  }
+  // add the slices' compensated sums across lanes
+  for (int m = 32; m >= (1 << lw); m >>= 1) {
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {
+      const T o = __shfl_xor(sum[d], m), oc = __shfl_xor(com[d], m);
+      kahan_add(sum[d], com[d], o);
+      com[d] += oc;
+    }
+  }
+  if (active && sl == 0) {
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {
+      st[d] = sum[d];
+      st[4 + d] = com[d];
+    }
+  }
+}
+
 // ------------------------------------------------------------------ launches
+// whether launch_expand takes k_expand_sl (and Coef::w)
+template <class Op>
+inline bool cart_items(const hot_tree* t) {
+  return !Op::fits(t->p) && t->list_p < 0 && !t->bg && t->n_munits_tiny > 0 &&
+         t->n_munits_tiny * 10 >= t->n_munits;
+}
+// whether nothing else is taken: the harmonic coefficients are not read then
+template <class Op>
+inline bool cart_only(const hot_tree* t) {
+  return cart_items<Op>(t) && t->n_munits_tiny == t->n_munits;
+}
+
 inline ListArgs list_args(const hot_tree* t, const NewtonRule& rule) {
   ListArgs A;
   A.units = nullptr;
@@ -530,8 +713,9 @@ inline ListArgs list_args(const hot_tree* t, const NewtonRule& rule) {
 
 // The expansion terms of every item added to state. Theta lists without
 // background subtraction where items of at most 32 sinks make a tenth of the
-// units or more: those with a cell per lane, the others with a sink per lane
-// (Op::any_size: all with a cell per lane).
+// units or more: those with a cell per lane, or by slices where the coefficients
+// exceed the registers, the others with a sink per lane (Op::any_size: all with a
+// cell per lane).
 template <int P, typename T, class Op>
 void launch_expand(hot_ctx* ctx, const hot_tree* t, const V4<T>* off, const V4<T>* bar,
                    const Coef<T>& cf, double eps, T* state) {
@@ -555,13 +739,20 @@ void launch_expand(hot_ctx* ctx, const hot_tree* t, const V4<T>* off, const V4<T
     // potentials are refused with background subtraction: no variant for them
     if constexpr (Op::NC == 3) go(k_expand<P, T, Op, false, true, true>, 0, all, W);
   } else {
-    int64_t cl = 0;  // units that take a cell per lane
+    int64_t cl = 0;  // units that do not take a sink per lane
     if constexpr (Op::fits(P)) {
       cl = Op::any_size ? all : small * 10 >= all ? small : 0;
       if (t->periodic)
         go(k_expand_cl<P, T, Op, true>, 0, cl, 1);
       else
         go(k_expand_cl<P, T, Op, false>, 0, cl, 1);
+    } else if (cart_items<Op>(t)) {
+      cl = t->n_munits_tiny;
+      A.units = t->munits.as<int4>();
+      A.n_units = cl;
+      auto kern = t->periodic ? k_expand_sl<P, T, Op, true> : k_expand_sl<P, T, Op, false>;
+      kern<<<(unsigned)cl, 64, 0, ctx->stream>>>(A, cf.w, off, bar, state, t->unit_part.as<T>());
+      HOT_CHECK_LAUNCH();
     }
     if (t->periodic)
       go(k_expand<P, T, Op, false, true, false>, cl, all - cl, W);

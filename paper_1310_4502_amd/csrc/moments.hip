@@ -14,6 +14,8 @@
 
 namespace hot {
 
+static __constant__ AlphaTable kAlpha = make_alpha_table();
+
 namespace {
 
 constexpr int kB = 256;
@@ -202,6 +204,26 @@ __global__ __launch_bounds__(kB) void k_m2m(int64_t c0, int64_t c1, const int32_
   }
 }
 
+// weighted moments scaled by the cell side, rows padded with zeros
+template <typename T>
+__global__ void k_weighted(const double* __restrict__ mom, int64_t C,
+                           const int8_t* __restrict__ c_level, double inv_side, int p,
+                           T* __restrict__ out) {
+  const int nmv = nm(p), stride = nm_pad(p);
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t c;
+  int s;
+  row_col(t, stride, c, s);
+  if (c >= C) return;
+  if (s >= nmv) {
+    out[c * stride + s] = T(0);
+    return;
+  }
+  const int order = kAlpha.a[s] + kAlpha.b[s] + kAlpha.c[s];
+  const double sc = pow2_pow(ldexp(inv_side, (int)c_level[c]), order);
+  out[c * stride + s] = (T)(kAlpha.w[s] * (mom[c * nmv + s] * sc));
+}
+
 // Solid-harmonic coefficients of every cell (gen_harmonics.py), one thread per
 // cell and order, the orders of a run of cells on one XCD so that its L2 holds
 // their moments. SRC 0: the matter's moments; 1: minus the cell's uniform cube
@@ -336,6 +358,7 @@ void build_moments(hot_ctx* ctx, hot_tree* t, const double* pos, const double* m
   launch_harmonics<float, 0>(ctx, t, t->hc32.as<float>(), t->tc32.as<float>(),
                              t->c_reach.as<float>());
   t->harm64_valid = false;
+  t->mw64_valid = false;
 }
 
 void harmonics_fp64(hot_ctx* ctx, hot_tree* t) {
@@ -344,6 +367,23 @@ void harmonics_fp64(hot_ctx* ctx, hot_tree* t) {
   launch_harmonics<double, 0>(ctx, t, t->hc64.as<double>(), t->tc64.as<double>(), nullptr);
   t->harm64_valid = true;
 }
+
+template <typename T>
+static void launch_weighted(hot_ctx* ctx, hot_tree* t, DBuf& w) {
+  const int64_t tot = t->n_cells * nm_pad(t->p);
+  w.alloc(ctx, (size_t)tot * sizeof(T));
+  k_weighted<T><<<grid_for(tot, kB), kB, 0, ctx->stream>>>(
+      t->mom64.as<double>(), t->n_cells, t->c_level.as<int8_t>(), 1.0 / t->side, t->p, w.as<T>());
+  HOT_CHECK_LAUNCH();
+}
+
+void weighted_fp64(hot_ctx* ctx, hot_tree* t) {
+  if (t->mw64_valid) return;
+  launch_weighted<double>(ctx, t, t->mw64);
+  t->mw64_valid = true;
+}
+
+void weighted_fp32(hot_ctx* ctx, hot_tree* t, DBuf& w) { launch_weighted<float>(ctx, t, w); }
 
 void harmonics_sub(hot_ctx* ctx, hot_tree* t, bool fp64) {
   alloc_harmonics(ctx, t, t->hsub, t->tsub, fp64 ? sizeof(double) : sizeof(float));

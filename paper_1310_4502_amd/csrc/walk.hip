@@ -863,7 +863,7 @@ void build_pair_segs(hot_ctx* ctx, hot_tree* t) {
   HOT_CHECK_LAUNCH();
   int64_t* so = t->pseg_off.as<int64_t>();
   scan_i64(ctx, so, so, G, so + G);
-  int64_t ns = 0, hu[3] = {0, 0, 0};
+  int64_t ns = 0, hu[4] = {0, 0, 0, 0};
   unsigned fl = 0;
   DBuf units;
   Readback rb(ctx);

@@ -144,3 +144,40 @@ def test_mixed_potential_of_low_orders(n_group, p):
     ref = t.eval_forces(x, m, 1e-5, HOT_FP64, with_pot=True)[1].cpu().numpy()
     pot = t.eval_forces(x, m, 1e-5, HOT_MIXED, with_pot=True)[1].cpu().numpy()
     assert rel(pot, ref) <= 2.0 ** -25, rel(pot, ref)
+
+
+# widths of a slice: 8 lanes up to 8 sinks, 16 to 16, 32 to 32; 33 and more: no slices
+@pytest.mark.parametrize("n_group", [1, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("p", [4, 5, 7, 8])
+@pytest.mark.parametrize("kernel,periodic", [("plummer", False), ("plummer", True), ("k1", False)])
+def test_small_items_of_high_orders(orc, n_group, p, kernel, periodic):
+    """Orders whose coefficients no lane can hold (FP64 fields from 5, FP64
+    Jacobians from 4, FP32 ones from 7): slices of a wavefront. To the bounds of
+    the other item sizes."""
+    n = 1200
+    pos = W.uniform(n, 31)
+    mass = np.random.default_rng(4).uniform(0.5, 1.5, n) / n
+    bar = W.cotangent(n, 3)
+    box = (0.0, 0.0, 0.0, 1.0)
+    ot = orc.Tree(pos, min(8, n_group), n_group, box)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, min(8, n_group), n_group, box)
+    for u in (ot, t):
+        if periodic:
+            u.build_lists_periodic(0.6, 0) if u is ot else u.build_interaction_lists_periodic(0.6, 0)
+        else:
+            u.build_lists(0.6, 0) if u is ot else u.build_interaction_lists(0.6, 0)
+    ot.compute_moments(pos, mass, p)
+    t.compute_moments(x, m, p)
+    eps = 0.02
+    oa, oph, _ = ot.eval(pos, mass, eps, kernel=kernel)
+    ox, om = ot.vjp(pos, mass, eps, bar, kernel=kernel)
+    for prec, tol in ((HOT_FP64, 1e-12), (HOT_MIXED, 1e-5)):
+        a, ph, _ = t.eval_forces(x, m, eps, prec, with_pot=True, kernel=kernel)
+        gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True, kernel=kernel)
+        # periodic fields are differences of the images' much larger ones
+        w = tol * (10 if periodic else 1)
+        assert rel(a.cpu().numpy(), oa) <= w
+        assert rel(ph.cpu().numpy(), oph) <= w * (100 if periodic else 1)
+        assert rel(gx.cpu().numpy(), ox) <= w * (10 if prec == HOT_MIXED else 1)
+        assert rel(gm.cpu().numpy(), om) <= w * (10 if prec == HOT_MIXED else 1)
