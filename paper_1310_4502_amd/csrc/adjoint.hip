@@ -824,7 +824,7 @@ __global__ void k_src_unit_sum(const int2* __restrict__ items, int64_t n_items,
 // lane accumulates sum_k abar_k d^(alpha+e_k) G for all alpha in registers; the
 // item's partial sums are reduced across lanes with a fixed butterfly.
 // P: the expansion order of the item's records. The block's item is
-// list[*first + block], below *last; its records end at citem_end (MIXQ, lists
+// list[*first + block], below *last (or item, list[], base + block); its records end at citem_end (MIXQ, lists
 // with per-entry orders) or with the run of its cell. The row is written with
 // stride out_stride, zero-filled from nm(P) up to out_nm (the cell's full moment
 // count).
@@ -839,7 +839,7 @@ template <int P, typename T, bool MIXQ, bool PER, bool K1, bool NEWTON>
 __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p_cell_adj(
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ first,
-    const uint32_t* __restrict__ last, const uint32_t* __restrict__ citem_rec, const int32_t* __restrict__ citem_cell,
+    const uint32_t* __restrict__ last, uint32_t base, const uint32_t* __restrict__ citem_rec, const int32_t* __restrict__ citem_cell,
     const uint32_t* __restrict__ crec_off, const uint32_t* __restrict__ citem_end, int out_stride,
     int out_nm,
     const uint64_t* __restrict__ mkey, double side, const uint32_t* __restrict__ mval,
@@ -850,9 +850,9 @@ __attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p
   constexpr int NM = nm(P);
   constexpr int NR = NEWTON ? 1 + 3 * P * P : NM;  // accumulated per lane
   const int lane = threadIdx.x;
-  const uint32_t at = *first + blockIdx.x;
-  if (at >= *last) return;
-  const int64_t it = (int64_t)list[at];
+  const uint32_t at = (first ? *first : base) + blockIdx.x;
+  if (last && at >= *last) return;
+  const int64_t it = list ? (int64_t)list[at] : (int64_t)at;
   const int c = citem_cell[it];
   const uint32_t r0 = citem_rec[it];
   uint32_t r1;
@@ -970,6 +970,7 @@ __attribute__((amdgpu_waves_per_eu(cell_adj_waves_per_simd<P, T>()))) void k_m2p
     __syncthreads();
     for (int a = lane; a < NM; a += 64) {
       T t = T(0);
+#pragma unroll 4
       for (int j = kRows.start[a]; j < kRows.start[a + 1]; ++j)
         t = hot_fma((T)kRows.val[j], s_h[kRows.idx[j]], t);
       o[a] = t;
@@ -1360,67 +1361,83 @@ void launch_expansion_cell_adj(hot_ctx* ctx, hot_tree* t, const V4<T>* off, cons
   tmark(ctx, HOT_T_ADJ_M2P_CELL, false);
   const int64_t NI = t->n_citems;
   if (NI > 0) {
-    // the items by class, the counts left on the device: both classes launch a
-    // block per item, those past their class's end return at once
-    DBuf flag, pos_y, pos_n, yes, no;
-    flag.alloc(ctx, (size_t)NI * sizeof(uint32_t));
-    pos_y.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
-    pos_n.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
-    yes.alloc(ctx, (size_t)NI * sizeof(uint32_t));
-    no.alloc(ctx, (size_t)NI * sizeof(uint32_t));
-    group_radius<T>(ctx, t, off);
-    // there are no trace parts below order 2 or without softening
-    const SourceRule rule{eps, P < 2 || eps == 0.0 ? -1.0 : kNewtonCS * eps * eps / newton_tol<T>(),
-                          t->c_bmax.as<double>()};
+    // Two classes of items where the Newtonian form's gain per sink outweighs the
+    // turn into raw moments, once per item, and the flags: from 768 sinks in the mean
+    // item at orders 7 and 8, 1024 at 6, 2048 at 3 to 5 and for lists of mixed orders.
+    // 48^3 grid, all items Cartesian against two classes, ms: order 4, 12 or 27 sinks a
+    // group (some 500, 1000 an item) 0.28, 0.24 against 0.39, 0.28, order 6 0.57, 0.50
+    // against 0.69, 0.55; order 8, 12 sinks 1.14 against 1.26; periodic, 27 sinks 2.10
+    // against 1.86, K1 1.18 against 1.00; error-bound lists, 27 sinks 0.72 against 0.98.
+    // Below order 3 the Newtonian row is the longer one.
+    const double sinks = (double)t->n_mrec / (double)NI * ((double)t->n / (double)t->n_groups);
+    const bool classes =
+        P >= 3 && sinks >= (mixq || P < 6 ? 2048.0 : P == 6 ? 1024.0 : 768.0);
     const uint32_t* qi = mixq ? t->qitems.as<uint32_t>() : nullptr;
-    auto fk = mixq ? (t->periodic ? k_citem_flag<true, true, K1> : k_citem_flag<true, false, K1>)
-                   : (t->periodic ? k_citem_flag<false, true, K1> : k_citem_flag<false, false, K1>);
-    fk<<<grid_for(NI, kWPB), kB, 0, st>>>(
-        NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
-        t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
-        t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
-        t->g_rad.as<float>(), rule, flag.as<uint32_t>());
-    HOT_CHECK_LAUNCH();
-    uint32_t* py = pos_y.as<uint32_t>();
-    uint32_t* pn = pos_n.as<uint32_t>();
-    scan_u32(ctx, flag.as<uint32_t>(), py, NI, py + NI);
-    k_citem_split<<<grid_for(NI + 1, kB), kB, 0, st>>>(NI, qi, flag.as<uint32_t>(), py,
-                                                       yes.as<uint32_t>(), no.as<uint32_t>(), pn);
-    HOT_CHECK_LAUNCH();
-    // list positions [a, b)
+    // the classes' items and, at every list position, their numbers before it (left on
+    // the device: both launch a block per item, those past their class's end return)
+    DBuf flag, pos_y, pos_n, yes, no;
+    if (classes) {
+      flag.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+      pos_y.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
+      pos_n.alloc(ctx, (size_t)(NI + 1) * sizeof(uint32_t));
+      yes.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+      no.alloc(ctx, (size_t)NI * sizeof(uint32_t));
+      group_radius<T>(ctx, t, off);
+      // nothing is left out without softening
+      const SourceRule rule{eps, eps == 0.0 ? -1.0 : kNewtonCS * eps * eps / newton_tol<T>(),
+                            t->c_bmax.as<double>()};
+      auto fk = mixq
+                    ? (t->periodic ? k_citem_flag<true, true, K1> : k_citem_flag<true, false, K1>)
+                    : (t->periodic ? k_citem_flag<false, true, K1> : k_citem_flag<false, false, K1>);
+      fk<<<grid_for(NI, kWPB), kB, 0, st>>>(
+          NI, qi, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
+          t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), t->mrec_key.as<uint64_t>(),
+          t->side, t->mrec_val.as<uint32_t>(), t->g_cell.as<int32_t>(), t->c_centre.as<double>(),
+          t->g_rad.as<float>(), rule, flag.as<uint32_t>());
+      HOT_CHECK_LAUNCH();
+      uint32_t* py = pos_y.as<uint32_t>();
+      scan_u32(ctx, flag.as<uint32_t>(), py, NI, py + NI);
+      k_citem_split<<<grid_for(NI + 1, kB), kB, 0, st>>>(
+          NI, qi, flag.as<uint32_t>(), py, yes.as<uint32_t>(), no.as<uint32_t>(),
+          pos_n.as<uint32_t>());
+      HOT_CHECK_LAUNCH();
+    }
+    // list positions [a, b), all of them (ends null) or those of a class
     auto cell = [&](auto kern, const uint32_t* list, const uint32_t* ends, int64_t a, int64_t b) {
       if (b <= a) return;
       kern<<<(unsigned)(b - a), 64, 0, st>>>(
-          list, ends + a, ends + b, t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
+          list, ends ? ends + a : nullptr, ends ? ends + b : nullptr, (uint32_t)a,
+          t->citem_rec.as<uint32_t>(), t->citem_cell.as<int32_t>(),
           t->mcell_rec.as<uint32_t>(), t->citem_end.as<uint32_t>(), nm_pad(P), nm(P),
           t->mrec_key.as<uint64_t>(), t->side, t->mrec_val.as<uint32_t>(),
           t->c_level.as<int8_t>(), t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
           t->g_cell.as<int32_t>(), t->c_centre.as<double>(), off, ab, inv_side, eps, part.as<T>());
       HOT_CHECK_LAUNCH();
     };
-    const uint32_t *ly = yes.as<uint32_t>(), *ln = no.as<uint32_t>();
+    // both classes of the order-Q items
+    auto order = [&](auto mixq_c, auto q_c, int64_t a, int64_t b) {
+      constexpr bool MQ = decltype(mixq_c)::value;
+      constexpr int Q = decltype(q_c)::value;
+      if constexpr (P >= 3) {
+        if (classes)
+          cell(t->periodic ? k_m2p_cell_adj<Q, T, MQ, true, K1, true>
+                           : k_m2p_cell_adj<Q, T, MQ, false, K1, true>,
+               yes.as<uint32_t>(), pos_y.as<uint32_t>(), a, b);
+      }
+      cell(t->periodic ? k_m2p_cell_adj<Q, T, MQ, true, K1, false>
+                       : k_m2p_cell_adj<Q, T, MQ, false, K1, false>,
+           classes ? no.as<uint32_t>() : qi, pos_n.as<uint32_t>(), a, b);
+    };
     if (mixq) {
       // one launch per order present: each kernel holds only its order's row
       const int64_t* qo = t->qitem_off;
-#define HOT_CELL_Q(Q)                                                                    \
-  if constexpr (Q <= P) {                                                                \
-    if (t->periodic) {                                                                   \
-      cell(k_m2p_cell_adj<Q, T, true, true, K1, true>, ly, py, qo[Q], qo[Q + 1]);        \
-      cell(k_m2p_cell_adj<Q, T, true, true, K1, false>, ln, pn, qo[Q], qo[Q + 1]);       \
-    } else {                                                                             \
-      cell(k_m2p_cell_adj<Q, T, true, false, K1, true>, ly, py, qo[Q], qo[Q + 1]);       \
-      cell(k_m2p_cell_adj<Q, T, true, false, K1, false>, ln, pn, qo[Q], qo[Q + 1]);      \
-    }                                                                                    \
-  }
+#define HOT_CELL_Q(Q) \
+  if constexpr (Q <= P) order(std::true_type{}, std::integral_constant<int, Q>{}, qo[Q], qo[Q + 1]);
       HOT_CELL_Q(0) HOT_CELL_Q(1) HOT_CELL_Q(2) HOT_CELL_Q(3) HOT_CELL_Q(4) HOT_CELL_Q(5)
       HOT_CELL_Q(6) HOT_CELL_Q(7) HOT_CELL_Q(8)
 #undef HOT_CELL_Q
-    } else if (t->periodic) {
-      cell(k_m2p_cell_adj<P, T, false, true, K1, true>, ly, py, 0, NI);
-      cell(k_m2p_cell_adj<P, T, false, true, K1, false>, ln, pn, 0, NI);
     } else {
-      cell(k_m2p_cell_adj<P, T, false, false, K1, true>, ly, py, 0, NI);
-      cell(k_m2p_cell_adj<P, T, false, false, K1, false>, ln, pn, 0, NI);
+      order(std::false_type{}, std::integral_constant<int, P>{}, 0, NI);
     }
   }
   const int64_t tot = C * nm(P);

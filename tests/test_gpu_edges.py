@@ -169,3 +169,32 @@ def test_gradients_of_massless_and_light_particles(orc, p, eps, lists):
         # per unit mass, so that light particles count
         assert_sinks(gx[light] / mass[light, None], ox[light] / mass[light, None], tol, "light")
         assert not gx[(mass == 0)].any()
+
+
+@pytest.mark.parametrize("p,eps", [(3, 2e-5), (4, 0.0), (6, 2e-5), (8, 2e-5), (8, 1e-6)])
+def test_massless_sources_of_large_items(orc, p, eps):
+    """Cell items of more than 2048 sinks on average, whose cotangents the Newtonian
+    form takes where it may (smaller ones are all Cartesian): a third of the
+    particles massless."""
+    n, n_group, theta = 6000, 130, 0.85
+    rng = np.random.default_rng(8)
+    pos = W.uniform(n, 6)
+    mass = np.where(rng.random(n) < 1 / 3, 0.0, 1.0 / n)
+    mass[pos[:, 2] < 0.3] = 0.0
+    bar = W.cotangent(n, 5)
+    box = (0.0, 0.0, 0.0, 1.0)
+    ot = orc.Tree(pos, n_group, n_group, box)
+    ot.build_lists(theta, 0)
+    ot.compute_moments(pos, mass, p)
+    ox, om = ot.vjp(pos, mass, eps, bar)
+    x, m, b = (torch.from_numpy(v).cuda() for v in (pos, mass, bar))
+    t = Tree(x, n_group, n_group, box)
+    t.build_interaction_lists(theta, 0)
+    t.compute_moments(x, m, p)
+    records = np.bincount(t.lists()[3])
+    sinks = records.sum() / np.ceil(records / 48).sum() * n / t.counts()["n_groups"]
+    assert sinks >= 2048
+    for prec, tol in ((HOT_FP64, 1e-11), (HOT_MIXED, 1e-3)):
+        gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True)
+        assert_sinks(gm.cpu().numpy(), om, tol, "mass gradient")
+        assert_sinks(gx.cpu().numpy(), ox, tol, "position gradient")
