@@ -1570,6 +1570,7 @@ void adjoint_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass,
   // the transposed lists (source side) are built beside the sink-side work
   TransposeAside aside(ctx, !t->has_transpose);
   DBuf off, ab, ab3, sink, src, mbar64, spos, smass, xb, mb;
+  unit_room<T>(ctx, t);
   off.alloc(ctx, n * sizeof(V4<T>));
   ab.alloc(ctx, n * sizeof(V4<T>));
   ab3.alloc(ctx, n * sizeof(V4<T>));

@@ -313,7 +313,7 @@ struct hot_tree {
   // others. pslots, mslots: what the partial
   // sums of the divided items' units are added up from, (item, slot, units)
   // for an item's first slot, units = 0 for the others; unit_part: 64 sinks x
-  // 8 sums per slot, of either kind (FP64 room)
+  // 8 sums per slot, of either kind (unit_room)
   int64_t n_punits = 0, n_munits = 0, n_munits_tiny = 0, n_munits_small = 0, n_pslots = 0, n_mslots = 0;
   hot::DBuf punits, munits, pslots, mslots, unit_part;
   // per group, the largest distance of its particles from its centre, filled by

@@ -366,8 +366,7 @@ void build_units(hot_ctx* ctx, hot_tree* t, const DBuf& sc, const int64_t* h) {
   t->g_rad.alloc(ctx, (size_t)t->n_groups * sizeof(float));
   t->pslots.alloc(ctx, room(t->n_pslots));
   t->mslots.alloc(ctx, room(t->n_mslots));
-  t->unit_part.alloc(ctx, (size_t)std::max<int64_t>(1, std::max(t->n_pslots, t->n_mslots)) *
-                              kUnitSums * sizeof(double));
+  unit_room<float>(ctx, t);
   k_unit_fill<<<grid_for(NI, kB), kB, 0, ctx->stream>>>(
       t->items.as<int2>(), NI, t->n_groups, t->g_first.as<int32_t>(), t->g_count.as<int32_t>(),
       t->pseg_off.as<int64_t>(), t->m2p_off.as<int64_t>(), sc.as<int64_t>(),
@@ -405,6 +404,7 @@ void forces_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* mass, 
     state_buf.alloc(ctx, n * 8 * sizeof(T));
     state = state_buf.as<T>();
   }
+  unit_room<T>(ctx, t);
   zero_flag_word(ctx, kFlagMass);
   k_offsets<T><<<grid_for(n, kB), kB, 0, st>>>(pos, mass, t->perm.as<uint32_t>(),
                                                t->group_of.as<int32_t>(), t->g_cell.as<int32_t>(),
@@ -477,6 +477,7 @@ void cube_field_t(hot_ctx* ctx, hot_tree* t, const double* pos, const double* ma
   const int64_t n = t->n;
   const int64_t nh = t->n_cells * harm_stride(t->p), nt = t->n_cells * trace_stride(t->p);
   DBuf off, state, zero, cube, tcube;
+  unit_room<T>(ctx, t);
   off.alloc(ctx, n * sizeof(V4<T>));
   state.alloc(ctx, n * 8 * sizeof(T));
   // one zero array serves both parts of the (absent) matter

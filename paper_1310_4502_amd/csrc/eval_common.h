@@ -358,6 +358,15 @@ __global__ __launch_bounds__(64) void k_unit_sum(const int4* __restrict__ slots,
   }
 }
 
+// Room for the partial sums of the divided items: 2 KB a slot in FP32, given with
+// the lists; 4 KB in FP64, on the first such call. unit_length allows at most about
+// a slot per item, or twice the wanted units on small sets (32 MB in FP32).
+template <typename T>
+inline void unit_room(hot_ctx* ctx, hot_tree* t) {
+  t->unit_part.alloc(ctx, (size_t)std::max<int64_t>(1, std::max(t->n_pslots, t->n_mslots)) *
+                              kUnitSums * sizeof(T));
+}
+
 // adds up the divided items' partial sums after a kernel over work units
 template <typename T, int NC, bool ADD>
 inline void sum_units(hot_ctx* ctx, const hot_tree* t, const DBuf& slots, int64_t n, T* state) {

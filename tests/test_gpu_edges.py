@@ -198,3 +198,27 @@ def test_massless_sources_of_large_items(orc, p, eps):
         gx, gm = t.eval_forces_adjoint(x, m, eps, b, prec, with_mass=True)
         assert_sinks(gm.cpu().numpy(), om, tol, "mass gradient")
         assert_sinks(gx.cpu().numpy(), ox, tol, "position gradient")
+
+
+def test_room_of_the_partial_sums():
+    """A tree's partial sums have FP32's room until an FP64 call needs twice that."""
+    n = 10000
+    pos = torch.from_numpy(W.plummer(n, 3)).cuda()
+    mass = torch.full((n,), 1.0 / n, dtype=torch.float64, device="cuda")
+    t = Tree(pos)
+    t.compute_moments(pos, mass, 4)
+    torch.cuda.synchronize()
+
+    def held():
+        return torch.cuda.memory_allocated()
+
+    before = held()
+    t.build_interaction_lists(0.6, 0)
+    lists = held() - before
+    assert lists < 15e6, lists  # 20 MB with FP64's room
+    acc = torch.empty_like(pos)
+    before = held()
+    t.eval_forces(pos, mass, 1e-4, HOT_MIXED, out=acc)
+    assert held() == before
+    t.eval_forces(pos, mass, 1e-4, HOT_FP64, out=acc)
+    assert held() > before
