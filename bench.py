@@ -54,11 +54,6 @@ def nm(p):
     return (p + 1) * (p + 2) * (p + 3) // 6
 
 
-def comb(n, k):
-    from math import comb as c
-    return c(n, k)
-
-
 # Algorithmic FP32 operations per interaction (FMA = 2, reciprocal square
 # root = 1), from the formulas each kernel evaluates, independent of how the
 # code is written:
@@ -75,16 +70,14 @@ def comb(n, k):
 #    cotangent (1 FMA): 33;
 #  expansion adjoint, sink side: the same with the 5 (2l - 3) second-derivative
 #    coefficients per degree, and the Hessian times abar;
-#  expansion adjoint, cell side: the basis and the (p + 1)^2 harmonic cotangents.
+#  expansion adjoint, cell side: the basis and the 1 + 3 p^2 harmonic cotangents.
 # The expansion counts are those of the generated expressions by order, in the
-# Newtonian form that nearly every entry takes; the softened form of the close
-# entries (1569, 2120 operations at p = 8) is not counted, so the rates
-# reported are lower bounds where it is used.
+# Newtonian form (gen_harmonics.flops, which a test holds them to); the softened
+# form of the close entries (1249, 1913 operations at p = 8) is not counted, so
+# the rates reported are lower bounds where it is used.
 FLOPS_P2P = 20
 FLOPS_P2P_SINK_ADJ = 28
 FLOPS_P2P_SRC_ADJ = 33
-
-
 FLOPS_M2P = (16, 38, 67, 118, 188, 276, 382, 506, 648)
 FLOPS_M2P_SINK_ADJ = (32, 60, 204, 262, 350, 465, 606, 773, 966)
 FLOPS_M2P_CELL_ADJ = (18, 34, 62, 112, 181, 268, 373, 496, 637)

@@ -323,8 +323,8 @@ __global__ void k_cq_items(const uint32_t* __restrict__ bnd, const uint32_t* __r
 }
 
 // ------------------------------------------------------------------- gathers
-template <typename T>
 // sorted cotangents, and three times them for the source-side pair kernel
+template <typename T>
 __global__ void k_abar(const double* __restrict__ abar, const uint32_t* __restrict__ perm,
                        int64_t n, V4<T>* __restrict__ ab, V4<T>* __restrict__ ab3) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -534,7 +534,6 @@ __global__ __launch_bounds__(kB) void k_p2p_sink_adj(
   }
 }
 
-// ------------------------------------------------- expansion terms, sink side
 // ----------------------------------------------------- pair terms, source side
 // One wavefront per source item (at most 64 particles of one group). The
 // records of the item are sorted by sink group; runs of one group are merged
@@ -1345,7 +1344,6 @@ void build_transpose(hot_ctx* ctx, hot_tree* t) {
   t->has_transpose = true;
 }
 
-// expansion terms, sink side (needs no transposed lists)
 // expansion terms, the moment cotangents (cell side, on the transposed
 // lists), then down the tree
 template <int P, typename T, bool K1>

@@ -11,8 +11,9 @@
 // wavefront-uniform, so its data arrives through scalar loads shared by all
 // 64 sinks. The interaction vector of a sink is written back once per
 // kernel (the paper's multi-stage write-back), with compensated (Kahan)
-// accumulation in mixed precision: one compensated add per expansion entry
-// and per block of at least kSumRun pair-summed sources.
+// accumulation in mixed precision: one compensated add per block of at least
+// kSumRun pair-summed sources and per expansion entry (a cell per lane: 64 entries
+// summed in FP64).
 //
 // Mixed precision: every position enters as an FP32 offset from its own
 // group's FP64 centre; the FP64 difference of two centres is formed once per

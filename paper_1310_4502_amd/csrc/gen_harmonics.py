@@ -195,10 +195,6 @@ def size_grad(l):
     return 1 if l == 0 else 3 * (2 * l - 1)
 
 
-def size_t(p):
-    return sum(size_grad(n - 2 * k) for n in range(2, p + 1) for k in range(1, n // 2 + 1))
-
-
 def off_hh(l):
     return {0: 0, 1: 1}.get(l, 4 + 5 * (l - 2) ** 2)
 
@@ -215,10 +211,6 @@ def off_th(l, k):
                 return o
             o += size_hess(n - 2 * kk)
     raise KeyError((l, k))
-
-
-def size_th(p):
-    return sum(size_hess(n - 2 * k) for n in range(2, p + 1) for k in range(1, n // 2 + 1))
 
 
 def block_map(l, k, hess):
@@ -708,6 +700,30 @@ def gen_cell_newton(P):
     return L
 
 
+def flops(kind, P, softened=False):
+    """Operations of the emitted expression per sink and cell, without the
+    potential (kind "field", "jacobian" or "cell"; softened: the full form under
+    Plummer softening): a fused multiply-add 2, any other 1."""
+    gen = {"field": gen_fwd_full if softened else gen_fwd_newton,
+           "jacobian": gen_sink_full if softened else gen_sink_newton, "cell": gen_cell_newton}
+    n, skip, depth = 0, 0, 0
+    for line in gen[kind](P):
+        for st in line.split(";"):
+            t = st.strip()
+            opens = t.count("{") - t.count("}")
+            if not skip and t.startswith(("if constexpr (K1) {", "if constexpr (POT)")):
+                if opens == 0:
+                    break  # a statement of its own
+                skip = depth + 1
+            if not skip:
+                n += 2 * t.count("hot_fma(") + t.count("hot_rsq(")
+                n += sum(t.count(o) for o in (" * ", " + ", " - ", " += "))
+            depth += opens
+            if skip and depth < skip:
+                skip = 0
+    return n
+
+
 def dispatch(parts, head, gen):
     parts += head
     for P in range(PMAX + 1):
@@ -717,12 +733,7 @@ def dispatch(parts, head, gen):
 
 
 def main(path):
-    fa = ", ".join(str(size_t(p)) for p in range(PMAX + 1))
-    fb = ", ".join(str(size_th(p)) for p in range(PMAX + 1))
-    parts = ["// Generated by gen_harmonics.py -- do not edit.", "#pragma once", "namespace hot {", "",
-             "// coefficients of the trace parts up to order p (first and second derivatives)",
-             f"constexpr int kTraceGrad[] = {{{fa}}};",
-             f"constexpr int kTraceHess[] = {{{fb}}};", ""]
+    parts = ["// Generated by gen_harmonics.py -- do not edit.", "#pragma once", "namespace hot {", ""]
     dispatch(parts, ["template <int P, typename T, bool POT>",
                      "__device__ __forceinline__ void harm_fwd_newton(T X, T Y, T Z, T e2, "
                      "const T* __restrict__ C, T& ax, T& ay, T& az, T& ph) {"], gen_fwd_newton)
@@ -763,8 +774,11 @@ def main(path):
         parts += ["template <typename T>",
                   f"__device__ __forceinline__ void harm_hess_coef{n}(const double* M, double sc, "
                   "T* __restrict__ h, T* __restrict__ t) {"] + gen_coef(n, True) + ["}"]
-        parts += [f"__device__ __forceinline__ void harm_coefT{n}(const double* h, double* M) {{"] + \
-            gen_coefT(n) + ["}"]
+    # the transposed maps, for the host tests
+    parts.append("#ifndef __HIP__")
+    for n in range(PMAX + 1):
+        parts += [f"inline void harm_coefT{n}(const double* h, double* M) {{"] + gen_coefT(n) + ["}"]
+    parts.append("#endif")
     start, idx, val = gen_rows_table()
     parts += ["struct HarmRows {", f"  short start[{len(start)}];", f"  short idx[{len(idx)}];",
               f"  double val[{len(val)}];", "};",

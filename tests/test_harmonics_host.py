@@ -197,3 +197,17 @@ def test_newtonian_rules_of_the_derivatives(orc, shim, p, ratio):
             worst_s = max(worst_s, np.linalg.norm(S, 2) * d ** 3 / 2 / (unit * b * d))
             worst_m = max(worst_m, np.linalg.norm(left_out(M, R, e2)) * d * d / (unit * b * d))
     assert worst_h <= ch and worst_s <= cs and worst_m <= cs, (worst_h, worst_s, worst_m)
+
+
+def test_benchmark_counts_the_generated_operations():
+    """The operation counts of the benchmark's rates are those of the emitted
+    expressions (order 0 without the terms that vanish there)."""
+    sys.path.insert(0, CSRC)
+    sys.path.insert(0, ROOT)
+    import bench
+    import gen_harmonics as g
+    for p in range(9):
+        if p > 0:
+            assert bench.flops_m2p(p) == g.flops("field", p)
+        assert bench.flops_m2p_sink_adj(p) == g.flops("jacobian", p)
+        assert bench.flops_m2p_cell_adj(p) == g.flops("cell", p)
