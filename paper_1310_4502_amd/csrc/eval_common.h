@@ -184,16 +184,16 @@ __device__ __forceinline__ T fold16(T a, T b) {
 template <typename T>
 struct Fold;
 // The four blocks of v_mfma_f64_4x4x4: lane 16 k + 4 b + i holds entry (i, k) of block
-// b as the left, (k, i) as the right operand and as the result. Each value times a
-// column of ones leaves its sums over k in that column, ones times those the block's
-// sums; the blocks, quads of a row of lanes, are then added.
+// b as the left, (k, i) as the right operand and as the result. A value times ones
+// leaves its sums over k, of which column u is kept for sink u (selected, not
+// multiplied: one sink's infinity stays its own); ones times those the block's sums;
+// the blocks, quads of a row of lanes, are then added.
 template <>
 struct Fold<float> {
   double t = 0.0;
   __device__ __forceinline__ void put(int u, float v) {
-    int q = (int)threadIdx.x & 3;
-    asm("" : "+v"(q));  // the columns are made where they are used: no registers for four
-    t = __builtin_amdgcn_mfma_f64_4x4x4f64((double)v, q == u ? 1.0 : 0.0, t, 0, 0, 0);
+    const double d = __builtin_amdgcn_mfma_f64_4x4x4f64((double)v, 1.0, 0.0, 0, 0, 0);
+    t = ((int)threadIdx.x & 3) == u ? d : t;
   }
   __device__ __forceinline__ double sum() const {
     double x = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, 0.0, 0, 0, 0);

@@ -222,3 +222,28 @@ def test_room_of_the_partial_sums():
     assert held() == before
     t.eval_forces(pos, mass, 1e-4, HOT_FP64, out=acc)
     assert held() > before
+
+
+@pytest.mark.parametrize("n_group", [7, 40])
+@pytest.mark.parametrize("prec,far", [(HOT_MIXED, 1e25), (HOT_FP64, 1e160)])
+def test_one_sinks_overflow_stays_its_own(n_group, prec, far):
+    """A particle moved so far that its own expansion terms overflow leaves the
+    sinks evaluated with it as they are (to 1e-5 of FP64 with the particle at a
+    distance that neither overflows nor pulls)."""
+    n = 1500
+    pos = W.uniform(n, 41)
+    x = torch.from_numpy(pos).cuda()
+    m = torch.full((n,), 1.0 / n, dtype=torch.float64, device="cuda")
+    t = Tree(x, min(8, n_group), n_group, (0.0, 0.0, 0.0, 1.0))
+    t.build_interaction_lists(0.6, 0)
+    for p in (2, 4, 8):
+        t.compute_moments(x, m, p)
+        moved, mild = x.clone(), x.clone()
+        moved[::97] *= far
+        mild[::97] *= 1e6
+        ref = t.eval_forces(mild, m, 0.02, HOT_FP64)[0].cpu().numpy()
+        a = t.eval_forces(moved, m, 0.02, prec)[0].cpu().numpy()
+        stay = np.ones(n, bool)
+        stay[::97] = False
+        assert np.isfinite(a[stay]).all()
+        assert rel(a[stay], ref[stay]) <= 1e-5
