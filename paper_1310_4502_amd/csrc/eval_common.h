@@ -178,9 +178,10 @@ __device__ __forceinline__ T fold16(T a, T b) {
 // that here() names; sink(lane) is the one a lane keeps. The 64 terms enter a
 // compensated sum with one add, so their own sum carries no rounding of T: FP32
 // terms are summed in FP64, on the matrix cores as far as the layout reaches (the
-// forces of a 4.1 M grid of 16-sink items at order 8 take 51.5 ms, 49.0 with plain
-// FP32 sums, whose error at order 2 is a tenth to a fifth larger), FP64 terms with
-// the rounding of every add kept.
+// forces of a 4.1 M grid of 16-sink items at order 8 take 48.5 ms, 50.1 with plain
+// FP32 sums, whose error at order 2 is a tenth to a fifth larger; potentials of a
+// 256 k Plummer set at order 4 2.53 and 2.41), FP64 terms with the rounding of every
+// add kept.
 template <typename T>
 struct Fold;
 // The four blocks of v_mfma_f64_4x4x4: lane 16 k + 4 b + i holds entry (i, k) of block
